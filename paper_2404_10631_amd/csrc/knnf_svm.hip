@@ -15,33 +15,55 @@
 // Every step is binary64; the probabilities are rounded once to binary32,
 // pixel-major with the class fastest (the layout the filter reads).
 //
-// Work shape: the cube is read once (4 B per pixel and band) and everything
-// else is per-pixel arithmetic, so the kernel is HBM-bound.  A block owns 256
-// consecutive pixels.  It stages the cube through LDS in chunks of 32 bands:
-// eight lanes cover one pixel's 128-byte piece of the chunk with 16-byte
-// loads.  The hyperplane weights of the chunk (M x 32 values) are staged
-// beside it.  Then each lane owns one pixel for the dot products (the weights
-// read as LDS broadcasts: read straight from memory at wave-uniform addresses
-// they became scalar loads whose waits lay on every wave's critical path) and
-// for the coupling iteration, whose sweep count differs from pixel to pixel.
-// The loads of the next chunk are in flight while the current one is used.
-// The fused variant (PC1 = true) also accumulates the PC1 projection from the
-// same chunks, so the pipeline's two steps before the filter read the cube
-// once.  knnf_svm on cubes whose pixel rows are not whole cache lines stages
-// linear runs of whole rows instead (svm_prob_lin_kernel).
+// Work shape: the cube is read once (4 B per pixel and band); the rest is
+// per-pixel binary64 arithmetic.  Step (i) is a matrix product, [pixels x
+// bands] by [bands x M], on the binary64 matrix instruction
+// (v_mfma_f64_4x4x4_4b: four blocks of 4 pixels x 4 bands x 4 hyperplanes).
+// It is used for its operand layout, not for its rate: on this chip it takes 16
+// cycles for 256 FMAs, the vector pipe's own binary64 rate, and does not
+// overlap with that pipe.  But a lane-per-pixel dot product needs every weight
+// in every lane, 8 bytes of LDS return bandwidth per FMA and lane (128 B/clk per
+// CU: 45k of the 65k cycles that the fused call on the 380 x 480 x 128 cube
+// took in that form); here a weight read from LDS serves 16 pixels.
+//   * A wavefront owns a tile of 64 pixels and goes through it in items of 16
+//     pixels x up to 128 bands: one contiguous span of memory, each cache line
+//     requested once.  A load takes two pixel rows, 32 lanes of 16-byte pieces
+//     (4 bands) each; up to 64 bands, four rows of 16.  Any band count from 4 on
+//     and any 4-byte alignment: the last piece of a pixel starts at bands - 4,
+//     and the bands that it repeats count as 0.  The next item's loads are
+//     issued before the current one is used.  (Two items in flight, persistent
+//     blocks of two to five tiles per wavefront, and blocks of 64, 128 and 512
+//     threads measured equal or slower.)
+//   * The item goes through a wavefront-private LDS buffer into the matrix
+//     operand layout (lane l: pixel l % 16 of a group of 16, piece l / 16 of a
+//     k-step of 16 bands; component e of the piece is the operand of matrix
+//     step e).  Loaded in that layout straight from memory, the lanes of a
+//     quarter wavefront touch 16 cache lines, and the first-level cache held
+//     the loads alone to 3.4 TB/s.
+//   * The weights of up to 128 bands are staged in LDS once per block, in
+//     operand order.
+//   * The sums go through LDS to one lane per pixel for the sigmoids and the
+//     coupling iteration, whose sweep count differs from pixel to pixel.
+// The fused variant (PC1 = true) carries the PC1 projection as one more column
+// of the product, so the pipeline's two steps before the filter read the cube
+// once.
+// What bounds it: 1000 x 1000 x 100, four classes, 84.5 us (105 us with the
+// lane-per-pixel product): the same kernel without its arithmetic takes 74 us
+// (5.6 TB/s, the rate of a plain read of the cube), the vector pipe is busy
+// for 50 us, and the two overlap only in part.  380 x 480 x 128 fused, 21 us
+// of kernel (27 us before), 17 us without the arithmetic.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
+#include <string.h>
 
 #include "knnf_device.h"
 
 namespace knnf {
 namespace {
 
-constexpr int SVM_THREADS = 256;              // pixels per block
-constexpr int SVM_CHUNK = 32;                 // bands per LDS stage
-constexpr int SVM_STRIDE = SVM_CHUNK + 4;     // LDS row stride (floats): conflict-free 16-byte reads
+constexpr int SVM_THREADS = 256;              // four wavefronts, a tile of 64 pixels each
+constexpr int SVM_TILE = 64;
 constexpr int SVM_SWEEPS = 100;
 constexpr double SVM_CLAMP = 1e-7;
 
@@ -51,10 +73,11 @@ __device__ __forceinline__ constexpr int pair_index(int i, int j) {
     return i * C - i * (i + 1) / 2 + (j - i - 1);
 }
 
-// Block-wide (min, max) of per-thread values -> pairs[2 * blockIdx.x ..].
+// Block-wide (min, max) of per-thread values -> pairs[2 * blockIdx.x ..];
+// lds: 2 NT / 64 doubles that no thread still uses.
 template <int NT>
-__device__ void svm_publish_minmax(double lo, double hi, double* pairs) {
-    __shared__ double slo[NT / 64], shi[NT / 64];
+__device__ void svm_publish_minmax(double lo, double hi, double* pairs, double* lds) {
+    double *slo = lds, *shi = lds + NT / 64;
     for (int m = 1; m < 64; m <<= 1) {
         lo = fmin(lo, __shfl_xor(lo, m));
         hi = fmax(hi, __shfl_xor(hi, m));
@@ -76,74 +99,37 @@ __device__ void svm_publish_minmax(double lo, double hi, double* pairs) {
 }
 
 // 1 / x in binary64 for the finite, normal x of the sigmoid and the coupling:
-// the hardware reciprocal refined by two Newton steps (an error of an ulp or
-// so, far below the 1e-6 the probabilities are held to, for a third of the
-// instructions of an IEEE division).
+// the hardware reciprocal (relative error e below 2^-20) corrected by 1 + e +
+// e^2 (an error of an ulp or so, far below the 1e-6 the probabilities are held
+// to, for a third of the instructions of an IEEE division).
 __device__ __forceinline__ double rcp64(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return fma(r, fma(-x, r, 1.0), r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
-// Weights of the chunk of bands c0 .. c0+31 for thread tid of NT: the M
-// hyperplanes, then (PC1) the band averages and the eigenvector, as (m, k)
-// = (e / 32, e % 32) with e = tid + NT * i; bands past the cube read as 0.
-template <int NT, int M, bool PC1>
-struct ChunkWeights {
-    static constexpr int NWT = (M + (PC1 ? 2 : 0)) * SVM_CHUNK;
-    static constexpr int NW = (NWT + NT - 1) / NT;  // per thread
-    double wv[NW];
-    __device__ __forceinline__ void fetch(int c0, int bands, const double* __restrict__ w,
-                                          const double* __restrict__ mean,
-                                          const double* __restrict__ vec) {
-#pragma unroll
-        for (int i = 0; i < NW; ++i) {
-            const int e = (int)threadIdx.x + NT * i;
-            const int m = e / SVM_CHUNK;
-            const int bb = c0 + (e % SVM_CHUNK);
-            double x = 0.0;
-            if (e < NWT && bb < bands)
-                x = m < M ? w[(int64_t)m * bands + bb] : (m == M ? mean[bb] : vec[bb]);
-            wv[i] = x;
-        }
-    }
-    __device__ __forceinline__ void stage(double* wl) const {
-#pragma unroll
-        for (int i = 0; i < NW; ++i) {
-            const int e = (int)threadIdx.x + NT * i;
-            if (e < NWT) wl[e] = wv[i];
-        }
-    }
-};
-
-// (i) for the bands c0 .. c0+nb-1 of one pixel, from its staged row (the
-// chunk's first band at row[0]) and the chunk's weights wl: the decision
-// values f and (PC1) the projection pj, band by band in ascending order.
-template <int M, bool PC1>
-__device__ __forceinline__ void svm_dot_chunk(const float* row, int nb, const double* wl,
-                                              double (&f)[M], double& pj) {
-    if (nb == SVM_CHUNK) {
-#pragma unroll
-        for (int k = 0; k < SVM_CHUNK / 4; ++k) {
-            const float4 x4 = *(const float4*)(row + 4 * k);
-            const double x[4] = {(double)x4.x, (double)x4.y, (double)x4.z, (double)x4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-#pragma unroll
-                for (int m = 0; m < M; ++m) f[m] = fma(wl[m * SVM_CHUNK + 4 * k + e], x[e], f[m]);
-                if constexpr (PC1)
-                    pj = fma(x[e] - wl[M * SVM_CHUNK + 4 * k + e], wl[(M + 1) * SVM_CHUNK + 4 * k + e],
-                             pj);
-            }
-        }
-    } else {
-        for (int k = 0; k < nb; ++k) {
-            const double x = (double)row[k];
-#pragma unroll
-            for (int m = 0; m < M; ++m) f[m] = fma(wl[m * SVM_CHUNK + k], x, f[m]);
-            if constexpr (PC1) pj = fma(x - wl[M * SVM_CHUNK + k], wl[(M + 1) * SVM_CHUNK + k], pj);
-        }
-    }
+// exp(z) for |z| <= 700: z = k ln 2 + r with |r| <= ln 2 / 2 (ln 2 in two
+// parts), and on that interval the degree-11 polynomial that interpolates exp
+// at Chebyshev points (relative error 1.6e-17 before rounding), by Horner's
+// rule.  The sigmoid's argument is capped to that range, so the special cases
+// of the library function (a third of its instructions) have no place.
+__device__ __forceinline__ double exp_capped(double z) {
+    const double k = __builtin_rint(z * 0x1.71547652b82fep+0);
+    double r = fma(k, -0x1.62e42fefa39efp-1, z);
+    r = fma(k, -0x1.abc9e3b39803fp-56, r);
+    double p = 0x1.af785e0dfd450p-26;
+    p = fma(p, r, 0x1.28b4063caeaedp-22);
+    p = fma(p, r, 0x1.71dde76a2d404p-19);
+    p = fma(p, r, 0x1.a01991aba4014p-16);
+    p = fma(p, r, 0x1.a01a01b80266fp-13);
+    p = fma(p, r, 0x1.6c16c187fc3f8p-10);
+    p = fma(p, r, 0x1.111111110db75p-7);
+    p = fma(p, r, 0x1.555555554f0ccp-5);
+    p = fma(p, r, 0x1.5555555555562p-3);
+    p = fma(p, r, 0x1.0000000000011p-1);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return __builtin_ldexp(p, (int)k);
 }
 
 // Steps (ii) and (iii) for one pixel: sigmoids of the decision values f,
@@ -155,12 +141,13 @@ __device__ __forceinline__ void svm_couple(const double (&f)[C * (C - 1) / 2],
                                            const double* __restrict__ B, float* o) {
     constexpr int M = C * (C - 1) / 2;
     // (ii) binary probabilities; r[m] is that of the pair's first class (z is
-    // capped where the clamp decides anyway, so 1 + exp(z) stays finite)
+    // capped where the clamp decides anyway, so exp(z) and 1 + exp(z) are
+    // finite and normal)
     double r[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const double z = fmin((f[m] + bias[m]) * A[m] + B[m], 700.0);
-        const double s = rcp64(1.0 + exp(z));
+        const double z = fmax(fmin(fma(f[m] + bias[m], A[m], B[m]), 700.0), -700.0);
+        const double s = rcp64(1.0 + exp_capped(z));
         r[m] = fmin(fmax(s, SVM_CLAMP), 1.0 - SVM_CLAMP);
     }
     // (iii) coupling.  Q[t][t] sums r_st^2 over s in ascending order;
@@ -184,12 +171,13 @@ __device__ __forceinline__ void svm_couple(const double (&f)[C * (C - 1) / 2],
         return t == j ? qtt[t] : t < j ? qo[pair_index<C>(t, j)] : qo[pair_index<C>(j, t)];
     };
 
-    // The sweep keeps Q p and p^T Q p up to date instead of recomputing
-    // them: the new p[t] equals p[t] + d with d = (p^T Q p - (Q p)[t]) / Q[t][t];
-    // before renormalising, Q p gains d times column t of Q and p^T Q p gains
-    // 2 d (Q p)[t] + d^2 Q[t][t]; renormalising divides p and Q p by 1 + d
-    // (the sum of p before it) and p^T Q p by its square.  Same fixed-point
-    // step as the plain form, O(C) per update instead of O(C^2).
+    // The sweep keeps Q p and p^T Q p up to date instead of recomputing them:
+    // the new p[t] equals p[t] + d with d = (p^T Q p - (Q p)[t]) / Q[t][t], by
+    // which Q p gains d times column t of Q and p^T Q p gains d times the sum of
+    // (Q p)[t] before and after.  Renormalising after each update is left to
+    // the end of the sweep: with u = s p, s the sum of u, the same step is
+    // u[t] += e, e = s d = (u^T Q u / s - (Q u)[t]) / Q[t][t], and s += e.  Same
+    // fixed-point step as the plain form, O(C) per update instead of O(C^2).
     double p[C], qp[C], rq[C];
 #pragma unroll
     for (int t = 0; t < C; ++t) {
@@ -211,236 +199,299 @@ __device__ __forceinline__ void svm_couple(const double (&f)[C * (C - 1) / 2],
 #pragma unroll
         for (int t = 0; t < C; ++t) err = fmax(err, fabs(qp[t] - pqp));
         if (!(err >= eps)) break;
+        double s = 1.0, inv = 1.0;
 #pragma unroll
         for (int t = 0; t < C; ++t) {
-            const double d = (pqp - qp[t]) * rq[t];
-            const double inv = rcp64(1.0 + d);
-            pqp = fma(d, fma(d, qtt[t], 2.0 * qp[t]), pqp) * inv * inv;
+            const double q0 = qp[t];
+            const double d = fma(pqp, inv, -q0) * rq[t];
 #pragma unroll
-            for (int j = 0; j < C; ++j) qp[j] = fma(d, Q(j, t), qp[j]) * inv;
+            for (int j = 0; j < C; ++j) qp[j] = fma(d, Q(j, t), qp[j]);
+            pqp = fma(d, q0 + qp[t], pqp);
             p[t] += d;
-#pragma unroll
-            for (int j = 0; j < C; ++j) p[j] *= inv;
+            s += d;
+            inv = rcp64(s);
         }
+#pragma unroll
+        for (int t = 0; t < C; ++t) {
+            qp[t] *= inv;
+            p[t] *= inv;
+        }
+        pqp *= inv * inv;
     }
 #pragma unroll
     for (int t = 0; t < C; ++t) o[t] = (float)p[t];
 }
 
-// A pixel's outputs once its decision values f and projection pj are
-// complete (every thread of the block calls it).
-template <int C, int NT, bool PC1>
-__device__ __forceinline__ void svm_finish(int64_t pix, int64_t npix,
-                                           const double (&f)[C * (C - 1) / 2], double pj,
-                                           const double* __restrict__ bias,
-                                           const double* __restrict__ A,
-                                           const double* __restrict__ B, float* __restrict__ out,
-                                           float* __restrict__ band, double* __restrict__ ws,
-                                           double* __restrict__ pairs) {
-    const bool in = pix < npix;
-    if constexpr (PC1) {
-        if (ws) {
-            // every thread of the block takes part (pixels past the frame add nothing)
-            svm_publish_minmax<NT>(in ? pj : __builtin_inf(), in ? pj : -__builtin_inf(), pairs);
-            if (in) ws[pix] = pj;
-        } else if (in) {
-            band[pix] = (float)pj;
-        }
-    }
-    if (in) svm_couple<C>(f, bias, A, B, out + pix * C);
+// Four floats at a 4-byte aligned address, as one load.
+__device__ __forceinline__ float4 load4(const char* p) {
+    float4 v;
+    memcpy(&v, __builtin_assume_aligned(p, 4), sizeof v);
+    return v;
 }
 
-// PC1 = true also accumulates the PC1 projection of each
-// pixel (Sec. II.C.2: the cube centred by the band averages, times the first
-// eigenvector), band by band in ascending order in binary64, from the same
-// staged chunks: the step before the filter reads the cube once for both of
-// its outputs.
-template <int C, bool VEC, bool PC1>
-__global__ void __launch_bounds__(SVM_THREADS)
+// Columns of the product: the M hyperplanes, and (PC1) the eigenvector; in
+// groups of four.
+template <int C, bool PC1>
+struct SvmCols {
+    static constexpr int M = C * (C - 1) / 2;
+    static constexpr int N = M + (PC1 ? 1 : 0);
+    static constexpr int NG = (N + 3) / 4;
+    static constexpr int ST = 4 * NG + 1;  // exchange row (doubles): odd, so the rows' banks differ
+    // pixels per exchange: a whole tile where its rows are short
+    static constexpr int XP = NG <= 3 ? SVM_TILE : 16;
+    static constexpr int WST = 4 * NG * 16;  // doubles of weights per k-step
+};
+
+// LDS traffic of one wavefront, in order.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// NL: 16-byte loads per lane and item (8: up to 128 bands per item; 4: up to
+// 64, for cubes of no more).
+template <int C, bool PC1, int NL>
+__global__ void __launch_bounds__(SVM_THREADS, C <= 4 ? 3 : C <= 6 ? 2 : 1)
 svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
                 const double* __restrict__ w, const double* __restrict__ bias,
                 const double* __restrict__ A, const double* __restrict__ B,
                 float* __restrict__ out, const double* __restrict__ mean,
                 const double* __restrict__ vec, float* __restrict__ band,
                 double* __restrict__ ws, double* __restrict__ pairs) {
-    constexpr int M = C * (C - 1) / 2;
-    using Weights = ChunkWeights<SVM_THREADS, M, PC1>;
-    __shared__ __attribute__((aligned(16))) float tile[SVM_THREADS * SVM_STRIDE];
-    __shared__ __attribute__((aligned(16))) double wl[Weights::NWT];
-    const int tid = threadIdx.x;
-    const int64_t first = (int64_t)blockIdx.x * SVM_THREADS;
-    const int64_t last = npix - 1;
-
-    double f[M];
-#pragma unroll
-    for (int m = 0; m < M; ++m) f[m] = 0.0;
-    double pj = 0.0;  // PC1 projection
-    const float* row = tile + tid * SVM_STRIDE;
-    // Staging of cube[first .. first+255][c0 .. c0+31] (rows past the frame
-    // repeat its last pixel, bands past the cube read as 0).  The next chunk
-    // is loaded into registers while the current one is used from LDS.
-    // 16-byte path: lane (q, r0) loads column 4q of rows r0, r0 + 32, ...
-    // Scalar path: lane (q, r0) loads band q of rows r0, r0 + 8, ...
-    constexpr int NLOAD = VEC ? 8 : 32;
-    using Piece = typename std::conditional<VEC, float4, float>::type;
-    Piece v[NLOAD];
-    Weights wt;
-    const int q = VEC ? (tid & 7) : (tid & 31);
-    const int r0 = VEC ? (tid >> 3) : (tid >> 5);
-    constexpr int RSTEP = VEC ? 32 : 8;
-    auto fetch = [&](int c0) {
-        const int b = c0 + (VEC ? 4 * q : q);
-#pragma unroll
-        for (int i = 0; i < NLOAD; ++i) {
-            int64_t p = first + r0 + RSTEP * i;
-            p = p < npix ? p : last;
-            if constexpr (VEC)
-                v[i] = b < bands ? *(const float4*)(cube + p * (int64_t)bands + b)
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-            else
-                v[i] = b < bands ? cube[p * (int64_t)bands + b] : 0.f;
-        }
-        wt.fetch(c0, bands, w, mean, vec);
+    using Cols = SvmCols<C, PC1>;
+    constexpr int M = Cols::M, N = Cols::N, NG = Cols::NG, ST = Cols::ST, XP = Cols::XP;
+    constexpr int G = SVM_TILE / 16;
+    constexpr int MAXP = NL * 4;  // pieces per pixel of an item
+    // weights[(4 s + e) / 2][group][k][n][e % 2]: lane (k, n) of matrix steps e
+    // and e + 1 reads 16 bytes
+    __shared__ __attribute__((aligned(16))) double wl[NL * Cols::WST];
+    // an item's pieces, a row of MAXP per pixel and one of padding (bank
+    // spread); after the tile's last item, its sums
+    union Buf {
+        float4 x[16 * (MAXP + 1)];
+        double sum[XP * ST];
     };
-    fetch(0);
-    for (int c0 = 0; c0 < bands; c0 += SVM_CHUNK) {
-#pragma unroll
-        for (int i = 0; i < NLOAD; ++i) {
-            if constexpr (VEC)
-                *(float4*)(tile + (r0 + RSTEP * i) * SVM_STRIDE + 4 * q) = v[i];
-            else
-                tile[(r0 + RSTEP * i) * SVM_STRIDE + q] = v[i];
-        }
-        wt.stage(wl);
-        __syncthreads();
-        if (c0 + SVM_CHUNK < bands) fetch(c0 + SVM_CHUNK);
-        svm_dot_chunk<M, PC1>(row, min(SVM_CHUNK, bands - c0), wl, f, pj);
-        __syncthreads();
-    }
-    svm_finish<C, SVM_THREADS, PC1>(first + tid, npix, f, pj, bias, A, B, out, band, ws, pairs);
-}
+    __shared__ __attribute__((aligned(16))) Buf buf[SVM_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int np = (bands + 3) >> 2;               // pieces per pixel
+    const int nchunk = (np + MAXP - 1) / MAXP;     // items per 16 pixels, stagings of weights
+    const int64_t tile0 = ((int64_t)blockIdx.x * (SVM_THREADS / 64) + wv) * SVM_TILE;  // first pixel
 
-// knnf_svm on cubes whose pixel rows are not whole 128-byte lines (bands * 4
-// not a multiple of 128, e.g. 100 bands): per-pixel band chunks split lines
-// between chunks and between neighbouring pixels, and a line evicted between
-// its two uses is fetched twice (1.6x the cube's bytes on the 1000 x 1000 x
-// 100 cube).  This variant reads the block's 256 pixels as 4 linear runs of
-// 64 whole pixel rows (each line once, in full), staged in LDS with a row
-// stride of S = 16 (mod 32) floats.  Four lanes share a pixel of a run: lane
-// part t takes the float4 pieces t, t+4, ... of the row (a quarter-
-// wavefront's 16-byte reads then cover all 64 banks), and a butterfly over
-// the four lanes completes the pixel's sums.  Lane part t keeps the sums of
-// run t, so thread 4 pl + t owns pixel 64 t + pl of the block for the
-// sigmoids and the coupling.  All weights are staged once, piece by piece.
-// The sums run in a different order than band by band (four interleaved
-// partial sums), which moves the binary64 results by rounding only.  (With
-// the PC1 projection added, the band-chunk kernel above measured faster, so
-// the fused call keeps it.)
-constexpr int LIN_RUN = 64;                     // pixels per linear run
-constexpr int LIN_MAX_BANDS = 128;
-constexpr int LIN_MAX_WEIGHTS = 2048;           // doubles of weights staged at once
-constexpr int LIN_MAX_C = 4;                    // more classes: the coupling's registers spill
-
-__host__ __device__ constexpr int lin_stride(int bands) {
-    return ((bands + 15) / 32) * 32 + 16;       // smallest S >= bands with S = 16 (mod 32)
-}
-// Doubles per piece of staged weights: the smallest >= 4 M that is 8 (mod
-// 16), so the four lanes of a quad (pieces k .. k+3) read on disjoint banks.
-__host__ __device__ constexpr int lin_piece(int m) { return ((4 * m + 7) / 16) * 16 + 8; }
-
-__device__ __forceinline__ double quad_sum(double v) {
-    // sum over the 4 lanes of a quad (xor 1, then xor 2), every lane gets it
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    v += __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0xB1, 0xF, 0xF, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, 0xB1, 0xF, 0xF, false));
-    lo = __double2loint(v);
-    hi = __double2hiint(v);
-    return v + __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x4E, 0xF, 0xF, false),
-                                __builtin_amdgcn_update_dpp(lo, lo, 0x4E, 0xF, 0xF, false));
-}
-
-template <int C>
-__global__ void __launch_bounds__(SVM_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
-svm_prob_lin_kernel(const float* __restrict__ cube, int64_t npix, int bands,
-                    const double* __restrict__ w, const double* __restrict__ bias,
-                    const double* __restrict__ A, const double* __restrict__ B,
-                    float* __restrict__ out) {
-    constexpr int M = C * (C - 1) / 2;
-    constexpr int PS = lin_piece(M);
-    constexpr int NLD = LIN_RUN * LIN_MAX_BANDS / 4 / SVM_THREADS;  // float4 loads per thread, max
-    extern __shared__ __attribute__((aligned(16))) double lin_smem[];
-    double* wl = lin_smem;                                 // bands / 4 pieces x PS
-    const int S = lin_stride(bands);
-    float* tile = (float*)(lin_smem + (bands >> 2) * PS);  // LIN_RUN x S
-    const int tid = threadIdx.x;
-    const int pl = tid >> 2, t = tid & 3;
-    const int64_t first = (int64_t)blockIdx.x * SVM_THREADS;
-    const int b4 = bands >> 2;                             // float4 pieces per pixel
-    const int nq = LIN_RUN * b4;                           // pieces per run
-    const float inv_b4 = 1.0f / (float)b4;
-
-    // weights by piece: wl[k * PS + m * 4 + e] is hyperplane m at band
-    // 4 k + e, so a piece's M x 4 weights are contiguous (16-byte LDS reads
-    // at constant offsets)
-    for (int e = tid; e < M * bands; e += SVM_THREADS) {
-        const int m = e / bands, bb = e - m * bands;
-        wl[(bb >> 2) * PS + m * 4 + (bb & 3)] = w[(int64_t)m * bands + bb];
-    }
-
-    // run r: pixels first + 64 r .. +63, read as one linear range of pieces
-    // (pixels past the cube read as 0 and are never written)
-    float4 v[NLD];
-    auto fetch = [&](int r) {
-        const int64_t p0 = first + (int64_t)LIN_RUN * r;
+    // Item (group, chunk) of the tile: a load takes RPL pixels, MAXP lanes each
+    // (lanes past the row's pieces load its last one and do not store it).
+    constexpr int RPL = 64 / MAXP;
+    const int lrow = lane / MAXP, lpc = lane % MAXP;
+    const uint32_t b4 = (uint32_t)bands * 4u;
+    float4 v[NL];
+    auto load_item = [&](int g, int chunk) {
+        // pixels past the cube repeat the last one
+        const int64_t p0 = min(tile0 + 16 * g, npix - 1);
         const char* src = (const char*)(cube + p0 * (int64_t)bands);
-        // pieces inside the run and the cube
-        const int lim = (int)min((int64_t)nq, max((int64_t)0, npix - p0) * b4);
+        const uint32_t last = (uint32_t)min((int64_t)15, npix - 1 - p0);
+        const int p = lpc + chunk * MAXP;
+        const uint32_t po = (uint32_t)(p < np - 1 ? 4 * p : bands - 4) * 4u;
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int q = tid + SVM_THREADS * i;
-            v[i] = q < lim ? *(const float4*)(src + (uint32_t)q * 16u) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int i = 0; i < NL; ++i)
+            v[i] = load4(src + (__umul24(min((uint32_t)(RPL * i + lrow), last), b4) + po));
+    };
+    // Weights of a chunk: fetched into registers, then stored to LDS.  Thread
+    // tid takes column tid % (4 NG) of band slots SPT j + tid / (4 NG); the
+    // last piece of a pixel starts at bands - 4 and has weight 0 for the bands
+    // that it repeats, as have slots and columns past the end.
+    constexpr int SPT = SVM_THREADS / (4 * NG), NSLOT = MAXP * 4;
+    constexpr int NW = (NSLOT + SPT - 1) / SPT;
+    const int wcol = tid % (4 * NG), wslot = tid / (4 * NG);
+    const double* wsrc = PC1 && wcol == M ? vec : w + (wcol < M ? wcol * bands : 0);
+    double wr[NW];
+    auto fetch_weights = [&](int chunk) {
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            const int slot = wslot + SPT * j + chunk * NSLOT, piece = slot >> 2;
+            const int b = piece < np - 1 ? slot : bands - 4 + (slot & 3);
+            const bool used = wcol < N && piece < np && b >= 4 * piece;
+            const double x = wsrc[used ? b : 0];
+            wr[j] = used ? x : 0.0;
         }
     };
-    double own[M];
+    auto store_weights = [&]() {
 #pragma unroll
-    for (int m = 0; m < M; ++m) own[m] = 0.0;
-    fetch(0);
-#pragma unroll 1
-    for (int r = 0; r < SVM_THREADS / LIN_RUN; ++r) {
+        for (int j = 0; j < NW; ++j) {
+            const int slot = wslot + SPT * j;
+            const int s = slot >> 4, k = (slot >> 2) & 3, e = slot & 3;
+            if (NSLOT % SPT == 0 || slot < NSLOT)
+                wl[s * Cols::WST + (((e >> 1) * NG + (wcol >> 2)) * 16 + k * 4 + (wcol & 3)) * 2 + (e & 1)] = wr[j];
+        }
+    };
+    load_item(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_weights(0);
+    store_weights();
+    __syncthreads();
+
+    char* xb = (char*)buf[wv].x;
+    const double* wk = wl + ((lane >> 4) * 4 + (lane & 3)) * 2;
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    double acc[G][NG];
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int q = tid + SVM_THREADS * i;
-            if (q < nq) {
-                // piece q is pixel q / b4 of the run, bands 4 (q % b4) ..
-                const int px = (int)(((float)q + 0.5f) * inv_b4);
-                *(float4*)(tile + px * S + 4 * (q - px * b4)) = v[i];
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int n = 0; n < NG; ++n) acc[g][n] = 0.0;
+    int chunk = 0;
+    do {
+        const int pc = min(MAXP, np - chunk * MAXP);
+        const int ns = (pc + 3) >> 2;
+        char* xw = xb + (lrow * (MAXP + 1) + lpc) * 16;
+        const char* xr = xb + ((lane & 15) * (MAXP + 1) + (lane >> 4)) * 16;
+        // slots past the row's pieces hold 0 (their weights are 0, but 0 times
+        // an infinity is not)
+        if (lpc >= pc) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+                *(float4*)(xw + i * RPL * (MAXP + 1) * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        // bands that the last piece repeats: 0 as well
+        const int rep = lpc + chunk * MAXP == np - 1 ? 4 * np - bands : 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            wave_lds_sync();
+            if (bands & 3) {
+#pragma unroll
+                for (int i = 0; i < NL; ++i) {
+                    v[i].x = rep > 0 ? 0.f : v[i].x;
+                    v[i].y = rep > 1 ? 0.f : v[i].y;
+                    v[i].z = rep > 2 ? 0.f : v[i].z;
+                }
+            }
+            if (lpc < pc) {
+#pragma unroll
+                for (int i = 0; i < NL; ++i) *(float4*)(xw + i * RPL * (MAXP + 1) * 16) = v[i];
+            }
+            wave_lds_sync();
+            // the next item's loads
+            if (g + 1 < G) load_item(g + 1, chunk);
+            else if (chunk + 1 < nchunk) load_item(0, chunk + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            for (int s = 0; s < ns; ++s) {
+                const float4 x = *(const float4*)(xr + s * 64);
+                const double xd[4] = {(double)x.x, (double)x.y, (double)x.z, (double)x.w};
+                const double* wp = wk + s * Cols::WST;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    d2 wt[NG];
+#pragma unroll
+                    for (int n = 0; n < NG; ++n)
+                        wt[n] = *(const d2*)(wp + (h * NG + n) * 32);
+#pragma unroll
+                    for (int n = 0; n < NG; ++n) 
+                        acc[g][n] = __builtin_amdgcn_mfma_f64_4x4x4f64(xd[2 * h], wt[n].x, acc[g][n], 0, 0, 0);
+#pragma unroll
+                    for (int n = 0; n < NG; ++n) 
+                        acc[g][n] = __builtin_amdgcn_mfma_f64_4x4x4f64(xd[2 * h + 1], wt[n].y, acc[g][n], 0, 0, 0);
+                }
             }
         }
-        __syncthreads();
-        if (r + 1 < SVM_THREADS / LIN_RUN) fetch(r + 1);
-        double f[M];
+        if (++chunk < nchunk) {
+            fetch_weights(chunk);
+            __syncthreads();
+            store_weights();
+            __syncthreads();
+        }
+    } while (chunk < nchunk);
+
+    // sums to one lane per pixel: lane l of group g holds pixel
+    // 16 g + 4 ((l / 4) % 4) + l / 16, column 4 n + l % 4
+    double f[N];
+    double* xr = buf[wv].sum;
+    const int op = 4 * ((lane >> 2) & 3) + (lane >> 4), oc = lane & 3;
+    wave_lds_sync();
+    if constexpr (XP == SVM_TILE) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int n = 0; n < NG; ++n) xr[(16 * g + op) * ST + 4 * n + oc] = acc[g][n];
+        wave_lds_sync();
+#pragma unroll
+        for (int m = 0; m < N; ++m) f[m] = xr[lane * ST + m];
+    } else {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int n = 0; n < NG; ++n) xr[op * ST + 4 * n + oc] = acc[g][n];
+            wave_lds_sync();
+#pragma unroll
+            for (int m = 0; m < N; ++m) {
+                const double y = xr[(lane & 15) * ST + m];
+                f[m] = g == 0 || lane >> 4 == g ? y : f[m];
+            }
+            wave_lds_sync();
+        }
+    }
+    const int64_t pix = tile0 + lane;
+    const bool in = pix < npix;
+    if constexpr (PC1) {
+        if (ws) {
+            // (the constant -(band averages . eigenvector) is left out: the
+            // normalisation removes it)
+            const double pj = f[M];
+            if (in) ws[pix] = pj;
+            __syncthreads();  // the buffers are free
+            svm_publish_minmax<SVM_THREADS>(in ? pj : __builtin_inf(), in ? pj : -__builtin_inf(),
+                                            pairs, buf[0].sum);
+        } else {
+            double c = 0.0;
+            for (int b = lane; b < bands; b += 64) c = fma(-mean[b], vec[b], c);
+            for (int m = 1; m < 64; m <<= 1) c += __shfl_xor(c, m);
+            if (in) band[pix] = (float)(f[M] + c);
+        }
+    }
+    if (in) {
+        double fm[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) fm[m] = f[m];
+        svm_couple<C>(fm, bias, A, B, out + pix * C);
+    }
+}
+
+// Fewer than four bands: one lane per pixel.
+template <int C, bool PC1>
+__global__ void __launch_bounds__(SVM_THREADS)
+svm_prob_few_kernel(const float* __restrict__ cube, int64_t npix, int bands,
+                    const double* __restrict__ w, const double* __restrict__ bias,
+                    const double* __restrict__ A, const double* __restrict__ B,
+                    float* __restrict__ out, const double* __restrict__ mean,
+                    const double* __restrict__ vec, float* __restrict__ band,
+                    double* __restrict__ ws, double* __restrict__ pairs) {
+    constexpr int M = C * (C - 1) / 2;
+    const int64_t nthreads = (int64_t)gridDim.x * SVM_THREADS;
+    double lo = __builtin_inf(), hi = -__builtin_inf();
+    for (int64_t pix = (int64_t)blockIdx.x * SVM_THREADS + threadIdx.x; pix < npix; pix += nthreads) {
+        const float* row = cube + pix * (int64_t)bands;
+        double f[M], pj = 0.0;
 #pragma unroll
         for (int m = 0; m < M; ++m) f[m] = 0.0;
-        const float* row = tile + pl * S;
-#pragma unroll 1
-        for (int k = t; k < b4; k += 4) {
-            const float4 xa = *(const float4*)(row + 4 * k);
-            const double x[4] = {(double)xa.x, (double)xa.y, (double)xa.z, (double)xa.w};
-            const double* wk = wl + k * PS;
+        for (int b = 0; b < bands; ++b) {
+            const double x = (double)row[b];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int m = 0; m < M; ++m) f[m] = fma(wk[m * 4 + e], x[e], f[m]);
+            for (int m = 0; m < M; ++m) f[m] = fma(w[(int64_t)m * bands + b], x, f[m]);
+            if constexpr (PC1) pj = fma(x - mean[b], vec[b], pj);
         }
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            f[m] = quad_sum(f[m]);
-            own[m] = t == r ? f[m] : own[m];
+        if constexpr (PC1) {
+            if (ws) {
+                ws[pix] = pj;
+                lo = fmin(lo, pj);
+                hi = fmax(hi, pj);
+            } else {
+                band[pix] = (float)pj;
+            }
         }
-        __syncthreads();
+        svm_couple<C>(f, bias, A, B, out + pix * C);
     }
-    svm_finish<C, SVM_THREADS, false>(first + LIN_RUN * t + pl, npix, own, 0.0, bias, A, B, out,
-                                      nullptr, nullptr, nullptr);
+    if constexpr (PC1) {
+        __shared__ double lds[2 * SVM_THREADS / 64];
+        if (ws) svm_publish_minmax<SVM_THREADS>(lo, hi, pairs, lds);
+    }
 }
 
 struct SvmArgs {
@@ -455,27 +506,19 @@ struct SvmArgs {
 template <int C, bool PC1>
 int launch_c(const SvmArgs& a, void* stream, int* nblocks) {
     const hipStream_t st = (hipStream_t)stream;
-    const int64_t blocks = (a.npix + SVM_THREADS - 1) / SVM_THREADS;
-    const bool vec = a.bands % 4 == 0 && ((uintptr_t)a.cube & 15) == 0;
-    bool lin = false;
-    if constexpr (C <= LIN_MAX_C && !PC1) {
-        constexpr int M = C * (C - 1) / 2;
-        const int wd = a.bands / 4 * lin_piece(M);       // doubles of staged weights
-        lin = vec && (a.bands * 4) % 128 != 0 && a.bands <= LIN_MAX_BANDS && wd <= LIN_MAX_WEIGHTS;
-        if (lin) {
-            const size_t lds = (size_t)wd * 8 + (size_t)LIN_RUN * lin_stride(a.bands) * 4;
-            hipLaunchKernelGGL((svm_prob_lin_kernel<C>), dim3((uint32_t)blocks), dim3(SVM_THREADS),
-                               lds, st, a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out);
-        }
-    }
-    if (!lin && vec)
-        hipLaunchKernelGGL((svm_prob_kernel<C, true, PC1>), dim3((uint32_t)blocks), dim3(SVM_THREADS),
-                           0, st, a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean,
-                           a.vec, a.band, a.ws, a.pairs);
-    else if (!lin)
-        hipLaunchKernelGGL((svm_prob_kernel<C, false, PC1>), dim3((uint32_t)blocks), dim3(SVM_THREADS),
-                           0, st, a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean,
-                           a.vec, a.band, a.ws, a.pairs);
+    const unsigned blocks = (unsigned)((a.npix + SVM_THREADS - 1) / SVM_THREADS);
+    if (a.bands < 4)
+        hipLaunchKernelGGL((svm_prob_few_kernel<C, PC1>), dim3(blocks), dim3(SVM_THREADS), 0, st,
+                           a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean, a.vec,
+                           a.band, a.ws, a.pairs);
+    else if (a.bands <= 64)
+        hipLaunchKernelGGL((svm_prob_kernel<C, PC1, 4>), dim3(blocks), dim3(SVM_THREADS), 0, st,
+                           a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean, a.vec,
+                           a.band, a.ws, a.pairs);
+    else
+        hipLaunchKernelGGL((svm_prob_kernel<C, PC1, 8>), dim3(blocks), dim3(SVM_THREADS), 0, st,
+                           a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean, a.vec,
+                           a.band, a.ws, a.pairs);
     if (nblocks) *nblocks = (int)blocks;
     return (int)hipGetLastError();
 }
