@@ -377,7 +377,7 @@ knnf_status knnf_server_destroy(knnf_server* srv);
  * vec   device, bands float64 (first eigenvector)
  * out   device, npix float32; may be the pc1 buffer of a knnf_frame
  * Asynchronous on `stream`.  Uses a context workspace (8 B per pixel when
- * normalize != 0, plus 16 KB) that grows on first use of a larger frame (that
+ * normalize != 0, plus 64 KB) that grows on first use of a larger frame (that
  * call synchronizes the device and allocates).  Calls that overlap on one
  * context race on the workspace: issue them on one stream.
  * Errors: KNNF_EINVAL for a NULL argument, npix outside [1, 2^40], bands
@@ -395,7 +395,7 @@ knnf_status knnf_pc1(knnf_ctx* ctx, const float* cube, int64_t npix, int32_t ban
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, kernels and results as knnf_pc1, but its
  * workspace is a static scratch array that each device holds for the life of
- * the process (8 MiB + 16 KiB), so the call never allocates or synchronises.
+ * the process (8 MiB + 64 KiB), so the call never allocates or synchronises.
  * Limit: with normalize != 0, npix <= KNNF_PC1_NOALLOC_MAX_PIXELS (larger:
  * KNNF_EINVAL, nothing enqueued); the raw projection uses no scratch.  Every
  * call on one device shares that device's scratch (nothing in it needs to

@@ -18,13 +18,21 @@
 // segment reads bands 4j .. 4j+3 with one 16-byte load, so a wavefront reads
 // 64/S whole pixels contiguously per load; the lane keeps its four averages
 // and eigenvector entries in registers for the whole launch.  The segment sum
-// is a butterfly over the S lanes.  Normalisation needs min and max over the
-// frame: each projection block stores its (min, max) pair, and every block of
-// the second launch reduces those pairs before rescaling its pixels (no
-// atomics on one address, no device-wide fence).
+// is a butterfly over the S lanes.  A block takes one contiguous range of
+// pixels, its four wavefronts side by side: with the wavefronts' reads spread
+// over the cube in a grid-stride loop, a plain read reached 5.7 instead of 6.5
+// TB/s (raw projection of 380 x 480 x 128: 18.2 and 17.2 us per call, about
+// 2.3 us of each the launch).  Band counts that are no multiple of 4 and
+// unaligned cubes take the same path (500 x 500 x 33: 13.0 us with the
+// normalisation, 49.6 us with one thread per pixel).
+// Normalisation needs min and max over the frame: each projection block stores
+// its (min, max) pair, and every block of the second launch reduces those pairs
+// before rescaling its pixels (no atomics on one address, no device-wide fence).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/knnf.h"
@@ -34,11 +42,13 @@ namespace knnf {
 namespace {
 
 constexpr int PC1_THREADS = 256;
-constexpr int PC1_UNROLL = 4;  // pixels per lane per iteration (independent loads in flight)
-// Projection grid cap: enough wavefronts to keep HBM busy (each has
-// PC1_UNROLL 16-byte loads in flight per lane), few enough partial pairs for
-// the normalisation blocks to reduce.
-constexpr int PC1_MAX_BLOCKS = 1024;
+constexpr int PC1_UNROLL = 4;  // loads of a wavefront in flight together (8: no faster)
+// Projection grid: a block takes at least 32 KiB of the cube (500 x 500 x 33:
+// 13.0 us, 15.2 us with blocks of 8 KiB, 14.5 with 64), and there are no more
+// blocks than the normalisation's blocks can reduce the pairs of at once
+// (1000 x 1000 x 100: 88.8 us, 91.2 with at most 1,024 blocks).
+constexpr int PC1_MAX_BLOCKS = 4096;
+constexpr int64_t PC1_BLOCK_BYTES = 32 * 1024;
 
 // Value of the partner lane for one butterfly step (64-bit through two
 // 32-bit lane moves): DPP quad_perm xor 1 / xor 2, row_half_mirror (pairs the
@@ -67,7 +77,7 @@ __device__ __forceinline__ double partner(double v) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Sum over each aligned group of S lanes (S = 16, 32, 64); every lane of the
+// Sum over each aligned group of S lanes (S = 8, 16, 32, 64); every lane of the
 // group ends with the same value (each step adds two equal-order partial sums,
 // and binary64 addition is commutative).
 template <int S>
@@ -75,7 +85,7 @@ __device__ __forceinline__ double seg_sum(double v) {
     v += partner<0>(v);
     v += partner<1>(v);
     v += partner<2>(v);
-    v += partner<3>(v);
+    if constexpr (S >= 16) v += partner<3>(v);
     if constexpr (S >= 32) v += partner<4>(v);
     if constexpr (S >= 64) v += partner<5>(v);
     return v;
@@ -84,10 +94,12 @@ __device__ __forceinline__ double seg_sum(double v) {
 // Block-wide min and max of per-thread values; thread 0 gets the result.
 __device__ void block_minmax(double lo, double hi, double* out_lo, double* out_hi) {
     __shared__ double slo[PC1_THREADS / 64], shi[PC1_THREADS / 64];
-    for (int m = 1; m < 64; m <<= 1) {
-        lo = fmin(lo, __shfl_xor(lo, m));
-        hi = fmax(hi, __shfl_xor(hi, m));
-    }
+    lo = fmin(lo, partner<0>(lo)), hi = fmax(hi, partner<0>(hi));
+    lo = fmin(lo, partner<1>(lo)), hi = fmax(hi, partner<1>(hi));
+    lo = fmin(lo, partner<2>(lo)), hi = fmax(hi, partner<2>(hi));
+    lo = fmin(lo, partner<3>(lo)), hi = fmax(hi, partner<3>(hi));
+    lo = fmin(lo, partner<4>(lo)), hi = fmax(hi, partner<4>(hi));
+    lo = fmin(lo, partner<5>(lo)), hi = fmax(hi, partner<5>(hi));
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         slo[w] = lo;
@@ -115,62 +127,85 @@ __device__ void publish_minmax(double lo, double hi, double* pairs) {
     }
 }
 
-// Projection, bands % 4 == 0, bands <= 4 * S, 16-byte aligned cube.
+// Four floats at a 4-byte aligned address, as one load.
+__device__ __forceinline__ float4 load4(const float* p) {
+    float4 v;
+    memcpy(&v, __builtin_assume_aligned(p, 4), sizeof v);
+    return v;
+}
+
+// Projection, 4 <= bands <= 4 * S, any 4-byte alignment.  Where bands is no
+// multiple of 4, a pixel's last piece starts at bands - 4 and the bands that it
+// repeats count as 0.  Block b takes the pixels [b * per, (b + 1) * per).
 template <int S>
 __global__ void __launch_bounds__(PC1_THREADS)
 pc1_project_vec4(const float* __restrict__ cube, int64_t npix, int bands,
                  const double* __restrict__ mean, const double* __restrict__ vec,
-                 float* __restrict__ out, double* __restrict__ ws, double* __restrict__ pairs) {
+                 float* __restrict__ out, double* __restrict__ ws, double* __restrict__ pairs,
+                 int64_t per) {
     constexpr int PW = 64 / S;  // pixels per wavefront per load
+    constexpr int STEP = PW * PC1_UNROLL, WAVES = PC1_THREADS / 64;
     const int lane = threadIdx.x & 63;
     const int j = lane % S;      // slot in the segment
     const int seg = lane / S;    // pixel of the segment within the wavefront group
-    const int b0 = 4 * j;
-    const bool act = b0 < bands;
+    const int np = (bands + 3) >> 2;
+    const bool act = j < np;
+    const int b0 = j < np - 1 ? 4 * j : bands - 4;        // first band of the lane's piece
+    const int rep = j == np - 1 ? 4 * np - bands : 0;     // its bands that the piece before covers
+    const int64_t p1 = min(npix, (int64_t)(blockIdx.x + 1) * per);
+    int64_t base = (int64_t)blockIdx.x * per + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * STEP;
     double mu[4], w[4];
+    float4 x[PC1_UNROLL];
+    // every lane loads (past the last pixel or band: a clamped address whose
+    // value is dropped), so all loads are in flight together
+    auto load = [&]() {
+        const float* rp = cube + min(base, npix - 1) * (int64_t)bands;
+        const uint32_t last = (uint32_t)min((int64_t)STEP, npix - 1 - min(base, npix - 1));
+#pragma unroll
+        for (int u = 0; u < PC1_UNROLL; ++u)
+            x[u] = load4(rp + (min((uint32_t)(u * PW + seg), last) * (uint32_t)bands + (uint32_t)b0));
+    };
+    load();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        mu[i] = act ? mean[b0 + i] : 0.0;
-        w[i] = act ? vec[b0 + i] : 0.0;
+        const bool use = act && i >= rep;
+        mu[i] = mean[b0 + i];
+        w[i] = use ? vec[b0 + i] : 0.0;
     }
-    const int64_t waves = (int64_t)gridDim.x * (PC1_THREADS / 64);
-    const int64_t wid = (int64_t)blockIdx.x * (PC1_THREADS / 64) + (threadIdx.x >> 6);
-    const int64_t stride = waves * PW * PC1_UNROLL;
     double lo = __builtin_inf(), hi = -__builtin_inf();
-    for (int64_t base = wid * PW * PC1_UNROLL; base < npix; base += stride) {
-        // every lane loads (past the last pixel or band: a clamped address
-        // whose value is dropped), so all loads are in flight together
-        float4 x[PC1_UNROLL];
-        const int col = act ? b0 : 0;
-        if (base + (int64_t)PW * PC1_UNROLL <= npix) {
-            const float* __restrict__ rp = cube + (base + seg) * (int64_t)bands + col;
-            const int64_t step = (int64_t)PW * bands;
-#pragma unroll
-            for (int u = 0; u < PC1_UNROLL; ++u) x[u] = *(const float4*)(rp + u * step);
-        } else {
-#pragma unroll
-            for (int u = 0; u < PC1_UNROLL; ++u) {
-                int64_t p = base + (int64_t)u * PW + seg;
-                p = p < npix ? p : npix - 1;
-                x[u] = *(const float4*)(cube + p * (int64_t)bands + col);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);  // issue every load before the first use
+    for (; base < p1; base += STEP * WAVES) {
+        double t[PC1_UNROLL];
 #pragma unroll
         for (int u = 0; u < PC1_UNROLL; ++u) {
-            const int64_t p = base + (int64_t)u * PW + seg;
-            double t = 0.0;
-            t = fma((double)x[u].x - mu[0], w[0], t);
-            t = fma((double)x[u].y - mu[1], w[1], t);
-            t = fma((double)x[u].z - mu[2], w[2], t);
-            t = fma((double)x[u].w - mu[3], w[3], t);
-            t = seg_sum<S>(act ? t : 0.0);
-            if (p < npix) {
-                lo = fmin(lo, t);
-                hi = fmax(hi, t);
+            if (bands & 3) {
+                x[u].x = rep > 0 ? 0.f : x[u].x;
+                x[u].y = rep > 1 ? 0.f : x[u].y;
+                x[u].z = rep > 2 ? 0.f : x[u].z;
+            }
+            double s = 0.0;
+            s = fma((double)x[u].x - mu[0], w[0], s);
+            s = fma((double)x[u].y - mu[1], w[1], s);
+            s = fma((double)x[u].z - mu[2], w[2], s);
+            s = fma((double)x[u].w - mu[3], w[3], s);
+            t[u] = act ? s : 0.0;
+        }
+        const int64_t cur = base;
+        if (base + STEP * WAVES < p1) {
+            base += STEP * WAVES;
+            load();  // the next step's loads, ahead of this one's sums
+            base = cur;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < PC1_UNROLL; ++u) {
+            const int64_t p = cur + u * PW + seg;
+            const double s = seg_sum<S>(t[u]);
+            if (p < p1) {
+                lo = fmin(lo, s);
+                hi = fmax(hi, s);
                 if (j == 0) {
-                    if (ws) ws[p] = t;
-                    else out[p] = (float)t;
+                    if (ws) ws[p] = s;
+                    else out[p] = (float)s;
                 }
             }
         }
@@ -178,7 +213,7 @@ pc1_project_vec4(const float* __restrict__ cube, int64_t npix, int bands,
     if (ws) publish_minmax(lo, hi, pairs);
 }
 
-// Projection for any band count and alignment: one thread per pixel.
+// Projection for fewer than 4 or more than 256 bands: one thread per pixel.
 __global__ void __launch_bounds__(PC1_THREADS)
 pc1_project_scalar(const float* __restrict__ cube, int64_t npix, int bands,
                    const double* __restrict__ mean, const double* __restrict__ vec,
@@ -200,11 +235,31 @@ pc1_project_scalar(const float* __restrict__ cube, int64_t npix, int bands,
 __global__ void __launch_bounds__(PC1_THREADS)
 pc1_normalise(const double* __restrict__ ws, int64_t npix, const double* __restrict__ pairs,
               int npairs, float* __restrict__ out) {
+    // four pixels per thread and step, their loads issued together; the first
+    // step's and the pairs' are in flight at once
+    const int64_t nthreads = (int64_t)gridDim.x * PC1_THREADS;
+    int64_t p = (int64_t)blockIdx.x * PC1_THREADS + threadIdx.x;
+    double x[4];
+    auto load = [&]() {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t pk = p + k * nthreads;
+            x[k] = ws[pk < npix ? pk : npix - 1];
+        }
+    };
+    load();
     // min and max over the frame from the projection blocks' pairs
+    typedef double d2 __attribute__((ext_vector_type(2)));
     double l = __builtin_inf(), h = -__builtin_inf();
-    for (int b = threadIdx.x; b < npairs; b += PC1_THREADS) {
-        l = fmin(l, pairs[2 * b]);
-        h = fmax(h, pairs[2 * b + 1]);
+    for (int b = threadIdx.x; b < npairs; b += 4 * PC1_THREADS) {
+        d2 q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = ((const d2*)pairs)[min(b + k * PC1_THREADS, npairs - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            l = fmin(l, q[k].x);
+            h = fmax(h, q[k].y);
+        }
     }
     __shared__ double pair[2];
     block_minmax(l, h, &pair[0], &pair[1]);
@@ -212,22 +267,15 @@ pc1_normalise(const double* __restrict__ ws, int64_t npix, const double* __restr
     const double lo = pair[0], hi = pair[1];
     const bool flat = !(hi > lo);
     const double range = hi - lo;
-    // four pixels per thread and step, their loads issued together (one at a
-    // time, each step waited for its load: the large cubes' passes were
-    // latency-bound)
-    const int64_t nthreads = (int64_t)gridDim.x * PC1_THREADS;
-    for (int64_t p = (int64_t)blockIdx.x * PC1_THREADS + threadIdx.x; p < npix; p += 4 * nthreads) {
-        double x[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t pk = p + k * nthreads;
-            x[k] = pk < npix ? ws[pk] : 0.0;
-        }
+    for (;;) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int64_t pk = p + k * nthreads;
             if (pk < npix) out[pk] = flat ? 0.0f : (float)((x[k] - lo) / range);
         }
+        p += 4 * nthreads;
+        if (p >= npix) break;
+        load();
     }
 }
 
@@ -249,7 +297,7 @@ int launch_pc1_normalise(const double* ws, int64_t npix, const double* pairs, in
 // pixels.  Each device holds its own copy for the life of the process; host
 // code uses the device address hipGetSymbolAddress reports for it (the
 // array's name is a host-side stand-in, not a device address).
-constexpr size_t kScratchHead = 16384;
+constexpr size_t kScratchHead = 65536;
 static_assert(2 * PC1_MAX_BLOCKS * sizeof(double) <= kScratchHead, "pairs fit the scratch head");
 constexpr size_t kScratchBytes = kScratchHead + sizeof(double) * (size_t)KNNF_PC1_NOALLOC_MAX_PIXELS;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -278,36 +326,33 @@ size_t pc1_scratch_head() { return kScratchHead; }
 int launch_pc1(const float* cube, int64_t npix, int bands, const double* mean, const double* vec,
                float* out, double* ws, double* pairs, int num_cu, void* stream) {
     hipStream_t st = (hipStream_t)stream;
-    const bool aligned = ((uintptr_t)cube & 15u) == 0;
-    int64_t want;
     int blocks;
-    if (aligned && bands % 4 == 0 && bands <= 256) {
-        const int S = bands <= 64 ? 16 : (bands <= 128 ? 32 : 64);
-        const int64_t per_block = (int64_t)(PC1_THREADS / 64) * (64 / S) * PC1_UNROLL;
-        want = (npix + per_block - 1) / per_block;
-        blocks = (int)(want < PC1_MAX_BLOCKS ? want : PC1_MAX_BLOCKS);
-        if (S == 16)
-            hipLaunchKernelGGL(pc1_project_vec4<16>, dim3(blocks), dim3(PC1_THREADS), 0, st, cube,
-                               npix, bands, mean, vec, out, ws, pairs);
-        else if (S == 32)
-            hipLaunchKernelGGL(pc1_project_vec4<32>, dim3(blocks), dim3(PC1_THREADS), 0, st, cube,
-                               npix, bands, mean, vec, out, ws, pairs);
-        else
-            hipLaunchKernelGGL(pc1_project_vec4<64>, dim3(blocks), dim3(PC1_THREADS), 0, st, cube,
-                               npix, bands, mean, vec, out, ws, pairs);
+    if (bands >= 4 && bands <= 256) {
+        const int S = bands <= 32 ? 8 : bands <= 64 ? 16 : bands <= 128 ? 32 : 64;
+        // a block's step: PC1_UNROLL loads of each wavefront
+        const int64_t step = (int64_t)(PC1_THREADS / 64) * (64 / S) * PC1_UNROLL;
+        const int64_t steps = (npix + step - 1) / step;
+        // steps per block: at least PC1_BLOCK_BYTES of the cube
+        const int64_t some = (PC1_BLOCK_BYTES + step * bands * 4 - 1) / (step * bands * 4);
+        const int64_t per = std::max<int64_t>(some, (steps + PC1_MAX_BLOCKS - 1) / PC1_MAX_BLOCKS);
+        blocks = (int)((steps + per - 1) / per);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(PC1_THREADS), 0, st, cube, npix, bands,
+                               mean, vec, out, ws, pairs, per * step);
+        };
+        if (S == 8) launch(pc1_project_vec4<8>);
+        else if (S == 16) launch(pc1_project_vec4<16>);
+        else if (S == 32) launch(pc1_project_vec4<32>);
+        else launch(pc1_project_vec4<64>);
     } else {
-        want = (npix + PC1_THREADS - 1) / PC1_THREADS;
+        const int64_t want = (npix + PC1_THREADS - 1) / PC1_THREADS;
         blocks = (int)(want < PC1_MAX_BLOCKS ? want : PC1_MAX_BLOCKS);
         hipLaunchKernelGGL(pc1_project_scalar, dim3(blocks), dim3(PC1_THREADS), 0, st, cube, npix,
                            bands, mean, vec, out, ws, pairs);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !ws) return (int)e;
-    const int64_t nb = (npix + PC1_THREADS - 1) / PC1_THREADS;
-    const int nblocks = (int)(nb < (int64_t)num_cu ? nb : (int64_t)num_cu);
-    hipLaunchKernelGGL(pc1_normalise, dim3(nblocks), dim3(PC1_THREADS), 0, st, ws, npix, pairs,
-                       blocks, out);
-    return (int)hipGetLastError();
+    return launch_pc1_normalise(ws, npix, pairs, blocks, out, num_cu, stream);
 }
 
 }  // namespace knnf
