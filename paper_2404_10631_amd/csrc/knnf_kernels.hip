@@ -154,111 +154,33 @@ __device__ __forceinline__ uint64_t merge64(uint64_t a, uint64_t b) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// ---- segmented sorts: the Q queries of a tile sorted together.  Segment q
-// (64 elements) lives in lanes q*P .. q*P+P-1, P = 64 / E; lane L holds
-// elements e = (L % P) * E + r in x[r], r < E.
+// ---- segmented sorts: the Q queries of a tile sorted together.  A segment of
+// P lanes (4 or 8) holds one query's P * E elements, E registers a lane; the
+// sorted order is element lp * E + r in register r of the segment's lane lp.
 //
-// The network is the all-ascending form of the bitonic sort: stage KS first
-// compares e with its mirror e ^ (KS - 1) inside each block of KS elements
-// (both halves ascending -> the smaller KS/2 in the lower half, as two
-// bitonic halves), then half-cleaners compare e with e ^ D, D = KS/4 .. 1.
-// The lower element of every pair takes the minimum, so pairs inside a lane
-// need no direction, and cross-lane partners are lane ^ 1, 2, 3 or 7 for
-// E >= 8: all DPP lane permutations within a row.
+// Each lane sorts its E elements (Batcher's odd-even merge sort), then runs of
+// E, 2E, 4E elements are merged bitonically: stage KS compares e with its
+// mirror e ^ (KS - 1) (both runs ascending -> the smaller half in the lower
+// lanes, as two bitonic halves), then half-cleaners compare e with e ^ D across
+// lanes (D >= E) and within the lane.
+//
+// Lanes that keep the larger element of a cross-lane pair hold their values
+// negated (u16 pairs: complemented) and keep the smaller of their own and the
+// partner's negated value: one instruction per element for binary32 values
+// (v_min_f32 with a negated DPP operand) and two for u16 pairs (v_not_b32 with
+// DPP, v_pk_min_u16), where a select by lane took two and four.  Which lanes
+// those are changes from stage to stage (lane bit KS / 2E of a mirror stage,
+// D / E of a half-cleaner); the XOR in between issues at twice the rate of a
+// minimum (2.4 against 4.5 cycles per wavefront on this chip).  Within a lane a
+// bitonic sequence may lie in either direction, so odd lanes are left negated,
+// hence sorted the other way round, while lanes merge their own elements; a
+// mirror stage, whose partner lane differs in bit 0, then pairs equal registers,
+// and a half-cleaner with lane ^ 1 opposite ones.
+//
+// 8 queries x 64 elements, VALU cycles of a wavefront by the measured rates of
+// its instructions: u16 pairs 1,050 (1,394 with selects by lane and bitonic
+// sorts within the lane), binary32 840 (967).
 
-// Value of lane L ^ X (X in 1, 2, 3, 7, 15 via DPP; others via xlane).
-template <int X>
-__device__ __forceinline__ uint32_t lanex(uint32_t v) {
-    if constexpr (X == 1) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // quad_perm 1,0,3,2
-    } else if constexpr (X == 2) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);  // quad_perm 2,3,0,1
-    } else if constexpr (X == 3) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x1B, 0xF, 0xF, false);  // quad_perm 3,2,1,0
-    } else if constexpr (X == 7) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);  // row_half_mirror
-    } else if constexpr (X == 15) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row_mirror
-    } else {
-        static_assert(X == 4 || X == 8 || X == 16 || X == 32, "unsupported lane permutation");
-        return xlane<X>(v);
-    }
-}
-
-// The u32 network sorts bit patterns of non-negative binary32 values (pass-A
-// distances, +inf padding): their unsigned order is their numeric order, so
-// a cross-lane pair keeps max(x, p) or min(x, p) as the median of x, p and
-// +inf or -inf (one v_med3_f32).
-__device__ __forceinline__ float side_sel(bool upper) {
-    return __int_as_float(upper ? 0x7f800000 : (int)0xff800000u);
-}
-__device__ __forceinline__ uint32_t keep_side(uint32_t x, uint32_t p, float sel) {
-    return __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(x), __uint_as_float(p), sel));
-}
-
-template <int E, int KS>
-__device__ __forceinline__ void seg_mirror_u32(uint32_t (&x)[E], int lp) {
-    if constexpr (KS <= E) {
-#pragma unroll
-        for (int r = 0; r < E; ++r) {
-            if (r & (KS / 2)) continue;
-            constexpr int M = KS - 1;
-            const uint32_t a = x[r], b = x[r ^ M];
-            x[r] = min(a, b);
-            x[r ^ M] = max(a, b);
-        }
-    } else {
-        const float sel = side_sel((lp & (KS / (2 * E))) != 0);
-        uint32_t p[E];
-#pragma unroll
-        for (int r = 0; r < E; ++r) p[r] = lanex<KS / E - 1>(x[E - 1 - r]);
-#pragma unroll
-        for (int r = 0; r < E; ++r) x[r] = keep_side(x[r], p[r], sel);
-    }
-}
-
-template <int E, int D>
-__device__ __forceinline__ void seg_half_u32(uint32_t (&x)[E], int lp) {
-    if constexpr (D < E) {
-#pragma unroll
-        for (int r = 0; r < E; ++r) {
-            if (r & D) continue;
-            const uint32_t a = x[r], b = x[r | D];
-            x[r] = min(a, b);
-            x[r | D] = max(a, b);
-        }
-    } else {
-        const float sel = side_sel((lp & (D / E)) != 0);
-#pragma unroll
-        for (int r = 0; r < E; ++r) x[r] = keep_side(x[r], lanex<D / E>(x[r]), sel);
-    }
-}
-
-template <int E, int KS, int D>
-__device__ __forceinline__ void seg_halves_u32(uint32_t (&x)[E], int lp) {
-    if constexpr (D >= 1) {
-        seg_half_u32<E, D>(x, lp);
-        seg_halves_u32<E, KS, D / 2>(x, lp);
-    }
-}
-
-template <int E, int KS, int SEG = WAVE>
-__device__ __forceinline__ void seg_stage_u32(uint32_t (&x)[E], int lp) {
-    seg_mirror_u32<E, KS>(x, lp);
-    seg_halves_u32<E, KS, KS / 4>(x, lp);
-    if constexpr (KS < SEG) seg_stage_u32<E, KS * 2, SEG>(x, lp);
-}
-
-template <int E, int SEG = WAVE>
-__device__ __forceinline__ void seg_sort_u32(uint32_t (&x)[E], int lp) {
-    seg_stage_u32<E, 2, SEG>(x, lp);
-}
-
-// ---- the same network on pairs of 16-bit keys: register r of lane L holds
-// element (L % P) * E + r of two independent segments, one in each half,
-// sorted together with packed unsigned 16-bit min / max (v_pk_min_u16,
-// v_pk_max_u16: integer instructions).  Cross-lane pairs keep min or max by
-// lane.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
@@ -268,66 +190,142 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
                                                                   __builtin_bit_cast(u16x2, b)));
 }
-__device__ __forceinline__ uint32_t pk_keep(uint32_t x, uint32_t p, bool upper) {
-    return upper ? pk_max(x, p) : pk_min(x, p);
-}
 
-template <int E, int KS>
-__device__ __forceinline__ void seg_mirror_pk(uint32_t (&x)[E], int lp) {
-    if constexpr (KS <= E) {
+// Register kinds of the network.  FLIP: the XOR that negates; cx: compare-
+// exchange within a lane; cross_same<X>: each register keeps the smaller of its
+// own value and the negated one of lane L ^ X (X = 1, 2, 3: quad_perm; 7:
+// row_half_mirror); cross_opposite1: of lane L ^ 1, registers paired r, E-1-r.
+struct PairU16 {  // two u16 keys, each half a segment of its own
+    static constexpr uint32_t FLIP = ~0u;
+    static __device__ __forceinline__ void cx(uint32_t& a, uint32_t& b) {
+        const uint32_t lo = pk_min(a, b), hi = pk_max(a, b);
+        a = lo;
+        b = hi;
+    }
+    template <int X>
+    static __device__ __forceinline__ uint32_t keep(uint32_t x, uint32_t y) {
+        constexpr int ctrl = X == 1 ? 0xB1 : X == 2 ? 0x4E : X == 3 ? 0x1B : 0x141;
+        return pk_min(x, ~(uint32_t)__builtin_amdgcn_mov_dpp((int)y, ctrl, 0xF, 0xF, false));
+    }
+    template <int X, int E>
+    static __device__ __forceinline__ void cross_same(uint32_t (&x)[E]) {
 #pragma unroll
-        for (int r = 0; r < E; ++r) {
-            if (r & (KS / 2)) continue;
-            constexpr int M = KS - 1;
-            const uint32_t a = x[r], b = x[r ^ M];
-            x[r] = pk_min(a, b);
-            x[r ^ M] = pk_max(a, b);
+        for (int r = 0; r < E; ++r) x[r] = keep<X>(x[r], x[r]);
+    }
+    template <int E>
+    static __device__ __forceinline__ void cross_opposite1(uint32_t (&x)[E]) {
+#pragma unroll
+        for (int r = 0; r < E / 2; ++r) {
+            const uint32_t a = x[r], b = x[E - 1 - r];
+            x[r] = keep<1>(a, b);
+            x[E - 1 - r] = keep<1>(b, a);
         }
-    } else {
-        const bool upper = (lp & (KS / (2 * E))) != 0;
-        uint32_t p[E];
-#pragma unroll
-        for (int r = 0; r < E; ++r) p[r] = lanex<KS / E - 1>(x[E - 1 - r]);
-#pragma unroll
-        for (int r = 0; r < E; ++r) x[r] = pk_keep(x[r], p[r], upper);
     }
-}
-
-template <int E, int D>
-__device__ __forceinline__ void seg_half_pk(uint32_t (&x)[E], int lp) {
-    if constexpr (D < E) {
+};
+struct KeyF32 {  // bit patterns of binary32 values (no -0 beside +0, no NaN that matters)
+    static constexpr uint32_t FLIP = 0x80000000u;
+    static __device__ __forceinline__ void cx(uint32_t& a, uint32_t& b) {
+        // (fminf and fmaxf would add canonicalising instructions)
+        uint32_t lo, hi;
+        asm("v_min_f32 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
+        asm("v_max_f32 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
+        a = lo;
+        b = hi;
+    }
+// (a DPP operand must not have been written in the two instructions before: s_nop 1)
+#define KNNF_DPP_ROW " row_mask:0xf bank_mask:0xf\n\t"
+#define KNNF_KEEP4(CTRL)                                                             \
+    asm("s_nop 1\n\t"                                                                \
+        "v_min_f32_dpp %0, -%0, %0 " CTRL KNNF_DPP_ROW                               \
+        "v_min_f32_dpp %1, -%1, %1 " CTRL KNNF_DPP_ROW                               \
+        "v_min_f32_dpp %2, -%2, %2 " CTRL KNNF_DPP_ROW                               \
+        "v_min_f32_dpp %3, -%3, %3 " CTRL KNNF_DPP_ROW                               \
+        : "+v"(x[r]), "+v"(x[r + 1]), "+v"(x[r + 2]), "+v"(x[r + 3]))
+    template <int X, int E>
+    static __device__ __forceinline__ void cross_same(uint32_t (&x)[E]) {
 #pragma unroll
-        for (int r = 0; r < E; ++r) {
-            if (r & D) continue;
-            const uint32_t a = x[r], b = x[r | D];
-            x[r] = pk_min(a, b);
-            x[r | D] = pk_max(a, b);
+        for (int r = 0; r < E; r += 4) {
+            if constexpr (X == 1) KNNF_KEEP4("quad_perm:[1,0,3,2]");
+            else if constexpr (X == 2) KNNF_KEEP4("quad_perm:[2,3,0,1]");
+            else if constexpr (X == 3) KNNF_KEEP4("quad_perm:[3,2,1,0]");
+            else KNNF_KEEP4("row_half_mirror");
         }
-    } else {
-        const bool upper = (lp & (D / E)) != 0;
+    }
+    template <int E>
+    static __device__ __forceinline__ void cross_opposite1(uint32_t (&x)[E]) {
 #pragma unroll
-        for (int r = 0; r < E; ++r) x[r] = pk_keep(x[r], lanex<D / E>(x[r]), upper);
+        for (int r = 0; r < E / 2; r += 2) {
+            uint32_t a, b;
+            asm("s_nop 1\n\t"
+                "v_min_f32_dpp %0, -%2, %4 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
+                "v_min_f32_dpp %1, -%3, %5 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
+                "v_min_f32_dpp %2, -%4, %2 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
+                "v_min_f32_dpp %3, -%5, %3 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
+                : "=&v"(a), "=&v"(b), "+v"(x[E - 1 - r]), "+v"(x[E - 2 - r])
+                : "v"(x[r]), "v"(x[r + 1]));
+            x[r] = a;
+            x[r + 1] = b;
+        }
     }
+#undef KNNF_KEEP4
+#undef KNNF_DPP_ROW
+};
+
+// Ascending sort of the lane's E elements.
+template <class T, int E>
+__device__ __forceinline__ void lane_sort(uint32_t (&x)[E]) {
+#pragma unroll
+    for (int p = 1; p < E; p *= 2)
+#pragma unroll
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int j = k % p; j + k < E; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < E && (i + j) / (2 * p) == (i + j + k) / (2 * p))
+                        T::cx(x[i + j], x[i + j + k]);
 }
 
-template <int E, int KS, int D>
-__device__ __forceinline__ void seg_halves_pk(uint32_t (&x)[E], int lp) {
-    if constexpr (D >= 1) {
-        seg_half_pk<E, D>(x, lp);
-        seg_halves_pk<E, KS, D / 2>(x, lp);
+// Ascending order of the lane's bitonic sequence.
+template <class T, int E>
+__device__ __forceinline__ void lane_merge(uint32_t (&x)[E]) {
+#pragma unroll
+    for (int d = E / 2; d >= 1; d /= 2)
+#pragma unroll
+        for (int r = 0; r < E; ++r)
+            if (!(r & d)) T::cx(x[r], x[r | d]);
+}
+
+template <class T, int E>
+__device__ __forceinline__ void flip_lanes(uint32_t (&x)[E], uint32_t mask) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) x[r] ^= mask;
+}
+// Ascending sort of each segment of P lanes.
+template <class T, int P, int E>
+__device__ __forceinline__ void seg_sort(uint32_t (&x)[E], int lp) {
+    static_assert(P == 4 || P == 8, "segment width");
+    const uint32_t m0 = (lp & 1) ? T::FLIP : 0u, m1 = (lp & 2) ? T::FLIP : 0u;
+    flip_lanes<T>(x, m0);
+    lane_sort<T>(x);
+    T::template cross_same<1>(x);  // runs of 2E
+    lane_merge<T>(x);
+    flip_lanes<T>(x, m0 ^ m1);
+    T::template cross_same<3>(x);  // runs of 4E
+    flip_lanes<T>(x, m0 ^ m1);
+    T::cross_opposite1(x);
+    if constexpr (P == 8) {
+        const uint32_t m2 = (lp & 4) ? T::FLIP : 0u;
+        lane_merge<T>(x);
+        flip_lanes<T>(x, m0 ^ m2);
+        T::template cross_same<7>(x);  // runs of 8E
+        flip_lanes<T>(x, m2 ^ m1);
+        T::template cross_same<2>(x);
+        flip_lanes<T>(x, m1 ^ m0);
+        T::cross_opposite1(x);
     }
-}
-
-template <int E, int KS, int SEG>
-__device__ __forceinline__ void seg_stage_pk(uint32_t (&x)[E], int lp) {
-    seg_mirror_pk<E, KS>(x, lp);
-    seg_halves_pk<E, KS, KS / 4>(x, lp);
-    if constexpr (KS < SEG) seg_stage_pk<E, KS * 2, SEG>(x, lp);
-}
-
-template <int E, int SEG>
-__device__ __forceinline__ void seg_sort_pk(uint32_t (&x)[E], int lp) {
-    seg_stage_pk<E, 2, SEG>(x, lp);
+    flip_lanes<T>(x, m0);
+    lane_merge<T>(x);
 }
 
 // Two non-negative binary32 bit patterns (or +inf / NaN bits) as a pair of
@@ -766,7 +764,7 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                 for (int u = 0; u < 8; ++u) xp[u] = pack_up(x[u], x[u + 8]);
             }
             if (lp == 0) S.iq[sq] = iqs;
-            seg_sort_pk<8, WAVE>(xp, lp);
+            seg_sort<PairU16, P>(xp, lp);
             // each group's element m - 1 (lane (m-1) / 8, register (m-1) % 8);
             // at least K candidates lie at or below the larger key
             const int m = (K + 1) / 2;
@@ -839,7 +837,8 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                 }
             }
             if (lp == 0) S.iq[sq] = iqs;
-            seg_sort_u32<EA, GS>(x, lp);
+            static_assert(NG == 1, "one group of P * EA elements");
+            seg_sort<KeyF32, P>(x, lp);
             // each group's element m - 1 (group lane (m-1) / EA, register
             // (m-1) % EA); the largest of the NG goes to the group-0 holder,
             // which writes the bound
@@ -1070,7 +1069,7 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
             const uint32_t dh = (uint32_t)(S.pend[sq][e] >> 32);
             x[u] = (own && e < cq) ? ((min(dh, 0x7f7fffc0u) & ~63u) | (uint32_t)e) : 0x7f800000u;
         }
-        seg_sort_u32<E>(x, lp);
+        seg_sort<KeyF32, P>(x, lp);
         uint64_t y[E];
 #pragma unroll
         for (int u = 0; u < E; ++u) y[u] = x[u] < 0x7f800000u ? S.pend[sq][x[u] & 63u] : KEY_INF;
