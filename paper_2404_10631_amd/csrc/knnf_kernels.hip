@@ -58,6 +58,13 @@ constexpr int WAVE = 64;
 constexpr int A2ROWS = 64;  // window rows per block of the LDS a2 table
 constexpr int A2PAD = 4;    // padding rows (+inf) so a 4-row group may start anywhere
 constexpr int MAXC = 16;
+// Pass A looks at 64 candidates per query for K up to SMALL_K (8-query tiles),
+// 128 beyond.  The larger block's tighter bound lets fewer candidates through
+// (K = 40: 45 instead of 48 of the 64 buffer slots, and 1 % instead of 4 % of
+// the queries overflow them), but takes twice the distances and a network of
+// twice the registers (380 x 480, K = 24: 52.3 against 54.0 us with the larger
+// block; K = 30: 0.8 % of the queries would overflow, 0.1 % with the larger).
+constexpr int SMALL_K = 28;
 
 __device__ __forceinline__ int lane_id() {
     return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -202,24 +209,40 @@ struct PairU16 {  // two u16 keys, each half a segment of its own
         a = lo;
         b = hi;
     }
-    template <int X>
-    static __device__ __forceinline__ uint32_t keep(uint32_t x, uint32_t y) {
-        constexpr int ctrl = X == 1 ? 0xB1 : X == 2 ? 0x4E : X == 3 ? 0x1B : 0x141;
-        return pk_min(x, ~(uint32_t)__builtin_amdgcn_mov_dpp((int)y, ctrl, 0xF, 0xF, false));
+// n0 .. n3 = ~y0 .. ~y3 of the lanes CTRL selects (a DPP operand must not have
+// been written in the two instructions before: s_nop 1)
+#define KNNF_NOT4(CTRL)                                                          \
+    asm("s_nop 1\n\t"                                                            \
+        "v_not_b32_dpp %0, %4 " CTRL " row_mask:0xf bank_mask:0xf\n\t"           \
+        "v_not_b32_dpp %1, %5 " CTRL " row_mask:0xf bank_mask:0xf\n\t"           \
+        "v_not_b32_dpp %2, %6 " CTRL " row_mask:0xf bank_mask:0xf\n\t"           \
+        "v_not_b32_dpp %3, %7 " CTRL " row_mask:0xf bank_mask:0xf"               \
+        : "=&v"(n[r]), "=&v"(n[r + 1]), "=&v"(n[r + 2]), "=&v"(n[r + 3])         \
+        : "v"(x[r]), "v"(x[r + 1]), "v"(x[r + 2]), "v"(x[r + 3]))
+    template <int X, int E>
+    static __device__ __forceinline__ void partner(const uint32_t (&x)[E], uint32_t (&n)[E]) {
+#pragma unroll
+        for (int r = 0; r < E; r += 4) {
+            if constexpr (X == 1) KNNF_NOT4("quad_perm:[1,0,3,2]");
+            else if constexpr (X == 2) KNNF_NOT4("quad_perm:[2,3,0,1]");
+            else if constexpr (X == 3) KNNF_NOT4("quad_perm:[3,2,1,0]");
+            else KNNF_NOT4("row_half_mirror");
+        }
     }
+#undef KNNF_NOT4
     template <int X, int E>
     static __device__ __forceinline__ void cross_same(uint32_t (&x)[E]) {
+        uint32_t n[E];
+        partner<X>(x, n);
 #pragma unroll
-        for (int r = 0; r < E; ++r) x[r] = keep<X>(x[r], x[r]);
+        for (int r = 0; r < E; ++r) x[r] = pk_min(x[r], n[r]);
     }
     template <int E>
     static __device__ __forceinline__ void cross_opposite1(uint32_t (&x)[E]) {
+        uint32_t n[E];
+        partner<1>(x, n);
 #pragma unroll
-        for (int r = 0; r < E / 2; ++r) {
-            const uint32_t a = x[r], b = x[E - 1 - r];
-            x[r] = keep<1>(a, b);
-            x[E - 1 - r] = keep<1>(b, a);
-        }
+        for (int r = 0; r < E; ++r) x[r] = pk_min(x[r], n[E - 1 - r]);
     }
 };
 struct KeyF32 {  // bit patterns of binary32 values (no -0 beside +0, no NaN that matters)
@@ -334,6 +357,14 @@ __device__ __forceinline__ uint32_t pack_up(uint32_t lo, uint32_t hi) {
     return ((lo + 0xffffu) >> 16) | ((hi + 0xffffu) & 0xffff0000u);
 }
 
+// Buffer slots are prefilled with the query's own index and, as distance bits,
+// PAD + 64 slot: above those of any candidate that the packed final selection
+// orders (distance bits up to BIG; queries with a larger bound take the exact
+// merge), and no two empty slots alike once the slot bits are set aside.
+constexpr uint32_t PAD = 0x7f7f0000u;
+constexpr uint32_t BIG = PAD - 1;
+constexpr int ROWS = 32;  // neighbour rows staged at a time in Eq. 2 (four classes)
+
 // Per-wavefront LDS state of one tile of QR x QC query pixels.
 template <int QR, int QC>
 struct alignas(16) TileState {
@@ -342,12 +373,12 @@ struct alignas(16) TileState {
         uint64_t pend[Q][WAVE];  // keys of candidates that passed the bound, unsorted
         float sums[Q][MAXC + 1]; // class sums for the argmax (after the final selection);
                                  // the odd row stride spreads the queries over the banks
+        float4 rows[Q][ROWS + 1];// four classes: the neighbours' probability rows, in order
     };
     // sorted top-K linear indices (first listn valid); rows padded by 16
     // bytes so that the queries' rows start on different banks (Eq. 2 reads
     // the same entry of every query at once, the final selection stores them)
     uint32_t list[Q][WAVE + 4];
-                              // before the scan: pass-A block distances
     uint32_t tauhi[Q];        // distance bits of the current bound on the K-th key
     float iq[Q];              // I of each query pixel (NaN for pixels off the frame)
     int listn[Q];             // valid list entries (<= K)
@@ -651,213 +682,385 @@ __device__ __forceinline__ float gather_add24(float s, const char* __restrict__ 
     return s;
 }
 
-// Process one tile: query pixels (r0 + qr, c0 + qc), qr < QR, qc < QC.
-// NA: pass-A block candidates per query (128 or 64; 64 for 16-query tiles).
-// NG: groups the NA candidates are split into for the bound (1, 2 or 4).
-template <int QR, int QC, bool PRUNE, int NA = (QR * QC == 8 ? 128 : WAVE),
-          int NG = (NA == 128 ? 2 : 1)>
-__device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const FrameDesc& f, int r0,
-                                             int c0, int lpr) {
-    constexpr int Q = QR * QC;
-    const int L = lane_id();
-    const int H = f.H, W = f.W, R = f.R, K = f.K, C = f.C;
-    const float lam = f.lambda;
-    const int nqr = min(QR, H - r0), nqc = min(QC, W - c0);
-    const float* __restrict__ pc1 = f.pc1;
-    const float qnan = __int_as_float(0x7fc00000);
-    const float pinf = __int_as_float(0x7f800000);
-
-    if (L < Q) S.listn[L] = 0;
-
-    // ---- pass A.  Any set of block candidates of which at least K have a
-    // distance <= d bounds the query's final K-th key from above by
-    // (d, max index).  The block's NA candidates are split into NG groups of
-    // the same spatial spread; with m = ceil(K / NG), the largest of the
-    // groups' m-th smallest distances is such a d (NG = 1: the block's K-th
-    // smallest).  All Q blocks are evaluated and sorted together: segment q
-    // of the wavefront (P lanes) holds query q's NA block candidates, EA per
-    // lane; group g is the segment's lanes g*LG .. g*LG + LG - 1.
-    constexpr int E = Q, P = WAVE / Q;          // final selection: 64 slots per query
-    constexpr int EA = NA / P;                  // pass-A candidates per lane
+// Pass A.  Any set of block candidates of which at least K have a distance <= d
+// bounds the query's final K-th key from above by (d, max index).  The block's
+// NA candidates (128 or 64) are split into two groups of the same spatial
+// spread; with m = ceil(K / 2), the larger of the groups' m-th smallest
+// distances is such a d.  All Q blocks are evaluated and sorted together:
+// segment q of the wavefront (P lanes) holds query q's block, the groups as the
+// low and high halves of NR registers of 16-bit keys rounded up.
+template <int QR, int QC, int NA>
+__device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
+                                           int nqr, int nqc) {
+    constexpr int Q = QR * QC, P = WAVE / Q, EA = NA / P, NR = EA / 2;
     constexpr int LNA = NA == 128 ? 7 : 6;
-    constexpr int LG = P / NG, GS = NA / NG;    // lanes and candidates per group
-    constexpr bool PK = NA == 128 && NG == 2;   // two groups as 16-bit key pairs
-    static_assert(NA == WAVE || (NA == 128 && Q == 8), "pass-A block size");
-    static_assert((NG == 1 || NG == 2 || NG == 4) && LG >= 1 && (WAVE + NG - 1) / NG <= GS,
-                  "pass-A groups");
+    static_assert((NA == 128 && Q == 8) || NA == 64, "pass-A block size");
+    const int L = lane_id();
+    const int H = f.H, W = f.W, R = f.R, K = f.K;
+    const float lam = f.lambda;
+    const float* __restrict__ pc1 = f.pc1;
     const int sq = L / P, lp = L % P;  // this lane's query (segment) and slot in it
     const int sqr = sq / QC, sqc = sq % QC;
     const bool sok = sqr < nqr && sqc < nqc;
     const bool off32 = (uint64_t)H * (uint64_t)W <= (1u << 30);  // band byte offsets fit 32 bits
-    {
-        const int r = r0 + sqr, c = c0 + sqc;
-        const int i0w = max(0, r - R), i1w = min(H - 1, r + R);
-        const int nr = i1w - i0w + 1;
-        const int lbr = nr >= 8 ? 3 : (nr >= 4 ? 2 : (nr >= 2 ? 1 : 0));
-        const int br = 1 << lbr;
-        const int lbc = LNA - lbr;
-        const int bc = 1 << lbc;
-        const int rb = min(max(r - br / 2, i0w), i1w - br + 1);
-        const int cb = max(0, min(c - bc / 2, W - bc));
-        // I of the segment's query pixel (NaN for pixels off the frame)
-        const float iqs = sok ? pc1[(uint32_t)r * (uint32_t)W + (uint32_t)c] : qnan;
-        const float frq = feat(lam, r), fcq = feat(lam, c);
-        // Element e = u * P + lp of the block is row rb + (e >> lbc), column
-        // cb + (e & (bc - 1)): the P lanes of a segment read P consecutive
-        // columns of one row per load, so a load touches few cache lines.
-        // Every lane loads (columns past the right edge clamped and given
-        // +inf; rows rb .. rb+br-1 are inside the frame even for queries off
-        // its bottom edge), so all EA loads are in flight together.
-        if constexpr (PK) {
-            // 128 candidates as 8 registers of 16-bit key pairs: group 0 in
-            // the low halves, group 1 in the high halves, each group's 64
-            // keys (8 per lane) sorted by one packed network
-            uint32_t xp[8];
-            if (W >= 16 && off32 && !ballot(lbr != 3)) {
-                // every block is 8 x 16: lane lp takes columns cb + 2 lp
-                // (group 0) and cb + 2 lp + 1 (group 1) of rows rb .. rb + 7,
-                // so both groups hold every row and alternate columns
-                const int j = cb + 2 * lp;
-                const uint32_t o4 = ((uint32_t)rb * (uint32_t)W + (uint32_t)j) * 4u;
-                const char* __restrict__ pcb = (const char*)pc1;
-                float p0[8], p1[8];
+    const int r = r0 + sqr, c = c0 + sqc;
+    const int i0w = max(0, r - R), i1w = min(H - 1, r + R);
+    const int nr = i1w - i0w + 1;
+    const int lbr = nr >= 8 ? 3 : (nr >= 4 ? 2 : (nr >= 2 ? 1 : 0));
+    const int br = 1 << lbr;
+    const int lbc = LNA - lbr;
+    const int bc = 1 << lbc;
+    const int rb = min(max(r - br / 2, i0w), i1w - br + 1);
+    const int cb = max(0, min(c - bc / 2, W - bc));
+    // I of the segment's query pixel (NaN for pixels off the frame)
+    const float iqs = sok ? pc1[(uint32_t)r * (uint32_t)W + (uint32_t)c] : __int_as_float(0x7fc00000);
+    const float frq = feat(lam, r), fcq = feat(lam, c);
+    // Every lane loads (columns past the right edge clamped and given +inf;
+    // rows rb .. rb+br-1 are inside the frame even for queries off its bottom
+    // edge), so all EA loads are in flight together.
+    uint32_t xp[NR];
+    if (W >= NA / 8 && off32 && !ballot(lbr != 3)) {
+        // every block is 8 rows x NA / 8 columns
+        const char* __restrict__ pcb = (const char*)pc1;
+        float pv[EA];
+        if constexpr (NA == 128) {
+            // lane lp takes columns cb + 2 lp (group 0) and cb + 2 lp + 1 (group
+            // 1): both groups hold every row and alternate columns
+            const int j = cb + 2 * lp;
+            const uint32_t o4 = ((uint32_t)rb * (uint32_t)W + (uint32_t)j) * 4u;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const char* row = pcb + (o4 + (uint32_t)u * (uint32_t)W * 4u);
-                    p0[u] = *(const float*)row;
-                    p1[u] = *(const float*)(row + 4);
-                }
-                const float b0 = fcq - feat(lam, j), b1 = fcq - feat(lam, j + 1);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const float a = frq - feat(lam, rb + u);
-                    const float a2 = a * a;
-                    const float e0 = iqs - p0[u], e1 = iqs - p1[u];
-                    // NaN bits for a query off the frame (segment unused)
-                    xp[u] = pack_up(__float_as_uint(fmaf(e0, e0, fmaf(b0, b0, a2))),
-                                    __float_as_uint(fmaf(e1, e1, fmaf(b1, b1, a2))));
-                }
-            } else {
-                // element e = u * 8 + lp of the block (u < 16): group 0 the
-                // elements u < 8, group 1 the rest
-                float pv[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int e = u * P + lp;
-                    const int i = rb + (e >> lbc);
-                    const int j = min(cb + (e & (bc - 1)), W - 1);
-                    pv[u] = pc1[(uint32_t)i * (uint32_t)W + (uint32_t)j];
-                }
-                uint32_t x[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int e = u * P + lp;
-                    const int i = rb + (e >> lbc);
-                    const int j = cb + (e & (bc - 1));
-                    const float a = frq - feat(lam, i);
-                    const float b = fcq - feat(lam, j);
-                    const float ee = iqs - pv[u];
-                    const uint32_t d = __float_as_uint(fmaf(ee, ee, fmaf(b, b, a * a)));
-                    x[u] = (sok && j < W) ? d : 0x7f800000u;  // +inf: no candidate
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) xp[u] = pack_up(x[u], x[u + 8]);
+            for (int u = 0; u < 8; ++u) {
+                const char* row = pcb + (o4 + (uint32_t)u * (uint32_t)W * 4u);
+                pv[2 * u] = *(const float*)row;
+                pv[2 * u + 1] = *(const float*)(row + 4);
             }
-            if (lp == 0) S.iq[sq] = iqs;
-            seg_sort<PairU16, P>(xp, lp);
-            // each group's element m - 1 (lane (m-1) / 8, register (m-1) % 8);
-            // at least K candidates lie at or below the larger key
-            const int m = (K + 1) / 2;
-            const uint32_t v = xp[uni((m - 1) % 8)];  // uniform register index
-            const uint32_t kk = max(v & 0xffffu, v >> 16);
-            if (lp == (m - 1) / 8) S.tauhi[sq] = sok ? kk << 16 : 0u;
+            const float b0 = fcq - feat(lam, j), b1 = fcq - feat(lam, j + 1);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float a = frq - feat(lam, rb + u);
+                const float a2 = a * a;
+                const float e0 = iqs - pv[2 * u], e1 = iqs - pv[2 * u + 1];
+                // NaN bits for a query off the frame (segment unused)
+                xp[u] = pack_up(__float_as_uint(fmaf(e0, e0, fmaf(b0, b0, a2))),
+                                __float_as_uint(fmaf(e1, e1, fmaf(b1, b1, a2))));
+            }
         } else {
-            uint32_t x[EA];
-            float pv[EA];
-            // full blocks: lane lp takes block column offset jl (a permutation of
-            // 0..7), so that the columns of every group spread over the block
-            const int jl = NG * (lp % LG) + lp / LG;
-            if (EA == 8 && NA == WAVE && W >= 8 && !ballot(lbr != 3)) {
-                // every block is 8 x 8 (P = 8): element u * 8 + lp is row rb + u,
-                // column cb + jl < W, so a lane's column term is computed once
-                const int j = cb + jl;
-                const uint32_t o = (uint32_t)rb * (uint32_t)W + (uint32_t)j;
+            // lane lp takes columns cb + lp (+ P for four lanes a segment), even
+            // rows for group 0 and odd rows for group 1
+            const int j = cb + lp;
+            const uint32_t o4 = ((uint32_t)rb * (uint32_t)W + (uint32_t)j) * 4u;
 #pragma unroll
-                for (int u = 0; u < EA; ++u) pv[u] = pc1[o + (uint32_t)u * (uint32_t)W];
-                const float b = fcq - feat(lam, j);
+            for (int h = 0; h < 8 / P; ++h)
 #pragma unroll
-                for (int u = 0; u < EA; ++u) {
-                    const float a = frq - feat(lam, rb + u);
-                    const float ee = iqs - pv[u];
-                    const uint32_t d = __float_as_uint(fmaf(ee, ee, fmaf(b, b, a * a)));
-                    x[u] = d;  // NaN bits for a query off the frame (segment unused)
-                }
-            } else if (EA == 16 && NA == 128 && W >= 16 && off32 && !ballot(lbr != 3)) {
-                // every block is 8 x 16 (P = 8): element u * 8 + lp is row
-                // rb + u / 2, column cb + 8 (u % 2) + jl < W, so a lane has two
-                // column terms and each row term serves two elements.  Byte
-                // offsets from the band's base fit 32 bits (off32): one add per
-                // row, the second column half as the load's immediate offset.
-                const int j = cb + jl;
-                const uint32_t o4 = ((uint32_t)rb * (uint32_t)W + (uint32_t)j) * 4u;
-                const char* __restrict__ pcb = (const char*)pc1;
+                for (int u = 0; u < 8; ++u)
+                    pv[8 * h + u] = *(const float*)(pcb + (o4 + (uint32_t)u * (uint32_t)W * 4u) + 4 * P * h);
 #pragma unroll
-                for (int u = 0; u < EA; ++u)
-                    pv[u] = *(const float*)(pcb + (o4 + (uint32_t)(u >> 1) * (uint32_t)W * 4u) +
-                                            32u * (u & 1));
-                const float b0 = fcq - feat(lam, j), b1 = fcq - feat(lam, j + 8);
+            for (int h = 0; h < 8 / P; ++h) {
+                const float b = fcq - feat(lam, j + P * h);
 #pragma unroll
-                for (int u = 0; u < EA; u += 2) {
-                    const float a = frq - feat(lam, rb + (u >> 1));
-                    const float a2 = a * a;
-                    const float e0 = iqs - pv[u], e1 = iqs - pv[u + 1];
-                    const uint32_t d0 = __float_as_uint(fmaf(e0, e0, fmaf(b0, b0, a2)));
-                    const uint32_t d1 = __float_as_uint(fmaf(e1, e1, fmaf(b1, b1, a2)));
-                    x[u] = d0;  // NaN bits for a query off the frame (segment unused)
-                    x[u + 1] = d1;
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < EA; ++u) {
-                    const int e = u * P + lp;
-                    const int i = rb + (e >> lbc);
-                    const int j = min(cb + (e & (bc - 1)), W - 1);
-                    pv[u] = pc1[(uint32_t)i * (uint32_t)W + (uint32_t)j];
-                }
-#pragma unroll
-                for (int u = 0; u < EA; ++u) {
-                    const int e = u * P + lp;
-                    const int i = rb + (e >> lbc);
-                    const int j = cb + (e & (bc - 1));
-                    const float a = frq - feat(lam, i);
-                    const float b = fcq - feat(lam, j);
-                    const float ee = iqs - pv[u];
-                    const uint32_t d = __float_as_uint(fmaf(ee, ee, fmaf(b, b, a * a)));
-                    x[u] = (sok && j < W) ? d : 0x7f800000u;  // +inf: no candidate
+                for (int u = 0; u < 4; ++u) {
+                    const float a0 = frq - feat(lam, rb + 2 * u), a1 = frq - feat(lam, rb + 2 * u + 1);
+                    const float e0 = iqs - pv[8 * h + 2 * u], e1 = iqs - pv[8 * h + 2 * u + 1];
+                    xp[4 * h + u] = pack_up(__float_as_uint(fmaf(e0, e0, fmaf(b, b, a0 * a0))),
+                                            __float_as_uint(fmaf(e1, e1, fmaf(b, b, a1 * a1))));
                 }
             }
-            if (lp == 0) S.iq[sq] = iqs;
-            static_assert(NG == 1, "one group of P * EA elements");
-            seg_sort<KeyF32, P>(x, lp);
-            // each group's element m - 1 (group lane (m-1) / EA, register
-            // (m-1) % EA); the largest of the NG goes to the group-0 holder,
-            // which writes the bound
-            const int m = (K + NG - 1) / NG;
-            const int uk = uni((m - 1) % EA);
-            uint32_t dk = x[uk];  // uniform register index
-            if constexpr (NG > 1) {
-                dk = (lp % LG) == (m - 1) / EA ? dk : 0u;
-                if constexpr (LG == 2) dk = max(dk, xlane<2>(dk));
-                dk = max(dk, xlane<4>(dk));
-            }
-            if (lp == (m - 1) / EA) S.tauhi[sq] = sok ? dk : 0u;
         }
-        wave_sync();
+    } else {
+        // element e = u * P + lp of the block is row rb + (e >> lbc), column cb +
+        // (e & (bc - 1)); group 0 the elements u < NR, group 1 the rest
+        float pv[EA];
+#pragma unroll
+        for (int u = 0; u < EA; ++u) {
+            const int e = u * P + lp;
+            const int i = rb + (e >> lbc);
+            const int j = min(cb + (e & (bc - 1)), W - 1);
+            pv[u] = pc1[(uint32_t)i * (uint32_t)W + (uint32_t)j];
+        }
+        uint32_t x[EA];
+#pragma unroll
+        for (int u = 0; u < EA; ++u) {
+            const int e = u * P + lp;
+            const int i = rb + (e >> lbc);
+            const int j = cb + (e & (bc - 1));
+            const float a = frq - feat(lam, i);
+            const float b = fcq - feat(lam, j);
+            const float ee = iqs - pv[u];
+            const uint32_t d = __float_as_uint(fmaf(ee, ee, fmaf(b, b, a * a)));
+            x[u] = (sok && j < W) ? d : 0x7f800000u;  // +inf: no candidate
+        }
+#pragma unroll
+        for (int u = 0; u < NR; ++u) xp[u] = pack_up(x[u], x[u + NR]);
+    }
+    if (lp == 0) S.iq[sq] = iqs;
+    // prefill the query's buffer slots (see PAD)
+    {
+        const uint32_t own = (uint32_t)r * (uint32_t)W + (uint32_t)c;
+        uint4* dst = (uint4*)S.pend[sq] + lp;
+#pragma unroll
+        for (int u = 0; u < WAVE / 2 / P; ++u) {
+            const uint32_t d = PAD + 128u * (uint32_t)(lp + u * P);
+            dst[u * P] = make_uint4(own, d, own, d + 64u);
+        }
+    }
+    seg_sort<PairU16, P>(xp, lp);
+    // each group's element m - 1 (lane (m-1) / NR, register (m-1) % NR); at
+    // least K candidates lie at or below the larger key
+    const int m = (K + 1) / 2;
+    const uint32_t v = xp[uni((m - 1) % NR)];  // uniform register index
+    const uint32_t kk = max(v & 0xffffu, v >> 16);
+    if (lp == (m - 1) / NR) S.tauhi[sq] = sok ? kk << 16 : 0u;
+}
+
+// Final selection and Eq. 2 of a tile; E: buffer slots per lane (all of them,
+// or the first half where no buffer holds more).
+template <int QR, int QC, int E>
+__device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
+                                            int nqr, int nqc) {
+    constexpr int Q = QR * QC, P = WAVE / Q;
+    const int L = lane_id();
+    const int H = f.H, W = f.W, K = f.K, C = f.C;
+    const int sq = L / P, lp = L % P;
+    const int sqr = sq / QC, sqc = sq % QC;
+    const bool sok = sqr < nqr && sqc < nqc;
+    const bool merged = S.listn[sq] != 0;  // selected by flush_query: the list holds its neighbours
+    const uint32_t pix = (uint32_t)(r0 + sqr) * (uint32_t)W + (uint32_t)(c0 + sqc);
+
+    // One segmented sort of the candidate buffers.  The network sorts 32-bit
+    // packed keys: the distance bits with their 6 low bits replaced by the
+    // buffer slot.  Packed order is exact wherever the distance parts differ;
+    // runs of equal distance parts are then put in (d, idx) order on the full
+    // keys by odd-even transposition (rarely needed).
+    uint32_t x[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        // slot blocks permuted by segment (u ^ sq: E is a power of two), so the
+        // segments' reads of one u spread over the banks
+        const int e = (u ^ (sq & (E - 1))) * P + lp;
+        const uint32_t dh = (uint32_t)(S.pend[sq][e] >> 32);
+        x[u] = (dh & ~63u) | (uint32_t)e;
+    }
+    seg_sort<KeyF32, P>(x, lp);
+    // two neighbours in sorted order share the distance part iff their keys
+    // differ in the slot bits only: (a ^ b) <= 63 (keys are distinct)
+    bool tie = false;
+#pragma unroll
+    for (int u = 0; u + 1 < E; ++u) tie |= (x[u] ^ x[u + 1]) < 64u;
+    {
+        uint32_t nx;  // the next lane's first
+        asm("s_nop 1\n\tv_mov_b32_dpp %0, %1 row_shl:1 row_mask:0xf bank_mask:0xf" : "=v"(nx) : "v"(x[0]));
+        tie |= lp < P - 1 && (x[E - 1] ^ nx) < 64u;
+    }
+    const bool ties = ballot(tie) != 0;
+    uint32_t id[E];
+    if (ties || f.out_nbr || f.out_dist) {
+        uint64_t y[E];
+#pragma unroll
+        for (int u = 0; u < E; ++u) y[u] = S.pend[sq][x[u] & 63u];
+        if (ties) {
+            for (;;) {
+                bool sw = false;
+#pragma unroll
+                for (int ph = 0; ph < 2; ++ph) {
+#pragma unroll
+                    for (int u = ph; u + 1 < E; u += 2) {
+                        const uint64_t a = y[u], b = y[u + 1];
+                        const bool t = b < a;
+                        y[u] = t ? b : a;
+                        y[u + 1] = t ? a : b;
+                        sw |= t;
+                    }
+                    if (ph == 1) {
+                        // pair (lane's last, next lane's first)
+                        const uint64_t nx = (uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)y[0], 0x101, 0xF, 0xF, false) |
+                                            ((uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(y[0] >> 32), 0x101, 0xF, 0xF, false) << 32);
+                        const uint64_t pv = (uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)y[E - 1], 0x111, 0xF, 0xF, false) |
+                                            ((uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(y[E - 1] >> 32), 0x111, 0xF, 0xF, false) << 32);
+                        const bool tn = lp < P - 1 && nx < y[E - 1];  // this lane keeps the smaller
+                        const bool tp = lp > 0 && y[0] < pv;          // this lane keeps the larger
+                        y[E - 1] = tn ? nx : y[E - 1];
+                        y[0] = tp ? pv : y[0];
+                        sw |= tn;
+                    }
+                }
+                if (!ballot(sw)) break;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            const int e = lp * E + u;
+            if (sok && !merged && e < K) {
+                if (f.out_nbr) f.out_nbr[(size_t)pix * K + e] = (int32_t)(uint32_t)y[u];
+                if (f.out_dist) f.out_dist[(size_t)pix * K + e] = __uint_as_float((uint32_t)(y[u] >> 32));
+            }
+            id[u] = (uint32_t)y[u];
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < E; ++u) id[u] = (uint32_t)S.pend[sq][x[u] & 63u];
     }
 
+    // ---- Eq. 2: sums in neighbour order, one lane per (query, class)
+    const uint32_t rowb = (uint32_t)C * 4u;  // bytes per probability row
+    const uint64_t npix = (uint64_t)H * (uint64_t)W;
+    const bool off24 = npix <= (1u << 24) && npix * rowb <= 0xFFFFFFFFull;
+    if (C == 4 && off24 && ((uintptr_t)f.prob & 15) == 0) {
+        // Four classes: every lane gathers its own ranks' rows (16 bytes, all in
+        // flight together); the rows go through LDS, ROWS neighbours at a time,
+        // to the lanes that sum them.  One load of a row serves four classes:
+        // 8 loads and 8 shifts per lane where a gather per class took 40 of
+        // each, in three trips to L2 instead of one.
+        if (ballot(merged)) {
+#pragma unroll
+            for (int u = 0; u < E; ++u) {
+                const int e = lp * E + u;
+                if (merged) id[u] = e < K && sok ? S.list[sq][e] : 0u;
+            }
+        }
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        f4 row[E];
+        if (sok && lp * E < K) {
+#pragma unroll
+            for (int u = 0; u < E; ++u) row[u] = *(const f4*)((const char*)f.prob + (id[u] << 4));
+        }
+        const int q = L >> 2, cl = L & 3;
+        const float* col = (const float*)S.rows[q < Q ? q : 0] + cl;
+        float s = 0.0f;
+        auto put_rows = [&](int h) __attribute__((always_inline)) {
+            wave_sync();  // the buffers, or the rows before, have been read
+            if (sok && lp * E / ROWS == h && lp * E < K) {
+#pragma unroll
+                for (int u = 0; u < E; ++u) *(f4*)&S.rows[sq][lp * E % ROWS + u] = row[u];
+            }
+            wave_sync();
+        };
+        auto add_rows = [&](int n) __attribute__((always_inline)) {
+            int k = 0;
+            for (; k + 8 <= n; k += 8) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = col[4 * (k + u)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s = s + v[u];
+            }
+            for (; k < n; ++k) s = s + col[4 * k];
+        };
+        put_rows(0);
+        add_rows(min(ROWS, K));
+        if constexpr (P * E > ROWS) {
+            if (K > ROWS) {
+                put_rows(1);
+                add_rows(K - ROWS);
+            }
+        }
+        const int qr = q / QC, qc = q % QC;
+        // class map: the lanes of a quad hold the query's four sums
+        const float s0 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0x00, 0xF, 0xF, false));
+        const float s1 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0x55, 0xF, 0xF, false));
+        const float s2 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0xAA, 0xF, 0xF, false));
+        const float s3 = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s), 0xFF, 0xF, 0xF, false));
+        int best = 0;
+        float bs = s0;
+        if (s1 > bs) { bs = s1; best = 1; }
+        if (s2 > bs) { bs = s2; best = 2; }
+        if (s3 > bs) { bs = s3; best = 3; }
+        if (q < Q && qr < nqr && qc < nqc) {
+            const uint32_t px = (uint32_t)(r0 * W + c0) + __umul24((uint32_t)qr, (uint32_t)W) + (uint32_t)qc;
+            *(float*)((char*)f.out_prob + ((px << 4) + (uint32_t)cl * 4u)) = s / (float)K;
+            if (cl == 0) f.out_class[px] = best;
+        }
+        return;
+    }
+    // other class counts: the lists go through LDS, 16 bytes at a time (entries
+    // from K on are never read)
+    if (sok && !merged && lp * E < K) {
+#pragma unroll
+        for (int u = 0; u < E; u += 4)
+            *(uint4*)&S.list[sq][lp * E + u] = make_uint4(id[u], id[u + 1], id[u + 2], id[u + 3]);
+    }
+    wave_sync();
+    // p / C by a reciprocal: (p + 0.5) / C sits at least 1/(2C) >= 1/32 from
+    // an integer and p < 2^10, far beyond the reciprocal's rounding
+    const float rc = __builtin_amdgcn_rcpf((float)C);
+    for (int p = L; p < Q * C; p += WAVE) {
+        const int q = (int)(uint32_t)(((float)p + 0.5f) * rc), cl = p - q * C;
+        const int qr = (int)((uint32_t)q / QC), qc = (int)((uint32_t)q % QC);
+        if (qr >= nqr || qc >= nqc) continue;
+        const uint32_t* lst = S.list[q];
+        float s = 0.0f;
+        int k = 0;
+        if (off24) {
+            const char* __restrict__ base = (const char*)f.prob;
+            const uint32_t cb = (uint32_t)cl * 4u;
+            for (; k + 16 <= K; k += 16) s = gather_add24<16>(s, base, lst + k, rowb, cb);
+            if (k + 8 <= K) {
+                s = gather_add24<8>(s, base, lst + k, rowb, cb);
+                k += 8;
+            }
+            for (; k < K; ++k) s = s + *(const float*)(base + (__umul24(lst[k], rowb) + cb));
+        } else {
+            const char* __restrict__ pb = (const char*)(f.prob + cl);
+            for (; k + 16 <= K; k += 16) s = gather_add<16>(s, pb, lst + k, rowb);
+            if (k + 8 <= K) {
+                s = gather_add<8>(s, pb, lst + k, rowb);
+                k += 8;
+            }
+            for (; k < K; ++k) s = s + *(const float*)(pb + (uint64_t)lst[k] * rowb);
+        }
+        S.sums[q][cl] = s;
+        if (off24) {
+            // the pixel's byte offset in the probability map fits 32 bits
+            const uint32_t pix = (uint32_t)(r0 * W + c0) + __umul24((uint32_t)qr, (uint32_t)W) + (uint32_t)qc;
+            *(float*)((char*)f.out_prob + (__umul24(pix, rowb) + (uint32_t)cl * 4u)) = s / (float)K;
+        } else {
+            const size_t pix = (size_t)(r0 + qr) * W + c0 + qc;
+            f.out_prob[pix * C + cl] = s / (float)K;
+        }
+    }
+    wave_sync();
+    if (L < Q) {
+        const int qr = L / QC, qc = L % QC;
+        if (qr < nqr && qc < nqc) {
+            int best = 0;
+            float bs = S.sums[L][0];
+            for (int cl = 1; cl < C; ++cl) {
+                const float v = S.sums[L][cl];
+                if (v > bs) { bs = v; best = cl; }
+            }
+            if (off24)
+                f.out_class[(uint32_t)(r0 * W + c0) + __umul24((uint32_t)qr, (uint32_t)W) + (uint32_t)qc] = best;
+            else
+                f.out_class[(size_t)(r0 + qr) * W + c0 + qc] = best;
+        }
+    }
+}
+
+// Process one tile: query pixels (r0 + qr, c0 + qc), qr < QR, qc < QC.
+// NA: largest pass-A block (128 candidates per query; 64 for 16-query tiles).
+template <int QR, int QC, bool PRUNE, int NA = (QR * QC == 8 ? 128 : WAVE)>
+__device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const FrameDesc& f, int r0,
+                                             int c0, int lpr) {
+    constexpr int Q = QR * QC;
+    const int L = lane_id();
+    const int H = f.H, W = f.W, R = f.R, K = f.K;
+    const float lam = f.lambda;
+    const int nqr = min(QR, H - r0), nqc = min(QC, W - c0);
+    const float* __restrict__ pc1 = f.pc1;
+    const float pinf = __int_as_float(0x7f800000);
+
+    if (L < Q) S.listn[L] = 0;
+
+    const bool big = NA == 128 && K > SMALL_K;  // block size (see SMALL_K)
+    if (big) {
+        if constexpr (NA == 128) tile_bound<QR, QC, 128>(S, f, r0, c0, nqr, nqc);
+    } else {
+        tile_bound<QR, QC, 64>(S, f, r0, c0, nqr, nqc);
+    }
+    wave_sync();
+
     // Work counter (only reported when f.stats is set): candidate distances
-    // evaluated for on-frame queries; pass A counts its NA block slots.
-    unsigned long long pairs = (unsigned long long)(nqr * nqc) * NA;
+    // evaluated for on-frame queries; pass A counts its block slots.
+    unsigned long long pairs = (unsigned long long)(nqr * nqc) * (big ? 128 : WAVE);
 
     // Uniform per-query values live in VGPRs (read from LDS) to keep the
     // scalar register file free for loop state.  Queries off the frame have
@@ -1038,168 +1241,29 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
         }
     }
 
-    // ---- final selection; neighbour outputs
+    // ---- final selection, Eq. 2, outputs
+    int most = 0;
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
+    for (int q = 0; q < Q; ++q) {
         if (L == 0) S.cnt[q] = cnt[q];
+        most = max(most, uni(cnt[q]));
+    }
     wave_sync();
     // queries whose buffer overflowed during the scan already hold a sorted
-    // list: merge their last candidates one query at a time (rare)
-    for (int q = 0; q < Q; ++q) {
-        const int qr = q / QC, qc = q % QC;
-        if (qr < nqr && qc < nqc && uni(S.listn[q]) > 0)
-            flush_query(S, f, r0, c0, q, uni(S.cnt[q]), true);
-    }
-    wave_sync();
+    // list, and those with a bound beyond the packed keys' range need the exact
+    // order: merge their candidates one query at a time (rare)
     {
-        // all other queries: one segmented sort of their candidate buffers.
-        // The network sorts 32-bit packed keys: the distance bits (clamped
-        // below +inf) with their 6 low bits replaced by the buffer slot.
-        // Packed order is exact wherever the distance parts differ; runs of
-        // equal distance parts are then put in (d, idx) order on the full
-        // keys by odd-even transposition (rarely needed).
-        const int cq = S.cnt[sq];
-        const bool own = sok && S.listn[sq] == 0;
-        uint32_t x[E];
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            // slot blocks permuted by segment (u ^ sq: E is a power of two and
-            // sq < E), so the segments' reads of one u spread over the banks
-            const int e = (u ^ sq) * P + lp;
-            const uint32_t dh = (uint32_t)(S.pend[sq][e] >> 32);
-            x[u] = (own && e < cq) ? ((min(dh, 0x7f7fffc0u) & ~63u) | (uint32_t)e) : 0x7f800000u;
-        }
-        seg_sort<KeyF32, P>(x, lp);
-        uint64_t y[E];
-#pragma unroll
-        for (int u = 0; u < E; ++u) y[u] = x[u] < 0x7f800000u ? S.pend[sq][x[u] & 63u] : KEY_INF;
-        // neighbours in sorted order: element lp*E + u, the next one is u + 1
-        // or the next lane's element 0 (same segment while lp < P - 1)
-        // two neighbours share the distance part iff their keys differ in the
-        // slot bits only: 1 <= (a ^ b) <= 63 (keys of candidates are distinct;
-        // two empty slots, both 0x7f800000, give 0; a candidate next to an
-        // empty slot differs above bit 22)
-        bool tie = false;
-#pragma unroll
-        for (int u = 0; u + 1 < E; ++u) tie |= (uint32_t)((x[u] ^ x[u + 1]) - 1u) < 63u;
-        {
-            const uint32_t nx = (uint32_t)__builtin_amdgcn_mov_dpp((int)x[0], 0x101, 0xF, 0xF, false);  // row_shl:1
-            tie |= lp < P - 1 && (uint32_t)((x[E - 1] ^ nx) - 1u) < 63u;
-        }
-        if (ballot(tie)) {
-            for (;;) {
-                bool sw = false;
-#pragma unroll
-                for (int ph = 0; ph < 2; ++ph) {
-#pragma unroll
-                    for (int u = ph; u + 1 < E; u += 2) {
-                        const uint64_t a = y[u], b = y[u + 1];
-                        const bool t = b < a;
-                        y[u] = t ? b : a;
-                        y[u + 1] = t ? a : b;
-                        sw |= t;
-                    }
-                    if ((ph == 1) == ((E & 1) == 0)) {
-                        // pair (lane's last, next lane's first)
-                        const uint64_t nx = (uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)y[0], 0x101, 0xF, 0xF, false) |
-                                            ((uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(y[0] >> 32), 0x101, 0xF, 0xF, false) << 32);
-                        const uint64_t pv = (uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)y[E - 1], 0x111, 0xF, 0xF, false) |
-                                            ((uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(y[E - 1] >> 32), 0x111, 0xF, 0xF, false) << 32);
-                        const bool tn = lp < P - 1 && nx < y[E - 1];  // this lane keeps the smaller
-                        const bool tp = lp > 0 && y[0] < pv;          // this lane keeps the larger
-                        y[E - 1] = tn ? nx : y[E - 1];
-                        y[0] = tp ? pv : y[0];
-                        sw |= tn;
-                    }
-                }
-                if (!ballot(sw)) break;
-            }
-        }
-        const size_t pix = (size_t)(r0 + sqr) * W + c0 + sqc;
-        if (own && lp * E < K) {
-            // the lane's E neighbours go to the list as 16-byte stores (entries
-            // from K on are never read); a slot without a candidate gathers
-            // the query's own row (see flush_query)
-#pragma unroll
-            for (int u = 0; u < E; u += 4) {
-                uint4 v;
-                v.x = y[u] == KEY_INF ? (uint32_t)pix : (uint32_t)y[u];
-                v.y = y[u + 1] == KEY_INF ? (uint32_t)pix : (uint32_t)y[u + 1];
-                v.z = y[u + 2] == KEY_INF ? (uint32_t)pix : (uint32_t)y[u + 2];
-                v.w = y[u + 3] == KEY_INF ? (uint32_t)pix : (uint32_t)y[u + 3];
-                *(uint4*)&S.list[sq][lp * E + u] = v;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            const int e = lp * E + u;
-            if (own && e < K) {
-                if (f.out_nbr) f.out_nbr[pix * K + e] = (int32_t)(uint32_t)y[u];
-                if (f.out_dist) f.out_dist[pix * K + e] = __uint_as_float((uint32_t)(y[u] >> 32));
-            }
+        const bool one = L < Q && L / QC < nqr && L % QC < nqc;
+        uint64_t need = ballot(one && (S.listn[L] > 0 || S.tauhi[L] > BIG));
+        while (need) {
+            const int q = (int)__builtin_ctzll(need);
+            need &= need - 1;
+            flush_query(S, f, r0, c0, q, uni(S.cnt[q]), true);
         }
     }
     wave_sync();
-
-    // ---- Eq. 2: sums in neighbour order, one lane per (query, class).  The
-    // neighbours' rows are L2-resident; up to 16 gathers are in flight.
-    const uint32_t rowb = (uint32_t)C * 4u;  // bytes per probability row
-    const uint64_t npix = (uint64_t)H * (uint64_t)W;
-    const bool off24 = npix <= (1u << 24) && npix * rowb <= 0xFFFFFFFFull;
-    // p / C by a reciprocal: (p + 0.5) / C sits at least 1/(2C) >= 1/32 from
-    // an integer and p < 2^10, far beyond the reciprocal's rounding
-    const float rc = __builtin_amdgcn_rcpf((float)C);
-    for (int p = L; p < Q * C; p += WAVE) {
-        const int q = (int)(uint32_t)(((float)p + 0.5f) * rc), cl = p - q * C;
-        const int qr = (int)((uint32_t)q / QC), qc = (int)((uint32_t)q % QC);
-        if (qr >= nqr || qc >= nqc) continue;
-        const uint32_t* lst = S.list[q];
-        float s = 0.0f;
-        int k = 0;
-        if (off24) {
-            const char* __restrict__ base = (const char*)f.prob;
-            const uint32_t cb = (uint32_t)cl * 4u;
-            for (; k + 16 <= K; k += 16) s = gather_add24<16>(s, base, lst + k, rowb, cb);
-            if (k + 8 <= K) {
-                s = gather_add24<8>(s, base, lst + k, rowb, cb);
-                k += 8;
-            }
-            for (; k < K; ++k) s = s + *(const float*)(base + (__umul24(lst[k], rowb) + cb));
-        } else {
-            const char* __restrict__ pb = (const char*)(f.prob + cl);
-            for (; k + 16 <= K; k += 16) s = gather_add<16>(s, pb, lst + k, rowb);
-            if (k + 8 <= K) {
-                s = gather_add<8>(s, pb, lst + k, rowb);
-                k += 8;
-            }
-            for (; k < K; ++k) s = s + *(const float*)(pb + (uint64_t)lst[k] * rowb);
-        }
-        S.sums[q][cl] = s;
-        if (off24) {
-            // the pixel's byte offset in the probability map fits 32 bits
-            const uint32_t pix = (uint32_t)(r0 * W + c0) + __umul24((uint32_t)qr, (uint32_t)W) + (uint32_t)qc;
-            *(float*)((char*)f.out_prob + (__umul24(pix, rowb) + (uint32_t)cl * 4u)) = s / (float)K;
-        } else {
-            const size_t pix = (size_t)(r0 + qr) * W + c0 + qc;
-            f.out_prob[pix * C + cl] = s / (float)K;
-        }
-    }
-    wave_sync();
-    if (L < Q) {
-        const int qr = L / QC, qc = L % QC;
-        if (qr < nqr && qc < nqc) {
-            int best = 0;
-            float bs = S.sums[L][0];
-            for (int cl = 1; cl < C; ++cl) {
-                const float v = S.sums[L][cl];
-                if (v > bs) { bs = v; best = cl; }
-            }
-            if (off24)
-                f.out_class[(uint32_t)(r0 * W + c0) + __umul24((uint32_t)qr, (uint32_t)W) + (uint32_t)qc] = best;
-            else
-                f.out_class[(size_t)(r0 + qr) * W + c0 + qc] = best;
-        }
-    }
+    if (most <= WAVE / 2 && K <= WAVE / 2) finish_tile<QR, QC, Q / 2>(S, f, r0, c0, nqr, nqc);
+    else finish_tile<QR, QC, Q>(S, f, r0, c0, nqr, nqc);
     if (f.stats && L == 0) {
         atomicAdd(&f.stats[0], pairs);
         atomicAdd(&f.stats[1], 1ull);
@@ -1280,7 +1344,7 @@ filter_batch_kernel(const FrameDesc* __restrict__ frames, const uint32_t* __rest
             const int band = (int)(s / ntc);
             const int tc = (int)(s - (uint32_t)band * ntc);
             // the claim loop's registers leave no room for 128-candidate blocks
-            process_tile<QR, QC, PRUNE, WAVE, 1>(lds[w], f, band * QR, tc * QC, lpr);
+            process_tile<QR, QC, PRUNE, WAVE>(lds[w], f, band * QR, tc * QC, lpr);
         }
     }
 }
