@@ -65,6 +65,13 @@ constexpr int MAXC = 16;
 // twice the registers (380 x 480, K = 24: 52.3 against 54.0 us with the larger
 // block; K = 30: 0.8 % of the queries would overflow, 0.1 % with the larger).
 constexpr int SMALL_K = 28;
+// A tile of such a K with a bound wider than eight pixels' spatial distance (its
+// K nearest reach far beyond the 8 x 8 block: outliers, about 1 % of the tiles)
+// takes the larger block after all: its own bound let whole regions through
+// (a 50 x 50 frame with a few such pixels 11.4 instead of 9.6 us; five pixels
+// instead of eight, 26 % of the tiles, cost 1024 frames of 50 x 50 708 instead of
+// 666 us).
+constexpr float WIDE2 = 64.0f;
 
 __device__ __forceinline__ int lane_id() {
     return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -648,9 +655,9 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                     }
                 }
             }
-            if (ovf) {
-                // rare: merge the full buffers into the sorted lists (which
-                // tightens the bounds), then append this step's survivors
+            if (__builtin_expect(ovf != 0, 0)) {
+                // rare: cut the full buffers down (which tightens the bounds) and
+                // append this step's survivors
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
                     if (L == 0) S.cnt[q] = cnt[q];
@@ -1102,12 +1109,18 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
 
     if (L < Q) S.listn[L] = 0;
 
-    const bool big = NA == 128 && K > SMALL_K;  // block size (see SMALL_K)
-    if (big) {
-        if constexpr (NA == 128) tile_bound<QR, QC, 128>(S, f, r0, c0, nqr, nqc);
-    } else {
+    // block size (see SMALL_K)
+    bool big = NA == 128 && (K > SMALL_K || lam == 0.0f);
+    if (!big) {
         tile_bound<QR, QC, 64>(S, f, r0, c0, nqr, nqc);
+        if constexpr (NA == 128) {
+            wave_sync();
+            const float lim = lam * lam * WIDE2;
+            big = ballot(S.tauhi[L % Q] > __float_as_uint(lim)) != 0;
+        }
     }
+    if constexpr (NA == 128)
+        if (big) tile_bound<QR, QC, 128>(S, f, r0, c0, nqr, nqc);
     wave_sync();
 
     // Work counter (only reported when f.stats is set): candidate distances
