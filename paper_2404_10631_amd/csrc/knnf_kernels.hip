@@ -56,7 +56,7 @@ namespace {
 constexpr uint64_t KEY_INF = ~0ull;
 constexpr int WAVE = 64;
 constexpr int A2ROWS = 64;  // window rows per block of the LDS a2 table
-constexpr int A2PAD = 4;    // padding rows (+inf) so a 4-row group may start anywhere
+constexpr int A2PAD = 4;    // padding rows (NaN) so a 4-row group may start anywhere
 constexpr int MAXC = 16;
 // Pass A looks at 64 candidates per query for K up to SMALL_K (8-query tiles),
 // 128 beyond.  The larger block's tighter bound lets fewer candidates through
@@ -396,7 +396,7 @@ struct alignas(16) TileState {
 // computes them per lane.
 template <int QR, int QC, bool PRUNE>
 struct alignas(16) TileLds : TileState<QR, QC> {
-    float a2t[A2ROWS + A2PAD][QR];  // fl32(a*a) for a block of window rows (+inf: inactive)
+    float a2t[A2ROWS + A2PAD][QR];  // fl32(a*a) for a block of window rows (NaN: inactive)
 };
 template <int QR, int QC>
 struct alignas(16) TileLds<QR, QC, true> : TileState<QR, QC> {};
@@ -535,7 +535,7 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
     const int H = f.H, W = f.W, R = f.R;
     const float lam = f.lambda;
     const float* __restrict__ pc1 = f.pc1;
-    const float pinf = __int_as_float(0x7f800000);
+    const float pinf = __int_as_float(0x7f800000), qnan = __int_as_float(0x7fc00000);
     const int rlo = max(0, r0 - R), rhi = min(H - 1, r0 + nqr - 1 + R);
 
     // ---- live rows
@@ -573,23 +573,18 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
     for (int blk = lo; blk <= hi; blk += PR) {
         const int bhi = min(blk + PR - 1, hi);
         const int i = blk + lr;
-        float a2[QR];   // this lane's row term per query row
-        bool rok[QR];   // this lane's row is live and in the query row's window
+        float a2[QR];   // this lane's row term per query row (NaN outside the block's rows
+                        // or the query row's window: no distance is within a bound)
         float a2n[QR];  // smallest row term of the block per query row (uniform)
 #pragma unroll
         for (int qr = 0; qr < QR; ++qr) {
             const int r = r0 + qr;
             const float a = feat(lam, r) - feat(lam, i);
-            a2[qr] = a * a;
-            rok[qr] = qr < nqr && i <= bhi && i >= r - R && i <= r + R;
+            a2[qr] = qr < nqr && i <= bhi && i >= r - R && i <= r + R ? a * a : qnan;
             const int wl = max(blk, r - R), wh = min(bhi, r + R);
             const float an = feat(lam, r) - feat(lam, min(max(r, wl), wh));
             a2n[qr] = (qr < nqr && wl <= wh) ? an * an : pinf;
         }
-        uint64_t rm[QR];  // lanes whose row is live and in the query row's window
-#pragma unroll
-        for (int qr = 0; qr < QR; ++qr) rm[qr] = ballot(rok[qr]);
-
         // live column steps on each side: a prefix, found 64 steps at a time
         int nside[2];
 #pragma unroll
@@ -615,7 +610,7 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
         }
         const int nright = nside[0], ns = ncen + nright + nside[1];
 
-        // rows past the frame or the window are loaded clamped and never pass
+        // rows past the frame or the window are loaded clamped
         const float* __restrict__ rowp = pc1 + (size_t)min(i, rhi) * W;
         auto step_col = [&](int st) {
             return st < ncen + nright ? c0 + SW * st : c0 - SW * (st - ncen - nright + 1);
@@ -623,19 +618,18 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
         float ipn = rowp[min(max(step_col(0) + lc, 0), W - 1)];
         for (int st = 0; st < ns; ++st) {
             const int jc = step_col(st);
-            const float ip = ipn;
-            if (st + 1 < ns) ipn = rowp[min(max(step_col(st + 1) + lc, 0), W - 1)];
             const int j = jc + lc;
             const bool jok = j >= 0 && j < W;
+            const float ip = jok ? ipn : qnan;
+            if (st + 1 < ns) ipn = rowp[min(max(step_col(st + 1) + lc, 0), W - 1)];
             const uint32_t idx = (uint32_t)i * (uint32_t)W + (uint32_t)j;
             float b[QC];
 #pragma unroll
             for (int qc = 0; qc < QC; ++qc) b[qc] = feat(lam, c0 + qc) - feat(lam, j);
-            const uint64_t jm = ballot(jok);
             if (f.stats) {
 #pragma unroll
                 for (int qr = 0; qr < QR; ++qr)
-                    pairs += (unsigned long long)__builtin_popcountll(jm & rm[qr]) * nqc;
+                    pairs += (unsigned long long)__builtin_popcountll(ballot(jok && a2[qr] == a2[qr])) * nqc;
             }
             uint32_t ovf = 0;  // queries whose buffer cannot take this step's survivors
 #pragma unroll
@@ -643,8 +637,8 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                 const int qr = q / QC, qc = q % QC;
                 const float e = iq[q] - ip;
                 const float d = fmaf(e, e, fmaf(b[qc], b[qc], a2[qr]));
-                const bool pass = jok && rok[qr] && __float_as_uint(d) <= th[q];
-                const uint64_t m = ballot(__float_as_uint(d) <= th[q]) & jm & rm[qr];
+                const bool pass = __float_as_uint(d) <= th[q];
+                const uint64_t m = ballot(pass);
                 if (m) {
                     const int n = __builtin_popcountll(m);
                     if (cnt[q] + n <= WAVE) {
@@ -868,7 +862,8 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
     const int m = (K + 1) / 2;
     const uint32_t v = xp[uni((m - 1) % NR)];  // uniform register index
     const uint32_t kk = max(v & 0xffffu, v >> 16);
-    if (lp == (m - 1) / NR) S.tauhi[sq] = sok ? kk << 16 : 0u;
+    // (not above +inf: the scans give candidates outside the window NaN distances)
+    if (lp == (m - 1) / NR) S.tauhi[sq] = sok ? min(kk << 16, 0x7f800000u) : 0u;
 }
 
 // Final selection and Eq. 2 of a tile; E: buffer slots per lane (all of them,
@@ -1105,7 +1100,7 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
     const float lam = f.lambda;
     const int nqr = min(QR, H - r0), nqc = min(QC, W - c0);
     const float* __restrict__ pc1 = f.pc1;
-    const float pinf = __int_as_float(0x7f800000);
+    const float pinf = __int_as_float(0x7f800000), qnan = __int_as_float(0x7fc00000);
 
     if (L < Q) S.listn[L] = 0;
 
@@ -1159,16 +1154,16 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
             const bool valid = j < W;
             const uint64_t vm = ballot(valid);
             const int jl = valid ? j : W - 1;
-            // lanes past the right edge get b = +inf, so every distance there is
-            // +inf (never below a finite bound; the append step checks `valid`)
+            // lanes past the right edge get b = NaN, so no distance there is
+            // within a bound
             float b[QC];
 #pragma unroll
-            for (int qc = 0; qc < QC; ++qc) b[qc] = valid ? feat(lam, c0 + qc) - feat(lam, j) : pinf;
+            for (int qc = 0; qc < QC; ++qc) b[qc] = valid ? feat(lam, c0 + qc) - feat(lam, j) : qnan;
 
             const int lo = rlo, hi = rhi;
 
             // Table blocks are aligned to rlo: block k holds rows rlo + 64k ...
-            // rlo + 64k + 63 (+inf past rhi and in the padding), so windows of up
+            // rlo + 64k + 63 (NaN past rhi and in the padding), so windows of up
             // to 64 rows fill it once per tile.
             for (int blk = rlo + ((lo - rlo) / A2ROWS) * A2ROWS; blk <= hi; blk += A2ROWS) {
                 if (blk != tab_base) {
@@ -1178,7 +1173,7 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                         const int r = r0 + qr, i = blk + rr;
                         const bool act = rr < A2ROWS && qr < nqr && i <= rhi && i >= r - R && i <= r + R;
                         const float a = feat(lam, r) - feat(lam, i);
-                        S.a2t[rr][qr] = act ? a * a : pinf;
+                        S.a2t[rr][qr] = act ? a * a : qnan;
                     }
                     wave_sync();
                     tab_base = blk;
@@ -1231,21 +1226,17 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                         if (ballot(mn <= th[q])) {
                             // rare: some candidate of the group is within the
                             // bound; append the group's survivors if they fit
-                            const int r = r0 + qr;
-                            bool rok[4];  // group rows inside the query row's window
                             uint64_t mu[4];
                             int n = 0;
 #pragma unroll
                             for (int u = 0; u < 4; ++u) {
-                                const int i = i0 + u;
-                                rok[u] = i <= hi && i >= r - R && i <= r + R;
-                                mu[u] = rok[u] ? ballot(__float_as_uint(d[u]) <= th[q]) & vm : 0ull;
+                                mu[u] = ballot(__float_as_uint(d[u]) <= th[q]);
                                 n += __builtin_popcountll(mu[u]);
                             }
                             if (cnt[q] + n <= WAVE) {
 #pragma unroll
                                 for (int u = 0; u < 4; ++u) {
-                                    if (valid && rok[u] && __float_as_uint(d[u]) <= th[q])
+                                    if (__float_as_uint(d[u]) <= th[q])
                                         S.pend[q][cnt[q] + mbcnt(mu[u])] = make_key(d[u], (i0 + u) * W + j);
                                     cnt[q] += __builtin_popcountll(mu[u]);
                                 }
