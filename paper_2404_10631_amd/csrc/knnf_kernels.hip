@@ -358,10 +358,10 @@ __device__ __forceinline__ void seg_sort(uint32_t (&x)[E], int lp) {
     lane_merge<T>(x);
 }
 
-// Two non-negative binary32 bit patterns (or +inf / NaN bits) as a pair of
-// 16-bit keys rounded up: key = ceil(d / 2^16), so d <= key << 16.
-__device__ __forceinline__ uint32_t pack_up(uint32_t lo, uint32_t hi) {
-    return ((lo + 0xffffu) >> 16) | ((hi + 0xffffu) & 0xffff0000u);
+// The upper halves of two binary32 bit patterns as a pair of 16-bit keys
+// (rounded down: d < (key + 1) << 16).
+__device__ __forceinline__ uint32_t pack_hi(uint32_t lo, uint32_t hi) {
+    return __builtin_amdgcn_perm(hi, lo, 0x07060302u);
 }
 
 // Buffer slots are prefilled with the query's own index and, as distance bits,
@@ -585,26 +585,31 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
             const float an = feat(lam, r) - feat(lam, min(max(r, wl), wh));
             a2n[qr] = (qr < nqr && wl <= wh) ? an * an : pinf;
         }
-        // live column steps on each side: a prefix, found 64 steps at a time
+        // live column steps on each side: a prefix, found P steps at a time, one
+        // (query, step) pair per lane
+        constexpr int P = WAVE / Q;
+        const int sq = L / P, lp = L % P;
+        const uint32_t thl = S.tauhi[sq];
+        const float fcl = feat(lam, c0 + sq % QC);
+        float a2l = a2n[0];
+#pragma unroll
+        for (int qr = 1; qr < QR; ++qr) a2l = sq / QC == qr ? a2n[qr] : a2l;
         int nside[2];
 #pragma unroll
         for (int side = 0; side < 2; ++side) {
             int n = 0;
             for (;;) {
-                const int st = n + L;
+                const int st = n + lp;
                 const int jc = side == 0 ? c0 + SW * (ncen + st) : c0 - SW * (st + 1);
                 const int jn = side == 0 ? jc : jc + SW - 1;  // the step's column nearest the tile
-                const float fj = feat(lam, jn);
-                uint64_t m = 0;
+                const float b = fcl - feat(lam, jn);
+                uint64_t m = ballot(__float_as_uint(fmaf(b, b, a2l)) <= thl &&
+                                    (side == 0 ? jc < W : jn >= 0));
 #pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    const float b = feat(lam, c0 + q % QC) - fj;
-                    m |= ballot(__float_as_uint(fmaf(b, b, a2n[q / QC])) <= th[q]);
-                }
-                m &= ballot(side == 0 ? jc < W : jn >= 0);
-                const int k = (~m) ? (int)__builtin_ctzll(~m) : WAVE;
+                for (int d = WAVE / 2; d >= P; d /= 2) m |= m >> d;  // any query's, in bits 0 .. P-1
+                const int k = (int)__builtin_ctzll(~m | (1ull << P));
                 n += k;
-                if (k < WAVE) break;
+                if (k < P) break;
             }
             nside[side] = n;
         }
@@ -741,7 +746,7 @@ __device__ __forceinline__ float gather_add24(float s, const char* __restrict__ 
 // spread; with m = ceil(K / 2), the larger of the groups' m-th smallest
 // distances is such a d.  All Q blocks are evaluated and sorted together:
 // segment q of the wavefront (P lanes) holds query q's block, the groups as the
-// low and high halves of NR registers of 16-bit keys rounded up.
+// low and high halves of NR registers of 16-bit keys rounded down.
 template <int QR, int QC, int NA>
 __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
                                            int nqr, int nqc) {
@@ -788,13 +793,22 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
                 pv[2 * u + 1] = *(const float*)(row + 4);
             }
             const float b0 = fcq - feat(lam, j), b1 = fcq - feat(lam, j + 1);
+            // one query row: the eight row terms are the same in every segment,
+            // lane u computes row u's
+            const float al = frq - feat(lam, rb + lp);
+            const float a2l = al * al;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const float a = frq - feat(lam, rb + u);
-                const float a2 = a * a;
+                float a2;
+                if constexpr (QR == 1) {
+                    a2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a2l), u));
+                } else {
+                    const float a = frq - feat(lam, rb + u);
+                    a2 = a * a;
+                }
                 const float e0 = iqs - pv[2 * u], e1 = iqs - pv[2 * u + 1];
                 // NaN bits for a query off the frame (segment unused)
-                xp[u] = pack_up(__float_as_uint(fmaf(e0, e0, fmaf(b0, b0, a2))),
+                xp[u] = pack_hi(__float_as_uint(fmaf(e0, e0, fmaf(b0, b0, a2))),
                                 __float_as_uint(fmaf(e1, e1, fmaf(b1, b1, a2))));
             }
         } else {
@@ -814,7 +828,7 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
                 for (int u = 0; u < 4; ++u) {
                     const float a0 = frq - feat(lam, rb + 2 * u), a1 = frq - feat(lam, rb + 2 * u + 1);
                     const float e0 = iqs - pv[8 * h + 2 * u], e1 = iqs - pv[8 * h + 2 * u + 1];
-                    xp[4 * h + u] = pack_up(__float_as_uint(fmaf(e0, e0, fmaf(b, b, a0 * a0))),
+                    xp[4 * h + u] = pack_hi(__float_as_uint(fmaf(e0, e0, fmaf(b, b, a0 * a0))),
                                             __float_as_uint(fmaf(e1, e1, fmaf(b, b, a1 * a1))));
                 }
             }
@@ -843,7 +857,7 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
             x[u] = (sok && j < W) ? d : 0x7f800000u;  // +inf: no candidate
         }
 #pragma unroll
-        for (int u = 0; u < NR; ++u) xp[u] = pack_up(x[u], x[u + NR]);
+        for (int u = 0; u < NR; ++u) xp[u] = pack_hi(x[u], x[u + NR]);
     }
     if (lp == 0) S.iq[sq] = iqs;
     // prefill the query's buffer slots (see PAD)
@@ -861,7 +875,7 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
     // least K candidates lie at or below the larger key
     const int m = (K + 1) / 2;
     const uint32_t v = xp[uni((m - 1) % NR)];  // uniform register index
-    const uint32_t kk = max(v & 0xffffu, v >> 16);
+    const uint32_t kk = max(v & 0xffffu, v >> 16) + 1u;
     // (not above +inf: the scans give candidates outside the window NaN distances)
     if (lp == (m - 1) / NR) S.tauhi[sq] = sok ? min(kk << 16, 0x7f800000u) : 0u;
 }
@@ -1300,24 +1314,27 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
     // ---- final selection, Eq. 2, outputs
     int most = 0;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        if (L == 0) S.cnt[q] = cnt[q];
-        most = max(most, uni(cnt[q]));
-    }
+    for (int q = 0; q < Q; ++q) most = max(most, uni(cnt[q]));
     wave_sync();
-    // queries whose buffer overflowed during the scan already hold a sorted
-    // list, and those with a bound beyond the packed keys' range need the exact
-    // order: merge their candidates one query at a time (rare)
+    // queries whose buffer overflowed and was merged hold a sorted list, and
+    // those with a bound beyond the packed keys' range need the exact order:
+    // merge their candidates one query at a time (rare)
     {
         const bool one = L < Q && L / QC < nqr && L % QC < nqc;
-        uint64_t need = ballot(one && (S.listn[L] > 0 || S.tauhi[L] > BIG));
-        while (need) {
-            const int q = (int)__builtin_ctzll(need);
-            need &= need - 1;
-            flush_query(S, f, r0, c0, q, uni(S.cnt[q]), true);
+        uint64_t need = ballot(one && (S.listn[L % Q] > 0 || S.tauhi[L % Q] > BIG));
+        if (__builtin_expect(need != 0, 0)) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (L == 0) S.cnt[q] = cnt[q];
+            wave_sync();
+            while (need) {
+                const int q = (int)__builtin_ctzll(need);
+                need &= need - 1;
+                flush_query(S, f, r0, c0, q, uni(S.cnt[q]), true);
+            }
+            wave_sync();
         }
     }
-    wave_sync();
     if (most <= WAVE / 2 && K <= WAVE / 2) finish_tile<QR, QC, Q / 2>(S, f, r0, c0, nqr, nqc);
     else finish_tile<QR, QC, Q>(S, f, r0, c0, nqr, nqc);
     if (f.stats && L == 0) {
