@@ -76,6 +76,14 @@ constexpr float WIDE2 = 64.0f;
 __device__ __forceinline__ int lane_id() {
     return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
+// The same, computed where it stands.  The rare merge paths use it: the compiler
+// moves what depends on the lane alone out of the scan's loops, and their 21 lane
+// masks alone cost every tile 110 vector instructions.
+__device__ __forceinline__ int lane_id_here() {
+    int L = lane_id();
+    asm volatile("" : "+v"(L));
+    return L;
+}
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ uint32_t uniu(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
@@ -107,7 +115,7 @@ __device__ __forceinline__ uint64_t make_key(float d, int idx) {
 // ---- cross-lane exchange with the partner lane L ^ J (no LDS traffic
 // except J = 4, which uses the LDS crossbar swizzle)
 template <int J>
-__device__ __forceinline__ uint32_t xlane(uint32_t v) {
+__device__ __forceinline__ uint32_t xlane(uint32_t v, int L) {
     if constexpr (J == 1) {
         return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false);
     } else if constexpr (J == 2) {
@@ -119,20 +127,19 @@ __device__ __forceinline__ uint32_t xlane(uint32_t v) {
     } else if constexpr (J == 16) {
         // permlane16_swap(v, v) yields rows {0,0,2,2} and {1,1,3,3}
         const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        return (lane_id() & 16) ? r[0] : r[1];
+        return (L & 16) ? r[0] : r[1];
     } else {
         // permlane32_swap(v, v) yields halves {lo,lo} and {hi,hi}
         const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        return (lane_id() & 32) ? r[0] : r[1];
+        return (L & 32) ? r[0] : r[1];
     }
 }
 
 // Compare-exchange of 64-bit keys (hi, lo) with partner L ^ J inside bitonic
 // stage S (S = 64: the final, all-ascending stage).
 template <int S, int J>
-__device__ __forceinline__ void cx_key(uint32_t& hi, uint32_t& lo) {
-    const int L = lane_id();
-    const uint32_t ph = xlane<J>(hi), pl = xlane<J>(lo);
+__device__ __forceinline__ void cx_key(uint32_t& hi, uint32_t& lo, int L) {
+    const uint32_t ph = xlane<J>(hi, L), pl = xlane<J>(lo, L);
     const uint64_t me = ((uint64_t)hi << 32) | lo, ot = ((uint64_t)ph << 32) | pl;
     const bool flip = ((L & J) != 0) != (S < WAVE && (L & S) != 0);
     const bool take = (ot < me) != flip;  // keys are unique apart from KEY_INF
@@ -141,30 +148,29 @@ __device__ __forceinline__ void cx_key(uint32_t& hi, uint32_t& lo) {
 }
 
 template <int S, int J>
-__device__ __forceinline__ void stage_key(uint32_t& hi, uint32_t& lo) {
-    cx_key<S, J>(hi, lo);
-    if constexpr (J > 1) stage_key<S, J / 2>(hi, lo);
+__device__ __forceinline__ void stage_key(uint32_t& hi, uint32_t& lo, int L) {
+    cx_key<S, J>(hi, lo, L);
+    if constexpr (J > 1) stage_key<S, J / 2>(hi, lo, L);
 }
 
 // Ascending bitonic sort of one 64-bit key per lane across the wavefront.
-__device__ __forceinline__ uint64_t sort64(uint64_t key) {
+__device__ __forceinline__ uint64_t sort64(uint64_t key, int L) {
     uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key;
-    stage_key<2, 1>(hi, lo);
-    stage_key<4, 2>(hi, lo);
-    stage_key<8, 4>(hi, lo);
-    stage_key<16, 8>(hi, lo);
-    stage_key<32, 16>(hi, lo);
-    stage_key<64, 32>(hi, lo);
+    stage_key<2, 1>(hi, lo, L);
+    stage_key<4, 2>(hi, lo, L);
+    stage_key<8, 4>(hi, lo, L);
+    stage_key<16, 8>(hi, lo, L);
+    stage_key<32, 16>(hi, lo, L);
+    stage_key<64, 32>(hi, lo, L);
     return ((uint64_t)hi << 32) | lo;
 }
 
 // a, b ascending across lanes; returns the 64 smallest of both, ascending.
-__device__ __forceinline__ uint64_t merge64(uint64_t a, uint64_t b) {
-    const int L = lane_id();
+__device__ __forceinline__ uint64_t merge64(uint64_t a, uint64_t b, int L) {
     const uint64_t rb = shfl64(b, WAVE - 1 - L);
     const uint64_t key = rb < a ? rb : a;  // bitonic: the 64 smallest of a and b
     uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key;
-    stage_key<64, 32>(hi, lo);
+    stage_key<64, 32>(hi, lo, L);
     return ((uint64_t)hi << 32) | lo;
 }
 
@@ -423,8 +429,10 @@ __device__ __forceinline__ float dist_to(const float* __restrict__ pc1, int W, f
 template <int QR, int QC>
 __device__ __forceinline__ uint64_t flush_query(TileState<QR, QC>& S, const FrameDesc& f, int r0,
                                              int c0, int q, int cnt, bool final) {
-    const int L = lane_id();
-    const int W = f.W, K = f.K;
+    const int L = lane_id_here();
+    const int K = f.K;
+    int W = f.W;  // (nor is the reciprocal for the division by W moved out)
+    asm volatile("" : "+s"(W));
     const float lam = f.lambda;
     const int r = r0 + q / QC, c = c0 + q % QC;
     wave_sync();
@@ -433,7 +441,7 @@ __device__ __forceinline__ uint64_t flush_query(TileState<QR, QC>& S, const Fram
     uint64_t key = KEY_INF;
     if (cnt > 0) {
         if (L < cnt) key = S.pend[q][L];
-        key = sort64(key);
+        key = sort64(key, L);
     }
     if (listn > 0) {
         uint64_t lk = KEY_INF;
@@ -441,7 +449,7 @@ __device__ __forceinline__ uint64_t flush_query(TileState<QR, QC>& S, const Fram
             const uint32_t idx = S.list[q][L];
             lk = make_key(dist_to(f.pc1, W, lam, r, c, iq, idx), (int)idx);
         }
-        key = (cnt > 0) ? merge64(lk, key) : lk;
+        key = (cnt > 0) ? merge64(lk, key, L) : lk;
     }
     if (L >= K) key = KEY_INF;
     const int nl = min(K, listn + cnt);
@@ -471,7 +479,7 @@ __device__ __forceinline__ uint64_t flush_query(TileState<QR, QC>& S, const Fram
 template <int QR, int QC>
 __device__ __forceinline__ bool tighten(TileState<QR, QC>& S, int q, int nb, uint32_t dn, uint32_t idx,
                                         uint32_t bound, int K, uint32_t own) {
-    const int L = lane_id();
+    const int L = lane_id_here();
     const uint64_t kb = S.pend[q][L];
     const uint32_t db = L < nb ? (uint32_t)(kb >> 32) : ~0u;
     auto count = [&](uint32_t t) {
@@ -603,8 +611,8 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                 const int jc = side == 0 ? c0 + SW * (ncen + st) : c0 - SW * (st + 1);
                 const int jn = side == 0 ? jc : jc + SW - 1;  // the step's column nearest the tile
                 const float b = fcl - feat(lam, jn);
-                uint64_t m = ballot(__float_as_uint(fmaf(b, b, a2l)) <= thl &&
-                                    (side == 0 ? jc < W : jn >= 0));
+                uint64_t m = ballot(__float_as_uint(fmaf(b, b, a2l)) <= thl) &
+                             ballot(side == 0 ? jc < W : jn >= 0);
 #pragma unroll
                 for (int d = WAVE / 2; d >= P; d /= 2) m |= m >> d;  // any query's, in bits 0 .. P-1
                 const int k = (int)__builtin_ctzll(~m | (1ull << P));
