@@ -383,7 +383,8 @@ template <int QR, int QC>
 struct alignas(16) TileState {
     static constexpr int Q = QR * QC;
     union {
-        uint64_t pend[Q][WAVE];  // keys of candidates that passed the bound, unsorted
+        uint32_t pend[Q][2][WAVE]; // candidates that passed the bound, unsorted: distance
+                                 // bits, linear indices
         float sums[Q][MAXC + 1]; // class sums for the argmax (after the final selection);
                                  // the odd row stride spreads the queries over the banks
         float4 rows[Q][ROWS + 1];// four classes: the neighbours' probability rows, in order
@@ -440,7 +441,7 @@ __device__ __forceinline__ uint64_t flush_query(TileState<QR, QC>& S, const Fram
     const int listn = uni(S.listn[q]);
     uint64_t key = KEY_INF;
     if (cnt > 0) {
-        if (L < cnt) key = S.pend[q][L];
+        if (L < cnt) key = make_key(__uint_as_float(S.pend[q][0][L]), (int)S.pend[q][1][L]);
         key = sort64(key, L);
     }
     if (listn > 0) {
@@ -480,8 +481,8 @@ template <int QR, int QC>
 __device__ __forceinline__ bool tighten(TileState<QR, QC>& S, int q, int nb, uint32_t dn, uint32_t idx,
                                         uint32_t bound, int K, uint32_t own) {
     const int L = lane_id_here();
-    const uint64_t kb = S.pend[q][L];
-    const uint32_t db = L < nb ? (uint32_t)(kb >> 32) : ~0u;
+    const uint32_t kb = S.pend[q][0][L], ib = S.pend[q][1][L];
+    const uint32_t db = L < nb ? kb : ~0u;
     auto count = [&](uint32_t t) {
         return __builtin_popcountll(ballot(db <= t)) + __builtin_popcountll(ballot(dn <= t));
     };
@@ -505,15 +506,55 @@ __device__ __forceinline__ bool tighten(TileState<QR, QC>& S, int q, int nb, uin
     const bool keepb = db <= hi, keepn = dn <= hi;
     const uint64_t mb = ballot(keepb), mn = ballot(keepn);
     wave_sync();
-    if (keepb) S.pend[q][mbcnt(mb)] = kb;
-    if (keepn) S.pend[q][__builtin_popcountll(mb) + mbcnt(mn)] = ((uint64_t)dn << 32) | idx;
-    if (L >= n) S.pend[q][L] = ((uint64_t)(PAD + 64u * (uint32_t)L) << 32) | own;
+    auto put = [&](int slot, uint32_t dist, uint32_t id) {
+        S.pend[q][0][slot] = dist;
+        S.pend[q][1][slot] = id;
+    };
+    if (keepb) put(mbcnt(mb), kb, ib);
+    if (keepn) put(__builtin_popcountll(mb) + mbcnt(mn), dn, idx);
+    if (L >= n) put(L, PAD + 64u * (uint32_t)L, own);
     if (L == 0) {
         S.cnt[q] = n;
         S.tauhi[q] = hi;
     }
     wave_sync();
     return true;
+}
+
+// Buffer counts as the pruned scan holds them: 4 * (n + 63), the byte offset of
+// the next slot plus a bias for which a count beyond 64 sets bit 9.
+constexpr int PEND_FULL = 512;
+__device__ __forceinline__ int pend_code(int n) { return 4 * (n + WAVE - 1); }
+__device__ __forceinline__ int pend_count(int code) { return code / 4 - (WAVE - 1); }
+
+// Append to the buffers of queries q .. q + 3 the lanes of masks m (distances d,
+// linear index idx); cnt: the queries' counts before, slot0: the buffers' LDS
+// address, less the counts' bias, in words.  Written out because the compiler
+// guards each store by a branch: 16 scalar instructions per query and step where
+// two are needed, with nearly every query storing in nearly every step.  The
+// caller's branch on the counts orders the compares before the masks' first
+// vector read; all 64 lanes are active.  LDS accesses of a wavefront stay in order.
+__device__ __forceinline__ void append4(int q, const uint64_t* m, const float* d, const int* cnt,
+                                        uint32_t idx, uint32_t slot0) {
+    uint32_t t;
+#define KNNF_APPEND(M, D, N, O)                                    \
+    "s_mov_b64 exec, %[" #M "]\n\t"                                \
+    "s_cbranch_execz .Lskip%=_" #O "\n\t"                          \
+    "v_mbcnt_lo_u32_b32 %[t], exec_lo, %[s]\n\t"                   \
+    "v_mbcnt_hi_u32_b32 %[t], exec_hi, %[t]\n\t"                   \
+    "v_lshl_add_u32 %[t], %[t], 2, %[" #N "]\n\t"                  \
+    "ds_write2st64_b32 %[t], %[" #D "], %[i] offset0:%[" #O "0] offset1:%[" #O "1]\n"  \
+    ".Lskip%=_" #O ":\n\t"
+    asm volatile(KNNF_APPEND(ma, da, na, a) KNNF_APPEND(mb, db, nb, b) KNNF_APPEND(mc, dc, nc, c)
+                     KNNF_APPEND(md, dd, nd, d) "s_mov_b64 exec, -1"
+                 : [t] "=&v"(t)
+                 : [ma] "s"(m[0]), [mb] "s"(m[1]), [mc] "s"(m[2]), [md] "s"(m[3]), [da] "v"(d[0]),
+                   [db] "v"(d[1]), [dc] "v"(d[2]), [dd] "v"(d[3]), [na] "s"(cnt[0]), [nb] "s"(cnt[1]),
+                   [nc] "s"(cnt[2]), [nd] "s"(cnt[3]), [i] "v"(idx), [s] "v"(slot0), [a0] "i"(2 * q),
+                   [a1] "i"(2 * q + 1), [b0] "i"(2 * q + 2), [b1] "i"(2 * q + 3), [c0] "i"(2 * q + 4),
+                   [c1] "i"(2 * q + 5), [d0] "i"(2 * q + 6), [d1] "i"(2 * q + 7)
+                 : "memory");
+#undef KNNF_APPEND
 }
 
 // Pruned scan (bit-identical to the exhaustive one).  Every term of Eq. 1 is
@@ -545,6 +586,12 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
     const float* __restrict__ pc1 = f.pc1;
     const float pinf = __int_as_float(0x7f800000), qnan = __int_as_float(0x7fc00000);
     const int rlo = max(0, r0 - R), rhi = min(H - 1, r0 + nqr - 1 + R);
+
+    // the counts are kept as buffer offsets (see append4)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cnt[q] = pend_code(cnt[q]);
+    const uint32_t slot0 = ((uint32_t)(uintptr_t)&S.pend[0][0][0] - (uint32_t)pend_code(0)) / 4;
+    const bool stats = f.stats != nullptr;
 
     // ---- live rows
     int lo = 0x7fffffff, hi = -1;
@@ -639,35 +686,45 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
             float b[QC];
 #pragma unroll
             for (int qc = 0; qc < QC; ++qc) b[qc] = feat(lam, c0 + qc) - feat(lam, j);
-            if (f.stats) {
+            if (stats) {
 #pragma unroll
                 for (int qr = 0; qr < QR; ++qr)
                     pairs += (unsigned long long)__builtin_popcountll(ballot(jok && a2[qr] == a2[qr])) * nqc;
             }
-            uint32_t ovf = 0;  // queries whose buffer cannot take this step's survivors
+            float d[Q];
+            uint64_t m[Q];
+            int cn[Q];
+            int full = 0;
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const int qr = q / QC, qc = q % QC;
                 const float e = iq[q] - ip;
-                const float d = fmaf(e, e, fmaf(b[qc], b[qc], a2[qr]));
-                const bool pass = __float_as_uint(d) <= th[q];
-                const uint64_t m = ballot(pass);
-                if (m) {
-                    const int n = __builtin_popcountll(m);
-                    if (cnt[q] + n <= WAVE) {
-                        if (pass) S.pend[q][cnt[q] + mbcnt(m)] = make_key(d, (int)idx);
-                        cnt[q] += n;
-                    } else {
+                d[q] = fmaf(e, e, fmaf(b[qc], b[qc], a2[qr]));
+                m[q] = ballot(__float_as_uint(d[q]) <= th[q]);
+                cn[q] = cnt[q] + 4 * __builtin_popcountll(m[q]);
+                full |= cn[q];
+            }
+            uint32_t ovf = 0;  // queries whose buffer cannot take this step's survivors
+            if (__builtin_expect((full & PEND_FULL) != 0, 0)) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    if (cn[q] & PEND_FULL) {
                         ovf |= 1u << q;
+                        m[q] = 0;
+                        cn[q] = cnt[q];
                     }
                 }
             }
+#pragma unroll
+            for (int q = 0; q < Q; q += 4) append4(q, m + q, d + q, cnt + q, idx, slot0);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) cnt[q] = cn[q];
             if (__builtin_expect(ovf != 0, 0)) {
                 // rare: cut the full buffers down (which tightens the bounds) and
                 // append this step's survivors
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
-                    if (L == 0) S.cnt[q] = cnt[q];
+                    if (L == 0) S.cnt[q] = pend_count(cnt[q]);
                 wave_sync();
                 while (ovf) {
                     const int q = __builtin_ctz(ovf);
@@ -689,7 +746,10 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                     if (kth != KEY_INF) thq = min(thq, (uint32_t)(kth >> 32));
                     const bool pass = jok && rq && __float_as_uint(d) <= thq;
                     const uint64_t m = ballot(pass);
-                    if (pass) S.pend[q][mbcnt(m)] = make_key(d, (int)idx);
+                    if (pass) {
+                        S.pend[q][0][mbcnt(m)] = __float_as_uint(d);
+                        S.pend[q][1][mbcnt(m)] = idx;
+                    }
                     wave_sync();
                     if (L == 0) {
                         S.cnt[q] = __builtin_popcountll(m);
@@ -699,12 +759,14 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                 }
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    cnt[q] = uni(S.cnt[q]);
+                    cnt[q] = pend_code(uni(S.cnt[q]));
                     th[q] = S.tauhi[q];
                 }
             }
         }
     }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cnt[q] = pend_count(cnt[q]);
 }
 
 // s + v[0] + v[1] + ... + v[N-1], left to right, where v[u] is the float at
@@ -871,11 +933,13 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
     // prefill the query's buffer slots (see PAD)
     {
         const uint32_t own = (uint32_t)r * (uint32_t)W + (uint32_t)c;
-        uint4* dst = (uint4*)S.pend[sq] + lp;
+        if constexpr (P >= 4) {
 #pragma unroll
-        for (int u = 0; u < WAVE / 2 / P; ++u) {
-            const uint32_t d = PAD + 128u * (uint32_t)(lp + u * P);
-            dst[u * P] = make_uint4(own, d, own, d + 64u);
+            for (int u = 0; u < WAVE / 4 / P; ++u) {
+                const uint32_t d = PAD + 256u * (uint32_t)(lp + u * P);
+                ((uint4*)S.pend[sq][0])[lp + u * P] = make_uint4(d, d + 64u, d + 128u, d + 192u);
+                ((uint4*)S.pend[sq][1])[lp + u * P] = make_uint4(own, own, own, own);
+            }
         }
     }
     seg_sort<PairU16, P>(xp, lp);
@@ -913,7 +977,7 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
         // slot blocks permuted by segment (u ^ sq: E is a power of two), so the
         // segments' reads of one u spread over the banks
         const int e = (u ^ (sq & (E - 1))) * P + lp;
-        const uint32_t dh = (uint32_t)(S.pend[sq][e] >> 32);
+        const uint32_t dh = S.pend[sq][0][e];
         x[u] = (dh & ~63u) | (uint32_t)e;
     }
     seg_sort<KeyF32, P>(x, lp);
@@ -932,7 +996,8 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
     if (ties || f.out_nbr || f.out_dist) {
         uint64_t y[E];
 #pragma unroll
-        for (int u = 0; u < E; ++u) y[u] = S.pend[sq][x[u] & 63u];
+        for (int u = 0; u < E; ++u)
+            y[u] = make_key(__uint_as_float(S.pend[sq][0][x[u] & 63u]), (int)S.pend[sq][1][x[u] & 63u]);
         if (ties) {
             for (;;) {
                 bool sw = false;
@@ -973,7 +1038,7 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
         }
     } else {
 #pragma unroll
-        for (int u = 0; u < E; ++u) id[u] = (uint32_t)S.pend[sq][x[u] & 63u];
+        for (int u = 0; u < E; ++u) id[u] = S.pend[sq][1][x[u] & 63u];
     }
 
     // ---- Eq. 2: sums in neighbour order, one lane per (query, class)
@@ -1258,8 +1323,11 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                             if (cnt[q] + n <= WAVE) {
 #pragma unroll
                                 for (int u = 0; u < 4; ++u) {
-                                    if (__float_as_uint(d[u]) <= th[q])
-                                        S.pend[q][cnt[q] + mbcnt(mu[u])] = make_key(d[u], (i0 + u) * W + j);
+                                    if (__float_as_uint(d[u]) <= th[q]) {
+                                        const int slot = cnt[q] + mbcnt(mu[u]);
+                                        S.pend[q][0][slot] = __float_as_uint(d[u]);
+                                        S.pend[q][1][slot] = (uint32_t)((i0 + u) * W + j);
+                                    }
                                     cnt[q] += __builtin_popcountll(mu[u]);
                                 }
                             } else {
@@ -1297,8 +1365,10 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                                     if (kth != KEY_INF) thq = min(thq, (uint32_t)(kth >> 32));
                                     msk = ballot(__float_as_uint(du) <= thq) & vm;
                                 }
-                                if (valid && __float_as_uint(du) <= thq)
-                                    S.pend[q][cq + mbcnt(msk)] = make_key(du, i * W + j);
+                                if (valid && __float_as_uint(du) <= thq) {
+                                    S.pend[q][0][cq + mbcnt(msk)] = __float_as_uint(du);
+                                    S.pend[q][1][cq + mbcnt(msk)] = (uint32_t)(i * W + j);
+                                }
                                 cq += __builtin_popcountll(msk);
                             }
                             wave_sync();
