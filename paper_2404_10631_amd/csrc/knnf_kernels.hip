@@ -25,14 +25,12 @@
 //     the window allows) are evaluated and sorted for all Q queries at once
 //     by a segmented bitonic network; any distance with at least K block
 //     candidates at or below it bounds the query's final K-th key from
-//     above.  8-query tiles sort the block as two interleaved groups of 64
-//     (16-bit keys rounded up, both groups in one packed network) and take
-//     the larger of the groups' ceil(K/2)-th keys; other tiles take the
-//     block's K-th distance.  The larger block's tighter bound lets fewer
-//     candidates through the scan than an 8 x 8 block's.
+//     above.  The block is sorted as two interleaved groups (16-bit keys, both
+//     in one packed network); the bound is the larger of the groups'
+//     ceil(K/2)-th keys.
 //   * pass B (collect): candidates with d <= d_K are appended to a per-query
-//     LDS buffer with ballot + mbcnt; a full buffer is merged into a sorted
-//     per-query list, which tightens the bound.  Two scans:
+//     LDS buffer with ballot + mbcnt; a full buffer is cut down by a tighter
+//     bound, or (equal distances) merged into a sorted per-query list.  Two scans:
 //       - pruned (default): 16-row x 4-column patches swept outward from the
 //         tile over the rows and column steps whose spatial lower bound is
 //         within some query's bound (bit-identical: every term of Eq. 1 is
@@ -62,9 +60,11 @@ constexpr int MAXC = 16;
 // 128 beyond.  The larger block's tighter bound lets fewer candidates through
 // (K = 40: 45 instead of 48 of the 64 buffer slots, and 1 % instead of 4 % of
 // the queries overflow them), but takes twice the distances and a network of
-// twice the registers (380 x 480, K = 24: 52.3 against 54.0 us with the larger
-// block; K = 30: 0.8 % of the queries would overflow, 0.1 % with the larger).
-constexpr int SMALL_K = 28;
+// twice the registers.  380 x 480, smaller against larger block: lambda 0.01,
+// K = 32 52.6 against 53.9 us, K = 40 60.3 / 60.1 (1000 x 1000: 241 / 249),
+// K = 48 77 / 70; lambda 1, K = 36 52.0 / 55.9, K = 44 53.3 / 57.3, K = 52
+// 92 / 59.
+constexpr int SMALL_K = 40;
 // A tile of such a K with a bound wider than eight pixels' spatial distance (its
 // K nearest reach far beyond the 8 x 8 block: outliers, about 1 % of the tiles)
 // takes the larger block after all: its own bound let whole regions through
@@ -174,32 +174,143 @@ __device__ __forceinline__ uint64_t merge64(uint64_t a, uint64_t b, int L) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// ---- segmented sorts: the Q queries of a tile sorted together.  A segment of
-// P lanes (4 or 8) holds one query's P * E elements, E registers a lane; the
+// ---- segmented networks: the Q queries of a tile together.  A segment of P
+// lanes (4 or 8) holds one query's P * E elements, E registers a lane; the
 // sorted order is element lp * E + r in register r of the segment's lane lp.
 //
-// Each lane sorts its E elements (Batcher's odd-even merge sort), then runs of
-// E, 2E, 4E elements are merged bitonically: stage KS compares e with its
-// mirror e ^ (KS - 1) (both runs ascending -> the smaller half in the lower
-// lanes, as two bitonic halves), then half-cleaners compare e with e ^ D across
-// lanes (D >= E) and within the lane.
+// Each lane sorts its E elements, then runs of E, 2E, 4E elements are merged
+// bitonically: stage KS compares e with its mirror e ^ (KS - 1) (both runs
+// ascending -> the smaller half in the lower lanes, as two bitonic halves), then
+// half-cleaners compare e with e ^ D across lanes (D >= E) and within the lane.
+// The tiles issue one vector instruction after another, so the count of
+// instructions is what a network costs.
 //
-// Lanes that keep the larger element of a cross-lane pair hold their values
-// negated (u16 pairs: complemented) and keep the smaller of their own and the
-// partner's negated value: one instruction per element for binary32 values
-// (v_min_f32 with a negated DPP operand) and two for u16 pairs (v_not_b32 with
-// DPP, v_pk_min_u16), where a select by lane took two and four.  Which lanes
-// those are changes from stage to stage (lane bit KS / 2E of a mirror stage,
-// D / E of a half-cleaner); the XOR in between issues at twice the rate of a
-// minimum (2.4 against 4.5 cycles per wavefront on this chip).  Within a lane a
-// bitonic sequence may lie in either direction, so odd lanes are left negated,
-// hence sorted the other way round, while lanes merge their own elements; a
-// mirror stage, whose partner lane differs in bit 0, then pairs equal registers,
-// and a half-cleaner with lane ^ 1 opposite ones.
+// 32-bit keys (final selection).  The median of an element, its partner and 0 or
+// all ones is the smaller or the larger of the two, so a cross-lane comparison
+// is a DPP move and a v_med3_u32 with a constant of the lane.  Within a lane,
+// with lo / md / hi the sorted three of four elements, the fourth is inserted by
+// min(lo, d), med3(lo, md, d), med3(md, hi, d), max(hi, d): 7 instructions for a
+// sort of 4 where 5 compare-exchanges take 10.  Two sorted pairs merge in 5 (6):
+// a cyclic bitonic sequence a, b, c, d in 6 (8), because min(b, d) never exceeds
+// max(a, c) in it nor max(b, d) falls below min(a, c).  8 queries x 64 elements:
+// 186 instructions (214 with compare-exchanges, negating the values of the lanes
+// that keep the larger element).
 //
-// 8 queries x 64 elements, VALU cycles of a wavefront by the measured rates of
-// its instructions: u16 pairs 1,050 (1,394 with selects by lane and bitonic
-// sorts within the lane), binary32 840 (967).
+// Pairs of 16-bit keys (pass A: two groups of candidates a query, one in each
+// half).  There is no packed median; lanes that keep the larger element hold
+// their keys complemented and keep the smaller of their own and the partner's
+// complement (v_not_b32 with DPP, v_pk_min_u16, and v_xor_b32 where the set of
+// such lanes changes).  Within a lane a bitonic sequence may lie in either
+// direction, so odd lanes stay complemented, hence sorted the other way round,
+// while lanes merge their own elements; a mirror stage, whose partner lane
+// differs in bit 0, then pairs equal registers, and a half-cleaner with lane ^ 1
+// opposite ones.
+
+__device__ __forceinline__ uint32_t med3u(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ void cx(uint32_t& a, uint32_t& b) {
+    const uint32_t lo = min(a, b);
+    b = max(a, b);
+    a = lo;
+}
+
+// Ascending order of four elements.
+__device__ __forceinline__ void sort4(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t& d) {
+    const uint32_t lo = min(min(a, b), c), md = med3u(a, b, c), hi = max(max(a, b), c);
+    a = min(lo, d);
+    b = med3u(lo, md, d);
+    c = med3u(md, hi, d);
+    d = max(hi, d);
+}
+// Ascending order of two sorted pairs (a, b), (c, d).
+__device__ __forceinline__ void merge22(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t& d) {
+    const uint32_t lo = min(a, c), t = max(a, c), hi = max(b, d);
+    const uint32_t m1 = min(min(t, b), d), m2 = med3u(t, b, d);
+    a = lo;
+    b = m1;
+    c = m2;
+    d = hi;
+}
+// Ascending order of a cyclic bitonic sequence of four.
+__device__ __forceinline__ void bitonic4(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t& d) {
+    const uint32_t lo = min(b, d), hi = max(b, d);
+    const uint32_t y0 = min(min(a, c), lo), y1 = med3u(a, c, lo);
+    const uint32_t y2 = med3u(a, c, hi), y3 = max(max(a, c), hi);
+    a = y0;
+    b = y1;
+    c = y2;
+    d = y3;
+}
+
+// Ascending order of x[0], x[S], x[2 S], ... (N elements, both halves sorted).
+template <int N, int S>
+__device__ __forceinline__ void merge_halves(uint32_t* x) {
+    if constexpr (N == 4) {
+        merge22(x[0], x[S], x[2 * S], x[3 * S]);
+    } else {
+        merge_halves<N / 2, 2 * S>(x);  // Batcher: even and odd elements, then neighbours
+        merge_halves<N / 2, 2 * S>(x + S);
+#pragma unroll
+        for (int i = 1; i + 1 < N; i += 2) cx(x[i * S], x[(i + 1) * S]);
+    }
+}
+// Ascending sort of the lane's E elements.
+template <int E>
+__device__ __forceinline__ void lane_sort(uint32_t* x) {
+    if constexpr (E == 4) {
+        sort4(x[0], x[1], x[2], x[3]);
+    } else {
+        lane_sort<E / 2>(x);
+        lane_sort<E / 2>(x + E / 2);
+        merge_halves<E, 1>(x);
+    }
+}
+// Ascending order of the lane's bitonic sequence.
+template <int E>
+__device__ __forceinline__ void lane_merge(uint32_t* x) {
+    if constexpr (E == 4) {
+        bitonic4(x[0], x[1], x[2], x[3]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < E / 2; ++r) cx(x[r], x[r + E / 2]);
+        lane_merge<E / 2>(x);
+        lane_merge<E / 2>(x + E / 2);
+    }
+}
+// Keep the smaller (keep = 0) or larger (all ones) of each element and its
+// partner in the lane that CTRL selects, the registers mirrored or not.
+template <int CTRL, bool MIRROR, int E>
+__device__ __forceinline__ void cross(uint32_t (&x)[E], uint32_t keep) {
+    uint32_t t[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r)
+        t[r] = (uint32_t)__builtin_amdgcn_mov_dpp((int)x[MIRROR ? E - 1 - r : r], CTRL, 0xF, 0xF, false);
+#pragma unroll
+    for (int r = 0; r < E; ++r) x[r] = med3u(x[r], t[r], keep);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_XOR7 = 0x141;
+
+// Ascending sort of each segment of P lanes.
+template <int P, int E>
+__device__ __forceinline__ void seg_sort(uint32_t (&x)[E], int lp) {
+    static_assert(P == 4 || P == 8, "segment width");
+    const uint32_t k0 = (lp & 1) ? ~0u : 0u, k1 = (lp & 2) ? ~0u : 0u;
+    lane_sort<E>(x);
+    cross<DPP_XOR1, true>(x, k0);  // runs of 2E
+    lane_merge<E>(x);
+    cross<DPP_XOR3, true>(x, k1);  // runs of 4E
+    cross<DPP_XOR1, false>(x, k0);
+    if constexpr (P == 8) {
+        lane_merge<E>(x);
+        cross<DPP_XOR7, true>(x, (lp & 4) ? ~0u : 0u);  // runs of 8E
+        cross<DPP_XOR2, false>(x, k1);
+        cross<DPP_XOR1, false>(x, k0);
+    }
+    lane_merge<E>(x);
+}
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
@@ -210,18 +321,12 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
                                                                   __builtin_bit_cast(u16x2, b)));
 }
+__device__ __forceinline__ void pk_cx(uint32_t& a, uint32_t& b) {
+    const uint32_t lo = pk_min(a, b);
+    b = pk_max(a, b);
+    a = lo;
+}
 
-// Register kinds of the network.  FLIP: the XOR that negates; cx: compare-
-// exchange within a lane; cross_same<X>: each register keeps the smaller of its
-// own value and the negated one of lane L ^ X (X = 1, 2, 3: quad_perm; 7:
-// row_half_mirror); cross_opposite1: of lane L ^ 1, registers paired r, E-1-r.
-struct PairU16 {  // two u16 keys, each half a segment of its own
-    static constexpr uint32_t FLIP = ~0u;
-    static __device__ __forceinline__ void cx(uint32_t& a, uint32_t& b) {
-        const uint32_t lo = pk_min(a, b), hi = pk_max(a, b);
-        a = lo;
-        b = hi;
-    }
 // n0 .. n3 = ~y0 .. ~y3 of the lanes CTRL selects (a DPP operand must not have
 // been written in the two instructions before: s_nop 1)
 #define KNNF_NOT4(CTRL)                                                          \
@@ -232,84 +337,45 @@ struct PairU16 {  // two u16 keys, each half a segment of its own
         "v_not_b32_dpp %3, %7 " CTRL " row_mask:0xf bank_mask:0xf"               \
         : "=&v"(n[r]), "=&v"(n[r + 1]), "=&v"(n[r + 2]), "=&v"(n[r + 3])         \
         : "v"(x[r]), "v"(x[r + 1]), "v"(x[r + 2]), "v"(x[r + 3]))
-    template <int X, int E>
-    static __device__ __forceinline__ void partner(const uint32_t (&x)[E], uint32_t (&n)[E]) {
+// Each register keeps the smaller of its own keys and the complemented ones of
+// lane L ^ X (X = 1, 2, 3: quad_perm; 7: row_half_mirror), in the same register
+// or (OPP) registers paired r, E-1-r.
+template <int X, bool OPP, int E>
+__device__ __forceinline__ void pk_cross(uint32_t (&x)[E]) {
+    uint32_t n[E];
 #pragma unroll
-        for (int r = 0; r < E; r += 4) {
-            if constexpr (X == 1) KNNF_NOT4("quad_perm:[1,0,3,2]");
-            else if constexpr (X == 2) KNNF_NOT4("quad_perm:[2,3,0,1]");
-            else if constexpr (X == 3) KNNF_NOT4("quad_perm:[3,2,1,0]");
-            else KNNF_NOT4("row_half_mirror");
-        }
+    for (int r = 0; r < E; r += 4) {
+        if constexpr (X == 1) KNNF_NOT4("quad_perm:[1,0,3,2]");
+        else if constexpr (X == 2) KNNF_NOT4("quad_perm:[2,3,0,1]");
+        else if constexpr (X == 3) KNNF_NOT4("quad_perm:[3,2,1,0]");
+        else KNNF_NOT4("row_half_mirror");
     }
+#pragma unroll
+    for (int r = 0; r < E; ++r) x[r] = pk_min(x[r], n[OPP ? E - 1 - r : r]);
+}
 #undef KNNF_NOT4
-    template <int X, int E>
-    static __device__ __forceinline__ void cross_same(uint32_t (&x)[E]) {
-        uint32_t n[E];
-        partner<X>(x, n);
+template <int E>
+__device__ __forceinline__ void pk_lane_merge(uint32_t (&x)[E]) {
 #pragma unroll
-        for (int r = 0; r < E; ++r) x[r] = pk_min(x[r], n[r]);
-    }
-    template <int E>
-    static __device__ __forceinline__ void cross_opposite1(uint32_t (&x)[E]) {
-        uint32_t n[E];
-        partner<1>(x, n);
+    for (int d = E / 2; d >= 1; d /= 2)
 #pragma unroll
-        for (int r = 0; r < E; ++r) x[r] = pk_min(x[r], n[E - 1 - r]);
-    }
-};
-struct KeyF32 {  // bit patterns of binary32 values (no -0 beside +0, no NaN that matters)
-    static constexpr uint32_t FLIP = 0x80000000u;
-    static __device__ __forceinline__ void cx(uint32_t& a, uint32_t& b) {
-        // (fminf and fmaxf would add canonicalising instructions)
-        uint32_t lo, hi;
-        asm("v_min_f32 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
-        asm("v_max_f32 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
-        a = lo;
-        b = hi;
-    }
-// (a DPP operand must not have been written in the two instructions before: s_nop 1)
-#define KNNF_DPP_ROW " row_mask:0xf bank_mask:0xf\n\t"
-#define KNNF_KEEP4(CTRL)                                                             \
-    asm("s_nop 1\n\t"                                                                \
-        "v_min_f32_dpp %0, -%0, %0 " CTRL KNNF_DPP_ROW                               \
-        "v_min_f32_dpp %1, -%1, %1 " CTRL KNNF_DPP_ROW                               \
-        "v_min_f32_dpp %2, -%2, %2 " CTRL KNNF_DPP_ROW                               \
-        "v_min_f32_dpp %3, -%3, %3 " CTRL KNNF_DPP_ROW                               \
-        : "+v"(x[r]), "+v"(x[r + 1]), "+v"(x[r + 2]), "+v"(x[r + 3]))
-    template <int X, int E>
-    static __device__ __forceinline__ void cross_same(uint32_t (&x)[E]) {
+        for (int r = 0; r < E; ++r)
+            if (!(r & d)) pk_cx(x[r], x[r | d]);
+}
+template <int E>
+__device__ __forceinline__ void pk_flip(uint32_t (&x)[E], uint32_t mask) {
 #pragma unroll
-        for (int r = 0; r < E; r += 4) {
-            if constexpr (X == 1) KNNF_KEEP4("quad_perm:[1,0,3,2]");
-            else if constexpr (X == 2) KNNF_KEEP4("quad_perm:[2,3,0,1]");
-            else if constexpr (X == 3) KNNF_KEEP4("quad_perm:[3,2,1,0]");
-            else KNNF_KEEP4("row_half_mirror");
-        }
-    }
-    template <int E>
-    static __device__ __forceinline__ void cross_opposite1(uint32_t (&x)[E]) {
-#pragma unroll
-        for (int r = 0; r < E / 2; r += 2) {
-            uint32_t a, b;
-            asm("s_nop 1\n\t"
-                "v_min_f32_dpp %0, -%2, %4 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
-                "v_min_f32_dpp %1, -%3, %5 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
-                "v_min_f32_dpp %2, -%4, %2 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
-                "v_min_f32_dpp %3, -%5, %3 quad_perm:[1,0,3,2]" KNNF_DPP_ROW
-                : "=&v"(a), "=&v"(b), "+v"(x[E - 1 - r]), "+v"(x[E - 2 - r])
-                : "v"(x[r]), "v"(x[r + 1]));
-            x[r] = a;
-            x[r + 1] = b;
-        }
-    }
-#undef KNNF_KEEP4
-#undef KNNF_DPP_ROW
-};
-
-// Ascending sort of the lane's E elements.
-template <class T, int E>
-__device__ __forceinline__ void lane_sort(uint32_t (&x)[E]) {
+    for (int r = 0; r < E; ++r) x[r] ^= mask;
+}
+// The segment's sorted element lp * E + rank in each lane (rank uniform): the last
+// merge within the lane follows the one path to it, E - 1 minima of keys that are
+// complemented on the levels where the larger half is wanted.
+template <int P, int E>
+__device__ __forceinline__ uint32_t pk_seg_rank(uint32_t (&x)[E], int lp, int rank) {
+    static_assert(P == 4 || P == 8, "segment width");
+    const uint32_t m0 = (lp & 1) ? ~0u : 0u, m1 = (lp & 2) ? ~0u : 0u;
+    pk_flip(x, m0);
+    // Batcher's odd-even merge sort of the lane's elements
 #pragma unroll
     for (int p = 1; p < E; p *= 2)
 #pragma unroll
@@ -319,49 +385,34 @@ __device__ __forceinline__ void lane_sort(uint32_t (&x)[E]) {
 #pragma unroll
                 for (int i = 0; i < k; ++i)
                     if (i + j + k < E && (i + j) / (2 * p) == (i + j + k) / (2 * p))
-                        T::cx(x[i + j], x[i + j + k]);
-}
-
-// Ascending order of the lane's bitonic sequence.
-template <class T, int E>
-__device__ __forceinline__ void lane_merge(uint32_t (&x)[E]) {
-#pragma unroll
-    for (int d = E / 2; d >= 1; d /= 2)
-#pragma unroll
-        for (int r = 0; r < E; ++r)
-            if (!(r & d)) T::cx(x[r], x[r | d]);
-}
-
-template <class T, int E>
-__device__ __forceinline__ void flip_lanes(uint32_t (&x)[E], uint32_t mask) {
-#pragma unroll
-    for (int r = 0; r < E; ++r) x[r] ^= mask;
-}
-// Ascending sort of each segment of P lanes.
-template <class T, int P, int E>
-__device__ __forceinline__ void seg_sort(uint32_t (&x)[E], int lp) {
-    static_assert(P == 4 || P == 8, "segment width");
-    const uint32_t m0 = (lp & 1) ? T::FLIP : 0u, m1 = (lp & 2) ? T::FLIP : 0u;
-    flip_lanes<T>(x, m0);
-    lane_sort<T>(x);
-    T::template cross_same<1>(x);  // runs of 2E
-    lane_merge<T>(x);
-    flip_lanes<T>(x, m0 ^ m1);
-    T::template cross_same<3>(x);  // runs of 4E
-    flip_lanes<T>(x, m0 ^ m1);
-    T::cross_opposite1(x);
+                        pk_cx(x[i + j], x[i + j + k]);
+    pk_cross<1, false>(x);  // runs of 2E
+    pk_lane_merge(x);
+    pk_flip(x, m0 ^ m1);
+    pk_cross<3, false>(x);  // runs of 4E
+    pk_flip(x, m0 ^ m1);
+    pk_cross<1, true>(x);
     if constexpr (P == 8) {
-        const uint32_t m2 = (lp & 4) ? T::FLIP : 0u;
-        lane_merge<T>(x);
-        flip_lanes<T>(x, m0 ^ m2);
-        T::template cross_same<7>(x);  // runs of 8E
-        flip_lanes<T>(x, m2 ^ m1);
-        T::template cross_same<2>(x);
-        flip_lanes<T>(x, m1 ^ m0);
-        T::cross_opposite1(x);
+        const uint32_t m2 = (lp & 4) ? ~0u : 0u;
+        pk_lane_merge(x);
+        pk_flip(x, m0 ^ m2);
+        pk_cross<7, false>(x);  // runs of 8E
+        pk_flip(x, m2 ^ m1);
+        pk_cross<2, false>(x);
+        pk_flip(x, m1 ^ m0);
+        pk_cross<1, true>(x);
     }
-    flip_lanes<T>(x, m0);
-    lane_merge<T>(x);
+    uint32_t was = m0;
+#pragma unroll
+    for (int d = E / 2; d >= 1; d /= 2) {
+        const uint32_t up = (rank & d) ? ~0u : 0u;
+#pragma unroll
+        for (int r = 0; r < 2 * d; ++r) x[r] ^= was ^ up;
+#pragma unroll
+        for (int r = 0; r < d; ++r) x[r] = pk_min(x[r], x[r + d]);
+        was = up;
+    }
+    return x[0] ^ was;
 }
 
 // The upper halves of two binary32 bit patterns as a pair of 16-bit keys
@@ -942,11 +993,10 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
             }
         }
     }
-    seg_sort<PairU16, P>(xp, lp);
     // each group's element m - 1 (lane (m-1) / NR, register (m-1) % NR); at
     // least K candidates lie at or below the larger key
     const int m = (K + 1) / 2;
-    const uint32_t v = xp[uni((m - 1) % NR)];  // uniform register index
+    const uint32_t v = pk_seg_rank<P>(xp, lp, uni((m - 1) % NR));
     const uint32_t kk = max(v & 0xffffu, v >> 16) + 1u;
     // (not above +inf: the scans give candidates outside the window NaN distances)
     if (lp == (m - 1) / NR) S.tauhi[sq] = sok ? min(kk << 16, 0x7f800000u) : 0u;
@@ -980,7 +1030,7 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
         const uint32_t dh = S.pend[sq][0][e];
         x[u] = (dh & ~63u) | (uint32_t)e;
     }
-    seg_sort<KeyF32, P>(x, lp);
+    seg_sort<P>(x, lp);
     // two neighbours in sorted order share the distance part iff their keys
     // differ in the slot bits only: (a ^ b) <= 63 (keys are distinct)
     bool tie = false;
