@@ -132,10 +132,12 @@ typedef enum { KNNF_SEARCH_EXHAUSTIVE = 0, KNNF_SEARCH_PRUNED = 1 } knnf_search;
  *   tile_cols     supported tiles (rows x cols): 1x8, 1x16, 2x4, 2x8, 4x4
  *   waves         wavefronts per workgroup; 1, 2 or 4
  *   launch        knnf_launch (batched launches only)
- *   chunk_rows    window chunk of the pruned search: the candidates a
- *                 wavefront evaluates per step form a patch of chunk_rows rows
- *                 x (64 / chunk_rows) columns; 8, 16 or 32 (the exhaustive
- *                 search always sweeps 4 rows x 64 columns)
+ *   chunk_rows    window chunk of the pruned search: the window rows that can
+ *                 hold a neighbour are split into equal blocks of at most
+ *                 2 * chunk_rows rows, and a wavefront evaluates per step the
+ *                 block's rows x as many columns as make up to 64 candidates;
+ *                 8, 16 or 32 (the exhaustive search always sweeps 4 rows x 64
+ *                 columns)
  *   flags         KNNF_PLAN_* bits
  * A zero tile, wave, launch or chunk field means "the context's default"
  * (initially a pruned search with 1 x 8 tiles, one wavefront per workgroup,
