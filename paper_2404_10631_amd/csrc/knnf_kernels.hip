@@ -30,7 +30,7 @@
 //     ceil(K/2)-th keys.
 //   * pass B (collect): candidates with d <= d_K are appended to a per-query
 //     LDS buffer with ballot + mbcnt; a full buffer is cut down by a tighter
-//     bound, or (equal distances) merged into a sorted per-query list.  Two scans:
+//     bound.  Two scans:
 //       - pruned (default): patches of 64 candidates, as high as the block of
 //         rows, swept over the rows and columns whose spatial lower bound is
 //         within some query's bound (bit-identical: every term of Eq. 1 is
@@ -88,9 +88,6 @@ __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlan
 __device__ __forceinline__ uint32_t uniu(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
-__device__ __forceinline__ uint64_t uni64(uint64_t v) {
-    return ((uint64_t)uniu((uint32_t)(v >> 32)) << 32) | (uint64_t)uniu((uint32_t)v);
-}
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ int mbcnt(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -101,12 +98,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-__device__ __forceinline__ uint32_t shfl(uint32_t v, int src) {
-    return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);
-}
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
-    return ((uint64_t)shfl((uint32_t)(v >> 32), src) << 32) | (uint64_t)shfl((uint32_t)v, src);
 }
 __device__ __forceinline__ uint64_t make_key(float d, int idx) {
     return ((uint64_t)__float_as_uint(d) << 32) | (uint64_t)(uint32_t)idx;
@@ -161,15 +152,6 @@ __device__ __forceinline__ uint64_t sort64(uint64_t key, int L) {
     stage_key<8, 4>(hi, lo, L);
     stage_key<16, 8>(hi, lo, L);
     stage_key<32, 16>(hi, lo, L);
-    stage_key<64, 32>(hi, lo, L);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// a, b ascending across lanes; returns the 64 smallest of both, ascending.
-__device__ __forceinline__ uint64_t merge64(uint64_t a, uint64_t b, int L) {
-    const uint64_t rb = shfl64(b, WAVE - 1 - L);
-    const uint64_t key = rb < a ? rb : a;  // bitonic: the 64 smallest of a and b
-    uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key;
     stage_key<64, 32>(hi, lo, L);
     return ((uint64_t)hi << 32) | lo;
 }
@@ -436,17 +418,18 @@ struct alignas(16) TileState {
     union {
         uint32_t pend[Q][2][WAVE]; // candidates that passed the bound, unsorted: distance
                                  // bits, linear indices
-        float sums[Q][MAXC + 1]; // class sums for the argmax (after the final selection);
-                                 // the odd row stride spreads the queries over the banks
         float4 rows[Q][ROWS + 1];// four classes: the neighbours' probability rows, in order
+        struct {                 // other class counts:
+            // neighbours' linear indices in order; rows padded by 16 bytes so that
+            // the queries' rows start on different banks (Eq. 2 reads the same
+            // entry of every query at once)
+            uint32_t list[Q][WAVE + 4];
+            float sums[Q][MAXC + 1]; // class sums for the argmax; the odd row stride
+                                 // spreads the queries over the banks
+        };
     };
-    // sorted top-K linear indices (first listn valid); rows padded by 16
-    // bytes so that the queries' rows start on different banks (Eq. 2 reads
-    // the same entry of every query at once, the final selection stores them)
-    uint32_t list[Q][WAVE + 4];
     uint32_t tauhi[Q];        // distance bits of the current bound on the K-th key
     float iq[Q];              // I of each query pixel (NaN for pixels off the frame)
-    int listn[Q];             // valid list entries (<= K)
     int cnt[Q];               // pending entries (mirror of the scan's registers)
 };
 
@@ -462,63 +445,30 @@ struct alignas(16) TileLds<QR, QC, true> : TileState<QR, QC> {};
 // Coordinate feature fr(x) = fl32(lambda * (float)x).
 __device__ __forceinline__ float feat(float lam, int x) { return lam * (float)x; }
 
-// Eq. 1 between query (r, c, iq) and the candidate with linear index idx,
-// evaluated exactly as in the scan loop.
-__device__ __forceinline__ float dist_to(const float* __restrict__ pc1, int W, float lam, int r,
-                                         int c, float iq, uint32_t idx) {
-    const int i = (int)(idx / (uint32_t)W);
-    const int j = (int)idx - i * W;
-    const float a = feat(lam, r) - feat(lam, i);
-    const float a2 = a * a;
-    const float b = feat(lam, c) - feat(lam, j);
-    const float e = iq - pc1[idx];
-    return fmaf(e, e, fmaf(b, b, a2));
-}
-
-// Merge query q's pending candidates into its sorted top-K list.  Returns the
-// new K-th key (KEY_INF while fewer than K candidates are known).  With
-// `final`, also writes the neighbour outputs of the query pixel.
+// Put query q's cnt candidates in exact (d, idx) order and write its neighbour
+// outputs, for bounds beyond the packed keys' range.  The buffer then holds the
+// indices in order under distance parts that only number them.
 template <int QR, int QC>
-__device__ __forceinline__ uint64_t flush_query(TileState<QR, QC>& S, const FrameDesc& f, int r0,
-                                             int c0, int q, int cnt, bool final) {
+__device__ __forceinline__ void order_query(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
+                                            int q, int cnt) {
     const int L = lane_id_here();
-    const int K = f.K;
-    int W = f.W;  // (nor is the reciprocal for the division by W moved out)
-    asm volatile("" : "+s"(W));
-    const float lam = f.lambda;
+    const int W = f.W, K = f.K;
     const int r = r0 + q / QC, c = c0 + q % QC;
-    wave_sync();
-    const float iq = S.iq[q];
-    const int listn = uni(S.listn[q]);
     uint64_t key = KEY_INF;
-    if (cnt > 0) {
-        if (L < cnt) key = make_key(__uint_as_float(S.pend[q][0][L]), (int)S.pend[q][1][L]);
-        key = sort64(key, L);
-    }
-    if (listn > 0) {
-        uint64_t lk = KEY_INF;
-        if (L < listn) {
-            const uint32_t idx = S.list[q][L];
-            lk = make_key(dist_to(f.pc1, W, lam, r, c, iq, idx), (int)idx);
-        }
-        key = (cnt > 0) ? merge64(lk, key, L) : lk;
-    }
-    if (L >= K) key = KEY_INF;
-    const int nl = min(K, listn + cnt);
+    if (L < cnt) key = make_key(__uint_as_float(S.pend[q][0][L]), (int)S.pend[q][1][L]);
+    key = sort64(key, L);
     wave_sync();
     // a slot without a candidate (only with non-finite inputs, or inputs that
     // change during the launch) gathers the query pixel's own row, never an
     // address outside the frame
-    if (L < K) S.list[q][L] = (final && key == KEY_INF) ? (uint32_t)(r * W + c) : (uint32_t)key;
-    if (final && L < K) {
+    S.pend[q][0][L] = (uint32_t)L << 6;
+    S.pend[q][1][L] = key == KEY_INF ? (uint32_t)r * (uint32_t)W + (uint32_t)c : (uint32_t)key;
+    if (L < K) {
         const size_t pix = (size_t)r * W + c;
         if (f.out_nbr) f.out_nbr[pix * K + L] = (int32_t)(uint32_t)key;
         if (f.out_dist) f.out_dist[pix * K + L] = __uint_as_float((uint32_t)(key >> 32));
     }
-    const uint64_t kth = uni64(shfl64(key, K - 1));
-    if (L == 0) S.listn[q] = nl;
     wave_sync();
-    return nl == K ? kth : KEY_INF;
 }
 
 // Make room in query q's full buffer: nb pending candidates and this step's (dn:
@@ -526,10 +476,11 @@ __device__ __forceinline__ uint64_t flush_query(TileState<QR, QC>& S, const Fram
 // `over` lie within the bound.  Any distance t with at least K candidates at or
 // below it bounds the K-th key, so a t that leaves at most 64 of them is found
 // by bisection (its counts are ballots), the buffer keeps those, and the bound
-// becomes t.  False if ties leave no such t (the caller merges exactly).  About
-// 100 instructions where the exact merge takes 350, and no merge at the end.
+// becomes t.  Where equal distances leave no such t, the smallest t with K
+// candidates is taken, and of those at t the ones up to an index that is found
+// the same way: ties go by the index.  About 100 instructions, 200 with ties.
 template <int QR, int QC>
-__device__ __forceinline__ bool tighten(TileState<QR, QC>& S, int q, int nb, uint32_t dn, uint32_t idx,
+__device__ __forceinline__ void tighten(TileState<QR, QC>& S, int q, int nb, uint32_t dn, uint32_t idx,
                                         uint32_t bound, int K, uint32_t own) {
     const int L = lane_id_here();
     const uint32_t kb = S.pend[q][0][L], ib = S.pend[q][1][L];
@@ -553,8 +504,35 @@ __device__ __forceinline__ bool tighten(TileState<QR, QC>& S, int q, int nb, uin
             if (c <= few) break;
         }
     }
-    if (n > WAVE) return false;
-    const bool keepb = db <= hi, keepn = dn <= hi;
+    bool keepb = db <= hi, keepn = dn <= hi;
+    if (n > WAVE) {
+        if (hi == 1 && count(0) >= K) {  // (the bisection never looks at 0)
+            hi = 0;
+            keepb = db == 0;
+            keepn = dn == 0;
+        }
+        const uint64_t lb = ballot(db < hi), ln = ballot(dn < hi);  // fewer than K
+        const uint64_t eb = ballot(db == hi), en = ballot(dn == hi);
+        n = __builtin_popcountll(lb | eb) + __builtin_popcountll(ln | en);
+        if (n > WAVE) {
+            int il = -1, ih = 0x7fffffff;  // fewer than K up to il, at least K up to ih
+            for (;;) {
+                const int mid = il + (int)((uint32_t)(ih - il) / 2);
+                const uint64_t mb = lb | (eb & ballot((int)ib <= mid));
+                const uint64_t mn = ln | (en & ballot((int)idx <= mid));
+                const int c = __builtin_popcountll(mb) + __builtin_popcountll(mn);
+                if (c < K) {
+                    il = mid;
+                } else {
+                    ih = mid;
+                    n = c;
+                    if (c <= few) break;  // reached: one index at a time adds one candidate
+                }
+            }
+            keepb = db < hi || (db == hi && (int)ib <= ih);
+            keepn = dn < hi || (dn == hi && (int)idx <= ih);
+        }
+    }
     const uint64_t mb = ballot(keepb), mn = ballot(keepn);
     wave_sync();
     auto put = [&](int slot, uint32_t dist, uint32_t id) {
@@ -569,7 +547,6 @@ __device__ __forceinline__ bool tighten(TileState<QR, QC>& S, int q, int nb, uin
         S.tauhi[q] = hi;
     }
     wave_sync();
-    return true;
 }
 
 // Buffer counts as the pruned scan holds them: 4 * (n + 63), the byte offset of
@@ -627,7 +604,7 @@ __device__ __forceinline__ void append4(int q, const uint64_t* m, const float* d
 // 8: 59.0; 1000 x 1000 231, 233, 236, 248).
 // Survivors (d <= tau's distance) are appended per query with ballot +
 // mbcnt; a full buffer is cut down to the candidates within a tighter bound
-// (tighten), or merged into the query's sorted list where ties prevent that.
+// (tighten).
 template <int QR, int QC>
 __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDesc& f, int r0,
                                             int c0, int nqr, int nqc, int lpr,
@@ -792,25 +769,9 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                     const float d = fmaf(e, e, fmaf(bq, bq, a * a));
                     const bool rq = lc < SW && i <= bhi && i >= r - R && i <= r + R;
                     const int nb = uni(S.cnt[q]);
-                    uint32_t thq = uniu(S.tauhi[q]);
+                    const uint32_t thq = uniu(S.tauhi[q]);
                     const uint32_t own = (uint32_t)r * (uint32_t)W + (uint32_t)(c0 + qc);
-                    if (uni(S.listn[q]) == 0 &&
-                        tighten(S, q, nb, jok && rq ? __float_as_uint(d) : ~0u, idx, thq, f.K, own))
-                        continue;
-                    const uint64_t kth = flush_query(S, f, r0, c0, q, nb, false);
-                    if (kth != KEY_INF) thq = min(thq, (uint32_t)(kth >> 32));
-                    const bool pass = jok && rq && __float_as_uint(d) <= thq;
-                    const uint64_t m = ballot(pass);
-                    if (pass) {
-                        S.pend[q][0][mbcnt(m)] = __float_as_uint(d);
-                        S.pend[q][1][mbcnt(m)] = idx;
-                    }
-                    wave_sync();
-                    if (L == 0) {
-                        S.cnt[q] = __builtin_popcountll(m);
-                        S.tauhi[q] = thq;
-                    }
-                    wave_sync();
+                    tighten(S, q, nb, jok && rq ? __float_as_uint(d) : ~0u, idx, thq, f.K, own);
                 }
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
@@ -1017,7 +978,7 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
     const int sq = L / P, lp = L % P;
     const int sqr = sq / QC, sqc = sq % QC;
     const bool sok = sqr < nqr && sqc < nqc;
-    const bool merged = S.listn[sq] != 0;  // selected by flush_query: the list holds its neighbours
+    const bool merged = S.tauhi[sq] > BIG;  // ordered by order_query, neighbours written
     const uint32_t pix = (uint32_t)(r0 + sqr) * (uint32_t)W + (uint32_t)(c0 + sqc);
 
     // One segmented sort of the candidate buffers.  The network sorts 32-bit
@@ -1105,13 +1066,6 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
         // to the lanes that sum them.  One load of a row serves four classes:
         // 8 loads and 8 shifts per lane where a gather per class took 40 of
         // each, in three trips to L2 instead of one.
-        if (ballot(merged)) {
-#pragma unroll
-            for (int u = 0; u < E; ++u) {
-                const int e = lp * E + u;
-                if (merged) id[u] = e < K && sok ? S.list[sq][e] : 0u;
-            }
-        }
         typedef float f4 __attribute__((ext_vector_type(4)));
         f4 row[E];
         if (sok && lp * E < K) {
@@ -1168,7 +1122,8 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
     }
     // other class counts: the lists go through LDS, 16 bytes at a time (entries
     // from K on are never read)
-    if (sok && !merged && lp * E < K) {
+    wave_sync();  // the buffers have been read
+    if (sok && lp * E < K) {
 #pragma unroll
         for (int u = 0; u < E; u += 4)
             *(uint4*)&S.list[sq][lp * E + u] = make_uint4(id[u], id[u + 1], id[u + 2], id[u + 3]);
@@ -1242,8 +1197,6 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
     const int nqr = min(QR, H - r0), nqc = min(QC, W - c0);
     const float* __restrict__ pc1 = f.pc1;
     const float pinf = __int_as_float(0x7f800000), qnan = __int_as_float(0x7fc00000);
-
-    if (L < Q) S.listn[L] = 0;
 
     // block size (see SMALL_K)
     bool big = NA == 128 && (K > SMALL_K || lam == 0.0f);
@@ -1390,8 +1343,8 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                         }
                     }
                     if (ovf) {
-                        // rare: merge full buffers into the sorted lists (which
-                        // tightens the bounds), appending the group row by row
+                        // rare: cut the full buffers down (which tightens the
+                        // bounds), appending the group row by row
 #pragma unroll
                         for (int q = 0; q < Q; ++q)
                             if (L == 0) S.cnt[q] = cnt[q];
@@ -1414,10 +1367,12 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
                                 uint64_t msk = ballot(__float_as_uint(du) <= thq) & vm;
                                 if (!msk) continue;
                                 if (cq + __builtin_popcountll(msk) > WAVE) {
-                                    const uint64_t kth = flush_query(S, f, r0, c0, q, cq, false);
-                                    cq = 0;
-                                    if (kth != KEY_INF) thq = min(thq, (uint32_t)(kth >> 32));
-                                    msk = ballot(__float_as_uint(du) <= thq) & vm;
+                                    const uint32_t own = (uint32_t)r * (uint32_t)W + (uint32_t)(c0 + qc);
+                                    tighten(S, q, cq, valid ? __float_as_uint(du) : ~0u,
+                                            (uint32_t)(i * W + j), thq, f.K, own);
+                                    cq = uni(S.cnt[q]);
+                                    thq = uniu(S.tauhi[q]);
+                                    continue;
                                 }
                                 if (valid && __float_as_uint(du) <= thq) {
                                     S.pend[q][0][cq + mbcnt(msk)] = __float_as_uint(du);
@@ -1448,12 +1403,10 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
 #pragma unroll
     for (int q = 0; q < Q; ++q) most = max(most, uni(cnt[q]));
     wave_sync();
-    // queries whose buffer overflowed and was merged hold a sorted list, and
-    // those with a bound beyond the packed keys' range need the exact order:
-    // merge their candidates one query at a time (rare)
+    // queries with a bound beyond the packed keys' range need the exact order (rare)
     {
         const bool one = L < Q && L / QC < nqr && L % QC < nqc;
-        uint64_t need = ballot(one && (S.listn[L % Q] > 0 || S.tauhi[L % Q] > BIG));
+        uint64_t need = ballot(one && S.tauhi[L % Q] > BIG);
         if (__builtin_expect(need != 0, 0)) {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
@@ -1462,9 +1415,8 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
             while (need) {
                 const int q = (int)__builtin_ctzll(need);
                 need &= need - 1;
-                flush_query(S, f, r0, c0, q, uni(S.cnt[q]), true);
+                order_query(S, f, r0, c0, q, uni(S.cnt[q]));
             }
-            wave_sync();
         }
     }
     if (most <= WAVE / 2 && K <= WAVE / 2) finish_tile<QR, QC, Q / 2>(S, f, r0, c0, nqr, nqc);
@@ -1486,10 +1438,11 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     return (b & 7) * per + (b >> 3);
 }
 
-// 8-query tiles are held to 80 VGPRs (six wavefronts per SIMD, the LDS
-// limit too): without the hint some instantiations took 81-90 registers and
-// ran at five, which cost the batched 1x8 launch 11 %.
-#define KNNF_WAVES_PER_EU(QR, QC) __attribute__((amdgpu_waves_per_eu((QR) * (QC) == 8 ? 6 : 1)))
+// 8-query tiles are held to 72 VGPRs, seven wavefronts per SIMD: 380 x 480 K=40
+// 52.3 us, 1000 x 1000 210, 1024 frames of 50 x 50 449; six wavefronts 53.6, 218
+// and 472; eight (64 registers, some spilled) 54.4, 212 and 447.  Their 4,320
+// bytes of LDS would allow nine.
+#define KNNF_WAVES_PER_EU(QR, QC) __attribute__((amdgpu_waves_per_eu((QR) * (QC) == 8 ? 7 : 1)))
 
 template <int QR, int QC, int WPB, bool PRUNE>
 __global__ void __launch_bounds__(WPB * WAVE) KNNF_WAVES_PER_EU(QR, QC)
@@ -1514,7 +1467,7 @@ filter_frame_kernel(FrameDesc f, int lpr) {
 // whole device sweeps neighbouring tiles (which share window rows) at the same
 // time.  Every wavefront leaves the loop after one failed claim, so the grid
 // always drains.  The claim loop's state would otherwise push the 8-query
-// tiles to 110 VGPRs (four wavefronts per SIMD); held at 80 they spill a few
+// tiles to 110 VGPRs (four wavefronts per SIMD); held at 72 they spill a few
 // dwords to scratch, reloaded once per tile.
 template <int QR, int QC, int WPB, bool PRUNE>
 __global__ void __launch_bounds__(WPB * WAVE) KNNF_WAVES_PER_EU(QR, QC)
