@@ -76,9 +76,11 @@ constexpr float WIDE2 = 64.0f;
 __device__ __forceinline__ int lane_id() {
     return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
-// The same, computed where it stands.  The rare merge paths use it: the compiler
-// moves what depends on the lane alone out of the scan's loops, and their 21 lane
-// masks alone cost every tile 110 vector instructions.
+// The same, computed where it stands: the compiler moves what depends on the lane
+// alone out of loops.  The rare paths use it (the 21 lane masks of a 64-key sort
+// cost every tile 110 vector instructions in front of the scan), and the
+// persistent kernel's tiles, whose lane constants its claim loop kept in registers
+// (108 bytes of them spilled).
 __device__ __forceinline__ int lane_id_here() {
     int L = lane_id();
     asm volatile("" : "+v"(L));
@@ -607,12 +609,11 @@ __device__ __forceinline__ void append4(int q, const uint64_t* m, const float* d
 // (tighten).
 template <int QR, int QC>
 __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDesc& f, int r0,
-                                            int c0, int nqr, int nqc, int lpr,
+                                            int c0, int nqr, int nqc, int lpr, int L,
                                             const float (&iq)[QR * QC],
                                             uint32_t (&th)[QR * QC], int (&cnt)[QR * QC],
                                             unsigned long long& pairs) {
     constexpr int Q = QR * QC;
-    const int L = lane_id();
     const int H = f.H, W = f.W, R = f.R;
     const float lam = f.lambda;
     const float* __restrict__ pc1 = f.pc1;
@@ -835,11 +836,10 @@ __device__ __forceinline__ float gather_add24(float s, const char* __restrict__ 
 // low and high halves of NR registers of 16-bit keys rounded down.
 template <int QR, int QC, int NA>
 __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
-                                           int nqr, int nqc) {
+                                           int nqr, int nqc, int L) {
     constexpr int Q = QR * QC, P = WAVE / Q, EA = NA / P, NR = EA / 2;
     constexpr int LNA = NA == 128 ? 7 : 6;
     static_assert((NA == 128 && Q == 8) || NA == 64, "pass-A block size");
-    const int L = lane_id();
     const int H = f.H, W = f.W, R = f.R, K = f.K;
     const float lam = f.lambda;
     const float* __restrict__ pc1 = f.pc1;
@@ -971,9 +971,8 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
 // or the first half where no buffer holds more).
 template <int QR, int QC, int E>
 __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
-                                            int nqr, int nqc) {
+                                            int nqr, int nqc, int L) {
     constexpr int Q = QR * QC, P = WAVE / Q;
-    const int L = lane_id();
     const int H = f.H, W = f.W, K = f.K, C = f.C;
     const int sq = L / P, lp = L % P;
     const int sqr = sq / QC, sqc = sq % QC;
@@ -1189,9 +1188,8 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
 // NA: largest pass-A block (128 candidates per query; 64 for 16-query tiles).
 template <int QR, int QC, bool PRUNE, int NA = (QR * QC == 8 ? 128 : WAVE)>
 __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const FrameDesc& f, int r0,
-                                             int c0, int lpr) {
+                                             int c0, int lpr, int L) {
     constexpr int Q = QR * QC;
-    const int L = lane_id();
     const int H = f.H, W = f.W, R = f.R, K = f.K;
     const float lam = f.lambda;
     const int nqr = min(QR, H - r0), nqc = min(QC, W - c0);
@@ -1201,7 +1199,7 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
     // block size (see SMALL_K)
     bool big = NA == 128 && (K > SMALL_K || lam == 0.0f);
     if (!big) {
-        tile_bound<QR, QC, 64>(S, f, r0, c0, nqr, nqc);
+        tile_bound<QR, QC, 64>(S, f, r0, c0, nqr, nqc, L);
         if constexpr (NA == 128) {
             wave_sync();
             const float lim = lam * lam * WIDE2;
@@ -1209,7 +1207,7 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
         }
     }
     if constexpr (NA == 128)
-        if (big) tile_bound<QR, QC, 128>(S, f, r0, c0, nqr, nqc);
+        if (big) tile_bound<QR, QC, 128>(S, f, r0, c0, nqr, nqc, L);
     wave_sync();
 
     // Work counter (only reported when f.stats is set): candidate distances
@@ -1231,7 +1229,7 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
 
     // ---- pass B
     if constexpr (PRUNE) {
-        scan_pruned<QR, QC>(S, f, r0, c0, nqr, nqc, lpr, iq, th, cnt, pairs);
+        scan_pruned<QR, QC>(S, f, r0, c0, nqr, nqc, lpr, L, iq, th, cnt, pairs);
     } else {
         // exhaustive: window rows x 64-column chunks, nearest chunk first
         const int rlo = max(0, r0 - R);
@@ -1419,8 +1417,8 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
             }
         }
     }
-    if (most <= WAVE / 2 && K <= WAVE / 2) finish_tile<QR, QC, Q / 2>(S, f, r0, c0, nqr, nqc);
-    else finish_tile<QR, QC, Q>(S, f, r0, c0, nqr, nqc);
+    if (most <= WAVE / 2 && K <= WAVE / 2) finish_tile<QR, QC, Q / 2>(S, f, r0, c0, nqr, nqc, L);
+    else finish_tile<QR, QC, Q>(S, f, r0, c0, nqr, nqc, L);
     if (f.stats && L == 0) {
         atomicAdd(&f.stats[0], pairs);
         atomicAdd(&f.stats[1], 1ull);
@@ -1457,7 +1455,7 @@ filter_frame_kernel(FrameDesc f, int lpr) {
     if (s >= ntiles) return;
     const uint32_t band = s / ntc;
     const uint32_t tc = s - band * ntc;
-    process_tile<QR, QC, PRUNE>(lds[w], f, (int)band * QR, (int)tc * QC, lpr);
+    process_tile<QR, QC, PRUNE>(lds[w], f, (int)band * QR, (int)tc * QC, lpr, lane_id());
 }
 
 // Persistent batched kernel: each wavefront claims tile tasks from one global
@@ -1466,9 +1464,7 @@ filter_frame_kernel(FrameDesc f, int lpr) {
 // task_start[k] .. task_start[k+1]-1.  Claims go out in task order, so the
 // whole device sweeps neighbouring tiles (which share window rows) at the same
 // time.  Every wavefront leaves the loop after one failed claim, so the grid
-// always drains.  The claim loop's state would otherwise push the 8-query
-// tiles to 110 VGPRs (four wavefronts per SIMD); held at 72 they spill a few
-// dwords to scratch, reloaded once per tile.
+// always drains.
 template <int QR, int QC, int WPB, bool PRUNE>
 __global__ void __launch_bounds__(WPB * WAVE) KNNF_WAVES_PER_EU(QR, QC)
 filter_batch_kernel(const FrameDesc* __restrict__ frames, const uint32_t* __restrict__ task_start,
@@ -1502,7 +1498,7 @@ filter_batch_kernel(const FrameDesc* __restrict__ frames, const uint32_t* __rest
             const int band = (int)(s / ntc);
             const int tc = (int)(s - (uint32_t)band * ntc);
             // the claim loop's registers leave no room for 128-candidate blocks
-            process_tile<QR, QC, PRUNE, WAVE>(lds[w], f, band * QR, tc * QC, lpr);
+            process_tile<QR, QC, PRUNE, WAVE>(lds[w], f, band * QR, tc * QC, lpr, lane_id_here());
         }
     }
 }
@@ -1530,7 +1526,7 @@ filter_items_kernel(const FrameDesc* __restrict__ frames, const uint32_t* __rest
     const uint32_t ntc = (uint32_t)((f.W + QC - 1) / QC);
     const int band = (int)(s / ntc);
     const int tc = (int)(s - (uint32_t)band * ntc);
-    process_tile<QR, QC, PRUNE>(lds[w], f, band * QR, tc * QC, lpr);
+    process_tile<QR, QC, PRUNE>(lds[w], f, band * QR, tc * QC, lpr, lane_id());
 }
 
 template <int QR, int QC, int WPB, bool PRUNE>
