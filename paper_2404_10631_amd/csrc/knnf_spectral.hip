@@ -18,8 +18,11 @@
 //      barrier, so the merge needs no second buffer); keys sit in LDS at
 //      XOR-swizzled positions, which spreads a wavefront's stores of 16
 //      consecutive keys per lane over the banks;
-//   2. each lane takes one query pixel of the two rows: a binary search finds
-//      where I_q falls in the sorted band; two cursors walk outward (values
+//   2. a binary search per query pixel of the two rows (one a lane) finds where
+//      I_q falls in the sorted band.  The nearest 64 candidates of a query are then
+//      merged from the 64 keys on either side by eight lanes (select_queries);
+//   3. queries that this leaves (equal distances across the end of those 64, K
+//      close to 64) walk the band, one a lane: two cursors go outward (values
 //      below and above I_q), skipping the band row that lies outside the
 //      query's own window, taking at each step the whole run of candidates
 //      whose distance equals the smaller of the two cursors' distances (a
@@ -33,17 +36,20 @@
 //      the subtraction can give distinct values the same distance) is
 //      emitted by repeated minimum.  That is the strict (d, idx) order of the
 //      general kernels, so the neighbour lists are the same;
-//   3. Eq. 2: the class sums add the neighbours' probabilities in that order
+//   4. Eq. 2: the class sums add the neighbours' probabilities in that order
 //      from +0 (binary32), then one correctly rounded division by K; the
 //      class map is the argmax of the sums, lowest class on ties.  The
 //      probabilities are gathered eight neighbours at a time, so the loads of
 //      a group are in flight together (one at a time, each waited for its
 //      predecessor's latency).
+// W480 x H380, K = 40: the sort takes 58 us, search, selection and Eq. 2 53 and the
+// few walks 7 (124.5 us a call; 173 with a walk for every query).
 // Work: O(n log n) per query row for the sort (n = band size) and
 // O(log n + K) per query, against O(n) distances per query for the scans.
 // Two query rows per workgroup halve the sorting per row and put the
 // W480 x H380 frame's 190 workgroups on the chip in one round (one row per
-// workgroup: 380 workgroups, two rounds, 0.255 against 0.183 ms).  Used for a
+// workgroup: 380 workgroups, two rounds, 0.255 against 0.183 ms when measured with
+// a walk for every query).  Used for a
 // single frame under the pruned search when lambda == 0 and the band holds at
 // most 16,384 pixels (it must fit in LDS).
 #include <hip/hip_runtime.h>
@@ -53,6 +59,7 @@
 
 #include "../../include/knnf.h"
 #include "knnf_device.h"
+#include "knnf_networks.h"
 
 namespace knnf {
 namespace {
@@ -156,9 +163,232 @@ __device__ __forceinline__ void sort_band(uint64_t* keys, int T, uint64_t (&v)[S
     }
 }
 
+constexpr int SP_SIDE = 64;                    // candidates looked at on each side of a query
+constexpr int SP_GROUP = 16;                   // queries per Eq. 2 pass of a wavefront
+
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// Orders LDS traffic of one wavefront (lanes exchange data through LDS).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ uint32_t lane_get(uint32_t v, int src) {
+    return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);
+}
+
+// The wavefront's 64 queries (query qi = q0 + lane, value x, first key not below it
+// a0), eight at a time: returns true in the lanes whose query was finished.
+//
+// A segment of eight lanes holds one query: the SP_SIDE keys below and above a0,
+// each side ascending in distance, merge into the nearest SP_SIDE of both by one
+// bitonic merge of packed keys (distance bits with the low seven replaced by the
+// side and offset; runs of equal distance parts are then put in (d, idx) order on
+// the full keys).  The band row outside a query's own window takes part and is
+// dropped by rank afterwards, so a query is finished if K of the 64 remain and
+// the K-th lies strictly before the last one kept (dropped candidates are not
+// nearer); else (K close to 64, many equal values, distances at +inf) it is left to
+// the walk.  Per eight queries about 500 vector instructions and two trips to
+// LDS, where the walk took K dependent steps of some 60 in each lane.
+//
+// Lane p of a segment holds the elements 8 l .. 8 l + 7 of the merged order, with
+// l such that l ^ 4, l ^ 2, l ^ 1 are the DPP partners p ^ 7, p ^ 2, p ^ 1.
+__device__ __forceinline__ bool select_queries(const FrameDesc& f, const uint64_t* keys, int n,
+                                               uint32_t first, int band_lo, int r0, int q0, float x,
+                                               int a0, uint16_t (*list)[SP_SIDE]) {
+    const int L = (int)(threadIdx.x & 63u);
+    const int W = f.W, C = f.C, K = f.K;
+    const int seg = L >> 3, p = L & 7;
+    const int l = (p & 4) ? 4 | ((p ^ 7) & 3) : p;
+    auto phys = [&](int ll) { return (L & 56) | ((ll & 4) ? (ll & 3) ^ 7 : ll); };  // lane of logical ll
+    const int next = phys(min(l + 1, 7)), last = phys(7);
+    const uint32_t k4 = (l & 4) ? ~0u : 0u, k2 = (l & 2) ? ~0u : 0u, k1 = (l & 1) ? ~0u : 0u;
+    constexpr uint32_t NOKEY = 0x7f800000u;
+    auto pos_of = [](int a, uint32_t slot) {  // band position of a packed key's slot
+        const int e = (int)(slot & 63u);
+        return (slot & 64u) ? a + e : a - 1 - e;
+    };
+    bool done = false;
+    uint64_t ok0 = 0, ok1 = 0;  // finished segments of the even and the odd round
+    const float rc = __builtin_amdgcn_rcpf((float)C);
+    for (int t = 0; t < 8; ++t) {
+        if (q0 + 8 * t >= 2 * W) break;
+        const int src = 8 * t + seg;
+        const int qi = q0 + src;
+        const float xq = __uint_as_float(lane_get(__float_as_uint(x), src));
+        const int aq = (int)lane_get((uint32_t)a0, src);
+        const int qr = qi >= W ? 1 : 0;
+        const int r = r0 + qr, c = qi - qr * W;
+        const bool live = qi < 2 * W && r < f.H;
+        const uint32_t q = (uint32_t)r * (uint32_t)W + (uint32_t)c;
+        const int lo_q = (max(0, r - f.R) - band_lo) * W;
+        const int hi_q = (min(f.H - 1, r + f.R) - band_lo + 1) * W;
+
+        uint32_t z[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t el = (uint32_t)(8 * l + u), er = 63u - el;
+            const int pl = aq - 1 - (int)el, pr = aq + (int)er;
+            const uint32_t vl = (uint32_t)(keys[sw(max(pl, 0))] >> 32);
+            const uint32_t vr = (uint32_t)(keys[sw(min(pr, n - 1))] >> 32);
+            const uint32_t dl = pl >= 0 ? min(dist0(xq, unsortable(vl)), NOKEY) : NOKEY;
+            const uint32_t dr = pr < n ? min(dist0(xq, unsortable(vr)), NOKEY) : NOKEY;
+            z[u] = min((dl & ~127u) | el, (dr & ~127u) | 64u | er);
+        }
+        cross<DPP_XOR7, false>(z, k4);
+        cross<DPP_XOR2, false>(z, k2);
+        cross<DPP_XOR1, false>(z, k1);
+        lane_merge<8>(z);
+
+        // full keys, in (d, idx) order
+        uint64_t y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int pos = min(max(pos_of(aq, z[u]), 0), n - 1);
+            const uint64_t key = keys[sw(pos)];
+            y[u] = ((uint64_t)(z[u] < NOKEY ? dist0(xq, key_value(key)) : ~0u) << 32) | key_index(key);
+        }
+        const uint32_t zlast = lane_get(z[7], last);
+        bool tie = l < 7 && ((lane_get(z[0], next) ^ z[7]) < 128u);
+#pragma unroll
+        for (int u = 0; u < 7; ++u) tie |= (z[u] ^ z[u + 1]) < 128u;
+        if (ballot(tie)) {
+            for (;;) {
+                bool moved = false;
+#pragma unroll
+                for (int ph = 0; ph < 2; ++ph) {
+#pragma unroll
+                    for (int u = ph; u + 1 < 8; u += 2) {
+                        const uint64_t a = y[u], b = y[u + 1];
+                        const bool s = b < a;
+                        y[u] = s ? b : a;
+                        y[u + 1] = s ? a : b;
+                        moved |= s;
+                    }
+                }
+                // pair (lane's last, next lane's first)
+                const int prev = phys(max(l - 1, 0));
+                const uint64_t nx = ((uint64_t)lane_get((uint32_t)(y[0] >> 32), next) << 32) |
+                                    lane_get((uint32_t)y[0], next);
+                const uint64_t pv = ((uint64_t)lane_get((uint32_t)(y[7] >> 32), prev) << 32) |
+                                    lane_get((uint32_t)y[7], prev);
+                const bool tn = l < 7 && nx < y[7], tp = l > 0 && y[0] < pv;
+                y[7] = tn ? nx : y[7];
+                y[0] = tp ? pv : y[0];
+                moved |= tn;
+                if (!ballot(moved)) break;
+            }
+        }
+        // ranks of the candidates inside the query's window
+        uint32_t okm = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int e = (int)((uint32_t)y[u] - first);
+            if ((uint32_t)(y[u] >> 32) < NOKEY && e >= lo_q && e < hi_q) okm |= 1u << u;
+        }
+        const int own = __builtin_popcount(okm);
+        int incl = own;
+#pragma unroll
+        for (int d = 1; d < 8; d *= 2) {
+            const int o = (int)lane_get((uint32_t)incl, phys(max(l - d, 0)));
+            if (l >= d) incl += o;
+        }
+        int rank = incl - own;
+        bool fin = false;
+        const int j = 8 * (t & 1) + seg;
+        int rk[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const bool ok = (okm >> u) & 1u;
+            rk[u] = ok ? rank : K;
+            fin |= ok && rank == K - 1 &&
+                   (zlast >= NOKEY || ((uint32_t)(y[u] >> 32) & ~127u) < (zlast & ~127u));
+            rank += ok ? 1 : 0;
+        }
+        const uint64_t okb = ballot(fin && live);
+        ok0 = (t & 1) ? ok0 : okb;
+        ok1 = (t & 1) ? okb : 0;
+        const bool mine = (uint32_t)(okb >> (8 * seg)) & 0xffu;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (mine && rk[u] < K) {
+                list[j][rk[u]] = (uint16_t)((uint32_t)y[u] - first);
+                if (f.out_nbr) {
+                    f.out_nbr[(size_t)q * K + rk[u]] = (int32_t)(uint32_t)y[u];
+                    f.out_dist[(size_t)q * K + rk[u]] = __uint_as_float((uint32_t)(y[u] >> 32));
+                }
+            }
+        }
+        if (t == (L >> 3)) done = (uint32_t)(okb >> (8 * (L & 7))) & 0xffu;
+        const bool more = t < 7 && q0 + 8 * (t + 1) < 2 * W;
+        if (!(t & 1) && more) continue;
+
+        // ---- Eq. 2 of the last two rounds: one lane per (query, class)
+        wave_sync();
+        const float* __restrict__ pb = f.prob + (size_t)first * C;
+        const int qb = q0 + 8 * (t & ~1);
+        float sums[SP_MAX_C / 4];
+        auto query_ok = [&](int jj) { return (uint32_t)((jj < 8 ? ok0 : ok1) >> (8 * (jj & 7))) & 0xffu; };
+#pragma unroll
+        for (int it = 0; it < SP_MAX_C / 4; ++it) {
+            const int w = L + 64 * it;
+            sums[it] = 0.0f;
+            if (w < SP_GROUP * C) {
+                // w / C: (w + 0.5) / C is at least 1/32 from an integer
+                const int jj = (int)(((float)w + 0.5f) * rc), cl = w - jj * C;
+                if (query_ok(jj)) {
+                    const uint16_t* lst = list[jj];
+                    float s = 0.0f;
+                    int k = 0;
+                    for (; k + 8 <= K; k += 8) {
+                        const uint4 pk = *(const uint4*)(lst + k);
+                        const uint32_t o[4] = {pk.x, pk.y, pk.z, pk.w};
+                        float v[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            v[u] = pb[((o[u / 2] >> (16 * (u & 1))) & 0xffffu) * (uint32_t)C + (uint32_t)cl];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) s = s + v[u];
+                    }
+                    for (; k < K; ++k) s = s + pb[(uint32_t)lst[k] * (uint32_t)C + (uint32_t)cl];
+                    sums[it] = s;
+                    const int qq = qb + jj;
+                    const int row = qq >= W ? 1 : 0;
+                    f.out_prob[((size_t)(r0 + row) * W + (qq - row * W)) * C + cl] = s / (float)K;
+                }
+            }
+        }
+        wave_sync();  // the lists have been read: the sums take their place
+        float* sm = (float*)list;
+#pragma unroll
+        for (int it = 0; it < SP_MAX_C / 4; ++it) {
+            const int w = L + 64 * it;
+            if (w < SP_GROUP * C) sm[w] = sums[it];
+        }
+        wave_sync();
+        if (L < SP_GROUP && query_ok(L)) {
+            int best = 0;
+            float bs = sm[L * C];
+            for (int cl = 1; cl < C; ++cl) {
+                const float v = sm[L * C + cl];
+                if (v > bs) {
+                    bs = v;
+                    best = cl;
+                }
+            }
+            const int qq = qb + L;
+            const int row = qq >= W ? 1 : 0;
+            f.out_class[(size_t)(r0 + row) * W + (qq - row * W)] = best;
+        }
+        wave_sync();
+    }
+    return done;
+}
+
 __global__ void __launch_bounds__(SP_THREADS)
 spectral_filter_kernel(FrameDesc f, int T) {
     __shared__ uint64_t keys[SP_MAX];
+    __shared__ __attribute__((aligned(16))) uint16_t lists[SP_THREADS / 64][SP_GROUP][SP_SIDE];
     // two query rows per workgroup share one band: the rows of both windows
     const int r0 = 2 * (int)blockIdx.x;
     const int t = threadIdx.x;
@@ -181,10 +411,11 @@ spectral_filter_kernel(FrameDesc f, int T) {
     // ---- 2. + 3. one lane per query pixel of rows r0 and r0 + 1
     const float* __restrict__ prob = f.prob;
     const bool vec4 = C % 4 == 0 && ((uintptr_t)prob & 15) == 0;
-    for (int qi = t; qi < 2 * W; qi += SP_THREADS) {
+    // (a wavefront's lanes stay together: select_queries is cooperative)
+    for (int qi = t; qi - (t & 63) < 2 * W; qi += SP_THREADS) {
         const int qr = qi >= W ? 1 : 0;
         const int r = r0 + qr, c = qi - qr * W;
-        if (r >= f.H) break;
+        const bool live = qi < 2 * W && r < f.H;
         // the query's own window as band offsets [lo_q, hi_q): keys of the
         // band's other rows are skipped
         const int lo_q = (max(0, r - f.R) - lo) * W;
@@ -194,7 +425,7 @@ spectral_filter_kernel(FrameDesc f, int T) {
             return e >= lo_q && e < hi_q;
         };
         const uint32_t q = (uint32_t)r * (uint32_t)W + (uint32_t)c;
-        const float x = f.pc1[q];
+        const float x = live ? f.pc1[q] : 0.0f;
         // first key whose value is >= x
         const uint64_t probe = (uint64_t)sortable(x) << 32;
         int a0 = 0, a1 = n;
@@ -203,6 +434,9 @@ spectral_filter_kernel(FrameDesc f, int T) {
             if (keys[sw(mid)] < probe) a0 = mid + 1;
             else a1 = mid;
         }
+        const bool done = select_queries(f, keys, n, first, lo, r0, qi - (t & 63), x, a0, lists[t >> 6]);
+        if (done || !live) continue;
+        // the walk, for what the selection leaves
         int L = a0 - 1, Rc = a0;  // next candidates below and above
         float s[SP_MAX_C];
 #pragma unroll
