@@ -53,8 +53,25 @@ struct BatchSlot {
     void* host_dev = nullptr;  // device address of the pinned staging, if mapped
     size_t cap = 0;           // work items
     hipEvent_t done = nullptr;
+    hipStream_t stream = nullptr;  // that `done` was recorded on
     bool recorded = false;
 };
+
+// Wait for the launch that used the slot.  The runtime looks into the stream that
+// an event was recorded on, which its owner may have destroyed since (a call then
+// failed with "event last recorded in a capturing stream", by what lay there), so
+// a stream other than the caller's `now`, which is alive, is asked by its handle
+// first; the runtime knows the valid ones.
+hipError_t wait_slot(BatchSlot& s, hipStream_t now) {
+    s.recorded = false;
+    if (s.stream != now) {
+        const hipError_t q = hipStreamQuery(s.stream);
+        if (q != hipSuccess) (void)hipGetLastError();
+        if (q == hipSuccess) return q;  // the stream is idle
+        if (q != hipErrorNotReady) return hipDeviceSynchronize();
+    }
+    return hipEventSynchronize(s.done);
+}
 
 size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 size_t off_task_start(size_t cap) { return round256(cap * sizeof(knnf::FrameDesc)); }
@@ -426,9 +443,8 @@ knnf_status launch_items(knnf_ctx* ctx, const WorkItem* items, int n, const knnf
     ctx->next_slot = (ctx->next_slot + 1) % kSlots;
     hipError_t e;
     if (s.recorded) {
-        e = hipEventSynchronize(s.done);
+        e = wait_slot(s, (hipStream_t)stream);
         if (e != hipSuccess) return ctx_fail(ctx, e, "batch slot wait");
-        s.recorded = false;
     }
     e = grow_slot(s, (size_t)n);
     if (e != hipSuccess) return fail(KNNF_ENOMEM, "batch table: %s", hipGetErrorString(e));
@@ -510,6 +526,7 @@ knnf_status launch_items(knnf_ctx* ctx, const WorkItem* items, int n, const knnf
         if (rc != 0) return ctx_fail(ctx, (hipError_t)rc, "batched launch");
         e = hipEventRecord(s.done, hs);
         if (e != hipSuccess) return ctx_fail(ctx, e, "batch slot record");
+        s.stream = hs;
         s.recorded = true;
         return KNNF_OK;
     }
@@ -526,8 +543,15 @@ knnf_status launch_items(knnf_ctx* ctx, const WorkItem* items, int n, const knnf
     if (rc != 0) return ctx_fail(ctx, (hipError_t)rc, "batched launch");
     e = hipEventRecord(s.done, hs);
     if (e != hipSuccess) return ctx_fail(ctx, e, "batch slot record");
+    s.stream = hs;
     s.recorded = true;
     return KNNF_OK;
+}
+
+void forget_stream(knnf_ctx* ctx, void* stream) {
+    std::lock_guard<std::mutex> lock(ctx->mu);
+    for (BatchSlot& s : ctx->slots)
+        if (s.recorded && s.stream == (hipStream_t)stream) (void)wait_slot(s, s.stream);
 }
 
 }  // namespace knnf
@@ -599,7 +623,7 @@ knnf_status knnf_destroy(knnf_ctx* ctx) {
     hipSetDevice(ctx->device);
     for (auto& s : ctx->slots) {
         if (s.done) {
-            if (s.recorded) hipEventSynchronize(s.done);
+            if (s.recorded) (void)wait_slot(s, nullptr);
             hipEventDestroy(s.done);
         }
         if (s.dev) hipFree(s.dev);
