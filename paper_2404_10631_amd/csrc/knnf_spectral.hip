@@ -43,7 +43,7 @@
 //      a group are in flight together (one at a time, each waited for its
 //      predecessor's latency).
 // W480 x H380, K = 40: the sort takes 58 us, search, selection and Eq. 2 53 and the
-// few walks 7 (124.5 us a call; 173 with a walk for every query).
+// few walks 2 (119 us a call; 173 with a walk for every query).
 // Work: O(n log n) per query row for the sort (n = band size) and
 // O(log n + K) per query, against O(n) distances per query for the scans.
 // Two query rows per workgroup halve the sorting per row and put the
@@ -196,7 +196,8 @@ __device__ __forceinline__ uint32_t lane_get(uint32_t v, int src) {
 __device__ __forceinline__ bool select_queries(const FrameDesc& f, const uint64_t* keys, int n,
                                                uint32_t first, int band_lo, int r0, int q0, float x,
                                                int a0, uint16_t (*list)[SP_SIDE]) {
-    const int L = (int)(threadIdx.x & 63u);
+    int L = (int)(threadIdx.x & 63u);
+    asm volatile("" : "+v"(L));  // its lane constants are not kept in registers across the walk
     const int W = f.W, C = f.C, K = f.K;
     const int seg = L >> 3, p = L & 7;
     const int l = (p & 4) ? 4 | ((p ^ 7) & 3) : p;
