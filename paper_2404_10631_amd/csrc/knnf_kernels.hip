@@ -20,14 +20,13 @@
 // Work decomposition (not the paper's; designed for 64-wide wavefronts):
 //   * One wavefront task = a tile of QR x QC query pixels (default 1 x 8).
 //     Per-query state lives in VGPRs and a small per-wavefront LDS block.
-//   * pass A (bound): the 128 candidates (8-query tiles; 64 for 16-query
-//     tiles) of a compact block around each query (8 rows x 16 columns where
-//     the window allows) are evaluated and sorted for all Q queries at once
-//     by a segmented bitonic network; any distance with at least K block
-//     candidates at or below it bounds the query's final K-th key from
-//     above.  The block is sorted as two interleaved groups (16-bit keys, both
-//     in one packed network); the bound is the larger of the groups'
-//     ceil(K/2)-th keys.
+//   * pass A (bound): the 64 or 128 candidates (see SMALL_K) of a compact block
+//     around each query (8 rows x 8 or 16 columns where the window allows) are
+//     evaluated and ranked for all Q queries at once by a segmented network;
+//     any distance with at least K block candidates at or below it bounds the
+//     query's final K-th key from above.  The block is ranked as two interleaved
+//     groups (16-bit keys, both in one packed network); the bound is the larger
+//     of the groups' ceil(K/2)-th keys.
 //   * pass B (collect): candidates with d <= d_K are appended to a per-query
 //     LDS buffer with ballot + mbcnt; a full buffer is cut down by a tighter
 //     bound.  Two scans:
@@ -328,13 +327,20 @@ constexpr uint32_t BIG = PAD - 1;
 constexpr int ROWS = 32;  // neighbour rows staged at a time in Eq. 2 (four classes)
 
 // Per-wavefront LDS state of one tile of QR x QC query pixels.
+template <int E>
+__device__ __forceinline__ int row_at(int r) { return E >= 8 ? r + (r >> 3) : r; }
+
 template <int QR, int QC>
 struct alignas(16) TileState {
     static constexpr int Q = QR * QC;
     union {
         uint32_t pend[Q][2][WAVE]; // candidates that passed the bound, unsorted: distance
                                  // bits, linear indices
-        float4 rows[Q][ROWS + 1];// four classes: the neighbours' probability rows, in order
+        // four classes: the neighbours' probability rows, in order; where a lane
+        // stores eight, one row is skipped after them (row_at: without the gap half
+        // the lanes of a segment met on each bank; 1000 x 1000, K = 40: 203 us
+        // against 210)
+        float4 rows[Q][ROWS + ROWS / 8 + 1];
         struct {                 // other class counts:
             // neighbours' linear indices in order; rows padded by 16 bytes so that
             // the queries' rows start on different banks (Eq. 2 reads the same
@@ -388,8 +394,8 @@ __device__ __forceinline__ void order_query(TileState<QR, QC>& S, const FrameDes
 }
 
 // Make room in query q's full buffer: nb pending candidates and this step's (dn:
-// each lane's distance bits, all ones for none; idx its linear index), of which
-// `over` lie within the bound.  Any distance t with at least K candidates at or
+// each lane's distance bits, all ones for none; idx its linear index), more than
+// 64 of them within the bound.  Any distance t with at least K candidates at or
 // below it bounds the K-th key, so a t that leaves at most 64 of them is found
 // by bisection (its counts are ballots), the buffer keeps those, and the bound
 // becomes t.  Where equal distances leave no such t, the smallest t with K
@@ -992,7 +998,7 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
             wave_sync();  // the buffers, or the rows before, have been read
             if (sok && lp * E / ROWS == h && lp * E < K) {
 #pragma unroll
-                for (int u = 0; u < E; ++u) *(f4*)&S.rows[sq][lp * E % ROWS + u] = row[u];
+                for (int u = 0; u < E; ++u) *(f4*)&S.rows[sq][row_at<E>(lp * E % ROWS + u)] = row[u];
             }
             wave_sync();
         };
@@ -1001,11 +1007,11 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
             for (; k + 8 <= n; k += 8) {
                 float v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = col[4 * (k + u)];
+                for (int u = 0; u < 8; ++u) v[u] = col[4 * (row_at<E>(k) + u)];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) s = s + v[u];
             }
-            for (; k < n; ++k) s = s + col[4 * k];
+            for (; k < n; ++k) s = s + col[4 * row_at<E>(k)];
         };
         put_rows(0);
         add_rows(min(ROWS, K));
@@ -1352,8 +1358,8 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 
 // 8-query tiles are held to 72 VGPRs, seven wavefronts per SIMD: 380 x 480 K=40
 // 52.3 us, 1000 x 1000 210, 1024 frames of 50 x 50 449; six wavefronts 53.6, 218
-// and 472; eight (64 registers, some spilled) 54.4, 212 and 447.  Their 4,320
-// bytes of LDS would allow nine.
+// and 472; eight (64 registers, some spilled) 54.4, 212 and 447.  Their 4,832
+// bytes of LDS would allow eight.
 #define KNNF_WAVES_PER_EU(QR, QC) __attribute__((amdgpu_waves_per_eu((QR) * (QC) == 8 ? 7 : 1)))
 
 template <int QR, int QC, int WPB, bool PRUNE>
