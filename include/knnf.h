@@ -216,8 +216,10 @@ knnf_status knnf_filter(knnf_ctx* ctx, const knnf_frame* frame,
  * on `stream` over a table of per-wavefront tile tasks, largest frames first
  * (plan->launch: one wavefront per task, or a persistent grid whose
  * wavefronts claim tasks from a shared counter).  Every frame's outputs are bitwise
- * equal to knnf_filter() of that frame alone.  The frame table is copied to
- * the context's device workspace with an asynchronous copy on `stream`; the
+ * equal to knnf_filter() of that frame alone.  The frame table is written to
+ * the context's device workspace on `stream` (a call may wait for an earlier one
+ * whose table it takes over; a call that a stream capture records, with the input
+ * check off, has a table of its own for the life of the context); the
  * caller's array may be reused when the call returns.  plan may be NULL: then
  * the plan knnf_tune cached for this frame list, else the context's default.
  * Calls on one context must not run concurrently from several host threads.

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -13,7 +14,9 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/knnf.h"
@@ -44,33 +47,38 @@ knnf_status hip_fail(hipError_t e, const char* what) {
 }
 
 // One slot of batch tables: device work table (frame descriptors, task
-// prefix, first tiles, claim counter) and a pinned host staging copy.  `done`
-// is recorded after the launch that uses the slot, so the slot is reused only
-// after that launch has finished.
+// prefix, first tiles, claim counter) and a pinned host staging copy.  `busy`
+// is a word of device-visible pinned host memory: set before the launch that uses
+// the slot, cleared by a kernel that follows it on its stream, so the slot is
+// reused only after that launch has finished.
 struct BatchSlot {
     void* dev = nullptr;
     void* host = nullptr;
     void* host_dev = nullptr;  // device address of the pinned staging, if mapped
     size_t cap = 0;           // work items
-    hipEvent_t done = nullptr;
-    hipStream_t stream = nullptr;  // that `done` was recorded on
-    bool recorded = false;
+    uint32_t* busy = nullptr;
+    uint32_t* busy_dev = nullptr;
 };
 
-// Wait for the launch that used the slot.  The runtime looks into the stream that
-// an event was recorded on, which its owner may have destroyed since (a call then
-// failed with "event last recorded in a capturing stream", by what lay there), so
-// a stream other than the caller's `now`, which is alive, is asked by its handle
-// first; the runtime knows the valid ones.
-hipError_t wait_slot(BatchSlot& s, hipStream_t now) {
-    s.recorded = false;
-    if (s.stream != now) {
-        const hipError_t q = hipStreamQuery(s.stream);
-        if (q != hipSuccess) (void)hipGetLastError();
-        if (q == hipSuccess) return q;  // the stream is idle
-        if (q != hipErrorNotReady) return hipDeviceSynchronize();
+// Wait for the launch that used the slot.  Nothing of the stream that it ran on is
+// looked at, neither by its handle nor through an event recorded on it: its owner
+// may have destroyed it since, another stream may have its handle, and the
+// per-thread stream's handle means another stream in each thread.  Should the word
+// stay set (work dropped with its stream), the whole device is waited for.
+void wait_slot(const BatchSlot& s) {
+    using clk = std::chrono::steady_clock;
+    auto busy = [&] { return __atomic_load_n(s.busy, __ATOMIC_ACQUIRE) != 0; };
+    for (int k = 0; k < 2000; ++k)
+        if (!busy()) return;
+    auto t0 = clk::now();
+    while (busy()) {
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
+        if (clk::now() - t0 < std::chrono::seconds(30)) continue;
+        if (hipDeviceSynchronize() == hipSuccess) break;
+        (void)hipGetLastError();
+        t0 = clk::now();
     }
-    return hipEventSynchronize(s.done);
+    __atomic_store_n(s.busy, 0u, __ATOMIC_RELAXED);
 }
 
 size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -130,6 +138,7 @@ struct knnf_ctx {
     std::mutex mu;
     BatchSlot slots[kSlots];
     int next_slot = 0;
+    std::vector<BatchSlot> captured;  // tables of batches recorded in stream captures
     unsigned long long* d_stats = nullptr;  // work counters while enabled
     bool stats_on = false;
     // PC1 workspace: [per-block (min, max) pairs][npix doubles]
@@ -138,7 +147,8 @@ struct knnf_ctx {
     // failure state: once a HIP call failed, every call returns KNNF_EDEVICE
     std::atomic<int> failed{0};
     char failed_msg[256] = {0};
-    // non-finite input check flags (host memory, and its device address)
+    // non-finite input check flags, then the slots' busy words (host memory, and its
+    // device address)
     uint32_t* check_host = nullptr;
     uint32_t* check_dev = nullptr;
     std::atomic<uint32_t> check_gen{0};
@@ -439,16 +449,36 @@ knnf_status launch_items(knnf_ctx* ctx, const WorkItem* items, int n, const knnf
         ~Restore() { if (prev != dev) hipSetDevice(prev); }
     } restore{prev, ctx->device};
 
-    BatchSlot& s = ctx->slots[ctx->next_slot];
-    ctx->next_slot = (ctx->next_slot + 1) % kSlots;
-    hipError_t e;
-    if (s.recorded) {
-        e = wait_slot(s, (hipStream_t)stream);
-        if (e != hipSuccess) return ctx_fail(ctx, e, "batch slot wait");
-    }
-    e = grow_slot(s, (size_t)n);
-    if (e != hipSuccess) return fail(KNNF_ENOMEM, "batch table: %s", hipGetErrorString(e));
     hipStream_t hs = (hipStream_t)stream;
+    hipError_t e;
+    // A batch that a stream capture records keeps a table of its own for the life of
+    // the context: the graph's replays, at any time, use it again.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(hs, &capture) != hipSuccess) (void)hipGetLastError();
+    const bool captured = capture != hipStreamCaptureStatusNone;
+    if (captured) {
+        BatchSlot own;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // allow allocations
+        const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        e = grow_slot(own, (size_t)n);
+        if (set) hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) return fail(KNNF_ENOMEM, "batch table: %s", hipGetErrorString(e));
+        try {
+            ctx->captured.push_back(own);
+        } catch (const std::bad_alloc&) {
+            hipFree(own.dev);
+            hipHostFree(own.host);
+            return fail(KNNF_ENOMEM, "batch table: out of host memory");
+        }
+    } else {
+        BatchSlot& next = ctx->slots[ctx->next_slot];
+        ctx->next_slot = (ctx->next_slot + 1) % kSlots;
+        wait_slot(next);
+        e = grow_slot(next, (size_t)n);
+        if (e != hipSuccess) return fail(KNNF_ENOMEM, "batch table: %s", hipGetErrorString(e));
+    }
+    const BatchSlot& s = captured ? ctx->captured.back()
+                                  : ctx->slots[(ctx->next_slot + kSlots - 1) % kSlots];
     constexpr size_t kDescWords = sizeof(knnf::FrameDesc) / 4;
     static_assert(sizeof(knnf::FrameDesc) % 4 == 0, "descriptor size");
     if ((size_t)n * (kDescWords + 2) + 1 <= (size_t)knnf::kTableWords) {
@@ -523,35 +553,32 @@ knnf_status launch_items(knnf_ctx* ctx, const WorkItem* items, int n, const knnf
                                        (const uint32_t*)((char*)s.dev + off_task_start(s.cap)),
                                        (const uint32_t*)((char*)s.dev + off_tile_base(s.cap)),
                                        (uint32_t)n, (uint32_t)total, cfg, stream);
-        if (rc != 0) return ctx_fail(ctx, (hipError_t)rc, "batched launch");
-        e = hipEventRecord(s.done, hs);
-        if (e != hipSuccess) return ctx_fail(ctx, e, "batch slot record");
-        s.stream = hs;
-        s.recorded = true;
-        return KNNF_OK;
+    } else {
+        rc = knnf::launch_zero_counter(d_ctr, stream);
+        if (rc != 0) return ctx_fail(ctx, (hipError_t)rc, "counter reset");
+        const uint64_t need_blocks = (total + p.waves - 1) / p.waves;
+        const int per_cu = knnf::persistent_blocks_per_cu(cfg);
+        const uint64_t grid = std::max<uint64_t>(1, std::min<uint64_t>(need_blocks,
+                                                      (uint64_t)ctx->num_cu * per_cu));
+        rc = knnf::launch_filter_batch((const knnf::FrameDesc*)s.dev,
+                                       (const uint32_t*)((char*)s.dev + off_task_start(s.cap)),
+                                       (const uint32_t*)((char*)s.dev + off_tile_base(s.cap)),
+                                       (uint32_t)n, (uint32_t)total, d_ctr, cfg, (int)grid, stream);
     }
-    rc = knnf::launch_zero_counter(d_ctr, stream);
-    if (rc != 0) return ctx_fail(ctx, (hipError_t)rc, "counter reset");
-    const uint64_t need_blocks = (total + p.waves - 1) / p.waves;
-    const int per_cu = knnf::persistent_blocks_per_cu(cfg);
-    const uint64_t grid = std::max<uint64_t>(1, std::min<uint64_t>(need_blocks,
-                                                  (uint64_t)ctx->num_cu * per_cu));
-    rc = knnf::launch_filter_batch((const knnf::FrameDesc*)s.dev,
-                                   (const uint32_t*)((char*)s.dev + off_task_start(s.cap)),
-                                   (const uint32_t*)((char*)s.dev + off_tile_base(s.cap)),
-                                   (uint32_t)n, (uint32_t)total, d_ctr, cfg, (int)grid, stream);
     if (rc != 0) return ctx_fail(ctx, (hipError_t)rc, "batched launch");
-    e = hipEventRecord(s.done, hs);
-    if (e != hipSuccess) return ctx_fail(ctx, e, "batch slot record");
-    s.stream = hs;
-    s.recorded = true;
+    if (captured) return KNNF_OK;
+    __atomic_store_n(s.busy, 1u, __ATOMIC_RELEASE);
+    rc = knnf::launch_zero_counter(s.busy_dev, stream);
+    if (rc != 0) {
+        __atomic_store_n(s.busy, 0u, __ATOMIC_RELAXED);
+        return ctx_fail(ctx, (hipError_t)rc, "batch slot mark");
+    }
     return KNNF_OK;
 }
 
-void forget_stream(knnf_ctx* ctx, void* stream) {
+void wait_batches(knnf_ctx* ctx) {
     std::lock_guard<std::mutex> lock(ctx->mu);
-    for (BatchSlot& s : ctx->slots)
-        if (s.recorded && s.stream == (hipStream_t)stream) (void)wait_slot(s, s.stream);
+    for (const BatchSlot& s : ctx->slots) wait_slot(s);
 }
 
 }  // namespace knnf
@@ -590,17 +617,17 @@ knnf_status knnf_create(knnf_ctx** out, int device) {
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
         c->num_cu = prop.multiProcessorCount;
-    for (auto& s : c->slots) {
-        e = hipEventCreateWithFlags(&s.done, hipEventDisableTiming);
-        if (e == hipSuccess) e = grow_slot(s, kSlotItems);
-        if (e != hipSuccess) break;
-    }
-    if (e == hipSuccess)
-        e = hipHostMalloc((void**)&c->check_host, kCheckSlots * sizeof(uint32_t),
-                          hipHostMallocMapped | hipHostMallocCoherent);
+    constexpr size_t words = kCheckSlots + kSlots;
+    e = hipHostMalloc((void**)&c->check_host, words * sizeof(uint32_t),
+                      hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) {
-        std::memset(c->check_host, 0, kCheckSlots * sizeof(uint32_t));
+        std::memset(c->check_host, 0, words * sizeof(uint32_t));
         e = hipHostGetDevicePointer((void**)&c->check_dev, c->check_host, 0);
+    }
+    for (int k = 0; k < kSlots && e == hipSuccess; ++k) {
+        c->slots[k].busy = c->check_host + kCheckSlots + k;
+        c->slots[k].busy_dev = c->check_dev + kCheckSlots + k;
+        e = grow_slot(c->slots[k], kSlotItems);
     }
     if (e == hipSuccess) e = (hipError_t)knnf::pc1_scratch_init(device, &c->pc1_scratch);
     hipSetDevice(prev);
@@ -622,12 +649,13 @@ knnf_status knnf_destroy(knnf_ctx* ctx) {
     hipGetDevice(&prev);
     hipSetDevice(ctx->device);
     for (auto& s : ctx->slots) {
-        if (s.done) {
-            if (s.recorded) (void)wait_slot(s, nullptr);
-            hipEventDestroy(s.done);
-        }
+        if (s.busy) wait_slot(s);
         if (s.dev) hipFree(s.dev);
         if (s.host) hipHostFree(s.host);
+    }
+    for (auto& s : ctx->captured) {
+        hipFree(s.dev);
+        hipHostFree(s.host);
     }
     if (ctx->d_stats) hipFree(ctx->d_stats);
     if (ctx->pc1_ws || ctx->check_host) hipDeviceSynchronize();

@@ -41,7 +41,8 @@ int launch_filter_batch(const FrameDesc* d_frames, const uint32_t* d_task_start,
 // query rows holds at most 16,384 pixels); same outputs as the scans.
 bool spectral_fits(const FrameDesc& f);
 int launch_spectral_frame(const FrameDesc& f, void* stream);
-// Zero the batched kernel's claim counter.
+// Zero the batched kernel's claim counter, or a batch slot's busy word (device-visible
+// host memory that the host polls).
 int launch_zero_counter(uint32_t* d_counter, void* stream);
 
 // Non-finite input check: the kernels store `gen` to *flag (device-visible

@@ -1605,7 +1605,9 @@ int launch_check_items(const FrameDesc* d_frames, uint32_t n, uint32_t max_words
     return (int)hipGetLastError();
 }
 
-__global__ void zero_counter_kernel(uint32_t* p) { *p = 0u; }
+__global__ void zero_counter_kernel(uint32_t* p) {
+    __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 int launch_zero_counter(uint32_t* d_counter, void* stream) {
     hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, d_counter);

@@ -120,7 +120,7 @@ int launch_filter_batch(const FrameDesc* d_frames, const uint32_t* d_task_start,
 int persistent_blocks_per_cu(const LaunchCfg&) { return 1; }
 
 int launch_zero_counter(uint32_t* d_counter, void* stream) {
-    return fakehip::enqueue((hipStream_t)stream, [d_counter] { *d_counter = 0; });
+    return fakehip::enqueue((hipStream_t)stream, [d_counter] { __atomic_store_n(d_counter, 0u, __ATOMIC_RELEASE); });
 }
 
 int launch_put_table(const TableWords& t, uint32_t* d_base, void* stream) {

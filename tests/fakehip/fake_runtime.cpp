@@ -16,6 +16,7 @@
 #include <cstring>
 #include <deque>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <set>
 #include <string>
@@ -30,13 +31,20 @@ struct FakeEvent {
     double t_done = 0.0;
 };
 
-struct FakeStream {
+// The work of one stream; a handle (FakeStream) names one at a time.
+struct FakeWorker {
     std::mutex mu;
     std::condition_variable cv;
     std::deque<std::function<void()>> q;
     uint64_t enq = 0, done = 0;
     bool stop = false;
-    std::thread worker;
+    std::thread thread;
+};
+
+struct FakeStream {
+    std::shared_ptr<FakeWorker> w;
+    bool capturing = false;
+    fakehip::Graph graph;
 };
 
 namespace {
@@ -44,6 +52,8 @@ namespace {
 thread_local hipError_t g_last = hipSuccess;
 std::mutex g_mu;                         // registries below
 std::set<FakeStream*> g_streams;
+std::vector<FakeStream*> g_free;         // destroyed handles, while they are reused
+bool g_reuse = false;
 std::map<const char*, size_t> g_pinned;  // pinned host allocations: base -> bytes
 std::atomic<int> g_fail_copy{-1};
 std::atomic<long> g_ops{0};
@@ -58,10 +68,10 @@ hipError_t set_last(hipError_t e) {
     return e;
 }
 
-void run_worker(FakeStream* s) {
+void run_worker(std::shared_ptr<FakeWorker> s) {
     std::unique_lock<std::mutex> lk(s->mu);
     for (;;) {
-        s->cv.wait(lk, [s] { return s->stop || !s->q.empty(); });
+        s->cv.wait(lk, [&s] { return s->stop || !s->q.empty(); });
         if (s->q.empty()) return;  // stopping and drained
         std::function<void()> op = std::move(s->q.front());
         s->q.pop_front();
@@ -72,6 +82,45 @@ void run_worker(FakeStream* s) {
         ++s->done;
         s->cv.notify_all();
     }
+}
+
+void finish(FakeWorker& w) {
+    {
+        std::lock_guard<std::mutex> lk(w.mu);
+        w.stop = true;
+        w.cv.notify_all();
+    }
+    if (w.thread.joinable()) w.thread.join();
+}
+
+// Workers of destroyed streams that go on in the background, joined at the end.
+struct Orphans {
+    std::vector<std::shared_ptr<FakeWorker>> all;
+    ~Orphans() {
+        for (auto& w : all) finish(*w);
+    }
+} g_orphans;
+
+std::shared_ptr<FakeWorker> new_worker() {
+    auto w = std::make_shared<FakeWorker>();
+    w->thread = std::thread(run_worker, w);
+    return w;
+}
+
+// The calling thread's own stream.
+struct PerThread {
+    std::shared_ptr<FakeWorker> w = new_worker();
+    ~PerThread() { finish(*w); }
+};
+
+// The worker a handle names now; null for a handle that names none.
+std::shared_ptr<FakeWorker> worker_of(hipStream_t s) {
+    if (s == hipStreamPerThread) {
+        thread_local PerThread own;
+        return own.w;
+    }
+    std::lock_guard<std::mutex> lk(g_mu);
+    return g_streams.count(s) ? s->w : nullptr;
 }
 
 void* alloc256(size_t n) {
@@ -90,13 +139,34 @@ hipError_t enqueue(hipStream_t s, std::function<void()> op) {
         g_ops.fetch_add(1);
         return hipSuccess;
     }
-    std::lock_guard<std::mutex> lk(s->mu);
-    s->q.push_back(std::move(op));
-    ++s->enq;
-    s->cv.notify_all();
+    const auto w = worker_of(s);
+    if (!w) return set_last(hipErrorContextIsDestroyed);
+    if (s != hipStreamPerThread && s->capturing) {
+        s->graph.push_back(std::move(op));
+        return hipSuccess;
+    }
+    std::lock_guard<std::mutex> lk(w->mu);
+    w->q.push_back(std::move(op));
+    ++w->enq;
+    w->cv.notify_all();
     return hipSuccess;
 }
 
+void reuse_stream_handles(bool on) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_reuse = on;
+}
+void begin_capture(hipStream_t s) {
+    s->graph.clear();
+    s->capturing = true;
+}
+Graph end_capture(hipStream_t s) {
+    s->capturing = false;
+    return std::move(s->graph);
+}
+void replay(const Graph& g, hipStream_t s) {
+    for (const auto& op : g) enqueue(s, op);
+}
 void fail_copy_after(int n) { g_fail_copy.store(n); }
 long ops_run() { return g_ops.load(); }
 
@@ -133,12 +203,17 @@ hipError_t hipGetLastError(void) {
     return e;
 }
 hipError_t hipDeviceSynchronize(void) {
-    std::set<FakeStream*> all;
+    std::vector<std::shared_ptr<FakeWorker>> all;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        all = g_streams;
+        for (FakeStream* s : g_streams) all.push_back(s->w);
+        all.insert(all.end(), g_orphans.all.begin(), g_orphans.all.end());
     }
-    for (FakeStream* s : all) hipStreamSynchronize(s);
+    for (auto& w : all) {
+        std::unique_lock<std::mutex> lk(w->mu);
+        const uint64_t target = w->enq;
+        w->cv.wait(lk, [&] { return w->done >= target; });
+    }
     return hipSuccess;
 }
 
@@ -201,41 +276,66 @@ hipError_t hipMemset(void* p, int v, size_t n) {
 }
 
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
-    FakeStream* x = new FakeStream;
-    x->worker = std::thread(run_worker, x);
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        g_streams.insert(x);
+    auto w = new_worker();
+    std::lock_guard<std::mutex> lk(g_mu);
+    FakeStream* x = nullptr;
+    if (!g_free.empty()) {
+        x = g_free.back();
+        g_free.pop_back();
+    } else {
+        x = new FakeStream;
     }
+    x->w = w;
+    g_streams.insert(x);
     *s = x;
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t s) {
     if (!s) return hipSuccess;
+    std::shared_ptr<FakeWorker> w;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        g_streams.erase(s);
+        if (!g_streams.erase(s)) return set_last(hipErrorContextIsDestroyed);
+        w = s->w;
+        if (g_reuse) {
+            s->w = nullptr;
+            g_free.push_back(s);
+            g_orphans.all.push_back(w);
+            return hipSuccess;
+        }
     }
-    {
-        std::lock_guard<std::mutex> lk(s->mu);
-        s->stop = true;
-        s->cv.notify_all();
-    }
-    s->worker.join();
+    finish(*w);
     delete s;
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t s) {
     if (!s) return hipSuccess;
-    std::unique_lock<std::mutex> lk(s->mu);
-    const uint64_t target = s->enq;
-    s->cv.wait(lk, [s, target] { return s->done >= target; });
+    const auto w = worker_of(s);
+    if (!w) return set_last(hipErrorContextIsDestroyed);
+    if (s != hipStreamPerThread && s->capturing) return set_last(hipErrorStreamCaptureUnsupported);
+    std::unique_lock<std::mutex> lk(w->mu);
+    const uint64_t target = w->enq;
+    w->cv.wait(lk, [&] { return w->done >= target; });
     return hipSuccess;
 }
 hipError_t hipStreamQuery(hipStream_t s) {
     if (!s) return hipSuccess;
-    std::lock_guard<std::mutex> lk(s->mu);
-    return s->done >= s->enq ? hipSuccess : set_last(hipErrorNotReady);
+    const auto w = worker_of(s);
+    if (!w) return set_last(hipErrorContextIsDestroyed);
+    std::lock_guard<std::mutex> lk(w->mu);
+    return w->done >= w->enq ? hipSuccess : set_last(hipErrorNotReady);
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status) {
+    *status = hipStreamCaptureStatusNone;
+    if (!s || s == hipStreamPerThread) return hipSuccess;
+    if (!worker_of(s)) return set_last(hipErrorContextIsDestroyed);
+    if (s->capturing) *status = hipStreamCaptureStatusActive;
+    return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode) {
+    static thread_local hipStreamCaptureMode now = hipStreamCaptureModeGlobal;
+    std::swap(now, *mode);
+    return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     uint64_t target;

@@ -18,6 +18,8 @@ enum {
     hipErrorInvalidValue = 1,
     hipErrorOutOfMemory = 2,
     hipErrorInvalidDevice = 101,
+    hipErrorContextIsDestroyed = 709,
+    hipErrorStreamCaptureUnsupported = 900,
     hipErrorNotReady = 600,
     hipErrorLaunchFailure = 719,
 };
@@ -49,6 +51,17 @@ struct hipPointerAttribute_t {
     void* hostPointer;
 };
 
+typedef enum {
+    hipStreamCaptureStatusNone = 0,
+    hipStreamCaptureStatusActive = 1
+} hipStreamCaptureStatus;
+typedef enum {
+    hipStreamCaptureModeGlobal = 0,
+    hipStreamCaptureModeThreadLocal = 1,
+    hipStreamCaptureModeRelaxed = 2
+} hipStreamCaptureMode;
+
+#define hipStreamPerThread ((hipStream_t)2)  // another stream in each thread
 #define hipEventDefault 0u
 #define hipEventDisableTiming 2u
 #define hipStreamDefault 0u
@@ -79,6 +92,8 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned flags);
 hipError_t hipStreamDestroy(hipStream_t s);
 hipError_t hipStreamSynchronize(hipStream_t s);
 hipError_t hipStreamQuery(hipStream_t s);
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status);
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode);
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
 
 hipError_t hipEventCreate(hipEvent_t* e);
@@ -91,11 +106,20 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b);
 
 // ---- controls of the fake, for the tests ----------------------------------
 #include <functional>
+#include <vector>
 namespace fakehip {
 // Run `op` on stream s in order (null stream: at once, on the calling thread).
 hipError_t enqueue(hipStream_t s, std::function<void()> op);
 // From now on, the n-th next hipMemcpyAsync (0 = the next one) fails.
 void fail_copy_after(int n);
+// From now on a destroyed stream's work goes on in the background, and its handle
+// names the next stream that is created (the runtime promises neither).
+void reuse_stream_handles(bool on);
+// Record s's operations instead of running them; their list; run it on a stream.
+typedef std::vector<std::function<void()>> Graph;
+void begin_capture(hipStream_t s);
+Graph end_capture(hipStream_t s);
+void replay(const Graph& g, hipStream_t s);
 // Number of operations each stream has run (all streams together).
 long ops_run();
 }  // namespace fakehip
