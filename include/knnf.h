@@ -359,7 +359,10 @@ knnf_status knnf_server_release(knnf_server* srv, uint64_t ticket);
 /* Wait until every submitted frame is done (timeout in seconds; <= 0: none). */
 knnf_status knnf_server_drain(knnf_server* srv, double timeout_s);
 
-/* Stop the scheduler after the GPU work in flight ends, and free the server. */
+/*
+ * Stop the scheduler after the GPU work in flight ends, and free the server.  The
+ * context is not touched: it may be destroyed before a server whose frames are done.
+ */
 knnf_status knnf_server_destroy(knnf_server* srv);
 
 /* ---- PC1 projection: the one-band image the filter reads ---------------

@@ -576,11 +576,6 @@ knnf_status launch_items(knnf_ctx* ctx, const WorkItem* items, int n, const knnf
     return KNNF_OK;
 }
 
-void wait_batches(knnf_ctx* ctx) {
-    std::lock_guard<std::mutex> lock(ctx->mu);
-    for (const BatchSlot& s : ctx->slots) wait_slot(s);
-}
-
 }  // namespace knnf
 
 extern "C" {

@@ -28,9 +28,6 @@ uint32_t tiles_of(int H, int W, const knnf_plan& p);
 knnf_status launch_items(knnf_ctx* ctx, const WorkItem* items, int n, const knnf_plan& p,
                          void* stream);
 
-// Wait for the launches of launch_items so far.
-void wait_batches(knnf_ctx* ctx);
-
 // Device ordinal of a context.
 int ctx_device(const knnf_ctx* ctx);
 

@@ -661,7 +661,6 @@ knnf_status knnf_server_destroy(knnf_server* s) {
     for (Step& st : s->steps) {
         if (st.stream) {
             hipStreamSynchronize(st.stream);
-            knnf::wait_batches(s->ctx);
             hipStreamDestroy(st.stream);
         }
         if (st.done) hipEventDestroy(st.done);

@@ -196,6 +196,29 @@ bool test_captured_batches() {
     return true;
 }
 
+// A server whose frames are done is closed after its context.
+bool test_server_closed_after_its_context() {
+    knnf_ctx* ctx = nullptr;
+    CHECK(knnf_create(&ctx, 0) == KNNF_OK);
+    void* pool = nullptr;
+    CHECK(hipMalloc(&pool, 1 << 20) == hipSuccess);
+    knnf_server* srv = nullptr;
+    CHECK(knnf_server_create(&srv, ctx, pool, 1 << 20, nullptr) == KNNF_OK);
+    Batch b(6, 90);
+    for (auto& f : b.frames) {
+        knnf_host_frame h{};
+        h.H = f->H, h.W = f->W, h.C = f->C, h.K = f->K, h.R = f->R, h.lambda = 0.01f;
+        h.pc1 = f->pc1.data(), h.prob = f->prob.data(), h.t_arrival = -1.0;
+        uint64_t t = 0;
+        CHECK(knnf_server_submit(srv, &h, &t) == KNNF_OK);
+    }
+    CHECK(knnf_server_drain(srv, 60.0) == KNNF_OK);
+    CHECK(knnf_destroy(ctx) == KNNF_OK);
+    CHECK(knnf_server_destroy(srv) == KNNF_OK);
+    hipFree(pool);
+    return true;
+}
+
 }  // namespace
 
 int main() {
@@ -204,6 +227,7 @@ int main() {
         {"destroyed_stream", test_destroyed_stream},
         {"per_thread_streams", test_per_thread_streams},
         {"captured_batches", test_captured_batches},
+        {"server_closed_after_its_context", test_server_closed_after_its_context},
     };
     int failed = 0;
     for (const auto& t : tests) {

@@ -5,7 +5,8 @@ A batched call takes the table that was used longest ago and has to wait for the
 launch that used it, whatever has become of that launch's stream: destroyed while
 the launch still ran, with another stream at its handle; the per-thread stream of
 another thread, which has the caller's handle; a stream whose work a capture
-recorded, to be replayed at any time.
+recorded, to be replayed at any time.  And closing a server leaves its context, which
+may be gone, alone.
 """
 import os
 import subprocess
@@ -14,7 +15,8 @@ import pytest
 
 from test_server_fake import CSRC, FAKE, ROOT, oracle_obj  # noqa: F401
 
-SOURCES = [os.path.join(CSRC, "knnf_api.cpp"), os.path.join(FAKE, "fake_runtime.cpp"),
+SOURCES = [os.path.join(CSRC, "knnf_api.cpp"), os.path.join(CSRC, "knnf_server.cpp"),
+           os.path.join(FAKE, "fake_runtime.cpp"),
            os.path.join(FAKE, "fake_device.cpp"), os.path.join(FAKE, "test_batch_slots.cpp")]
 
 
@@ -37,4 +39,4 @@ def test_tables_are_reused_after_their_launch(oracle_obj, name, flags, env):  # 
     run = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=dict(os.environ, **env))
     assert run.returncode == 0, (run.stdout + run.stderr)[-4000:]
     assert run.stdout.split() == ["ok", "destroyed_stream", "ok", "per_thread_streams", "ok",
-                                  "captured_batches"]
+                                  "captured_batches", "ok", "server_closed_after_its_context"]
