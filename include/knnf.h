@@ -460,10 +460,10 @@ knnf_status knnf_svm(knnf_ctx* ctx, const float* cube, int64_t npix, int32_t ban
  * projection from the same staged bands (the pipeline's classification and
  * dimensionality-reduction steps, Sec. II.C.1-2, read the image once instead
  * of twice).  out_prob is knnf_svm's output (bitwise the same); out_band is
- * knnf_pc1's (normalize as there; the projection is summed uncentred, as one
- * more column of the hyperplanes' product, and the constant mean . vec is
- * subtracted, so it can differ from knnf_pc1's, which centres each band, by
- * the last binary32 bit).  Arguments, layouts and limits as in
+ * knnf_pc1's (normalize as there; each band is centred as there, but the
+ * binary64 terms are summed in another order, so the results differ by the rounding
+ * of those sums, as a rule in the last binary32 bit at most).  Arguments, layouts and
+ * limits as in
  * those two calls; `cube` must hold both steps' input.  With normalize != 0
  * it uses the context workspace of knnf_pc1 (8 B per pixel plus 16 B per 256
  * pixels; growing it synchronizes the device and allocates).  Asynchronous on

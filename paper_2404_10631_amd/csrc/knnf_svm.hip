@@ -44,14 +44,19 @@
 //     operand order.
 //   * The sums go through LDS to one lane per pixel for the sigmoids and the
 //     coupling iteration, whose sweep count differs from pixel to pixel.
-// The fused variant (PC1 = true) carries the PC1 projection as one more column
-// of the product, so the pipeline's two steps before the filter read the cube
-// once.
+// The fused variant (PC1 = true) adds the PC1 projection, so the pipeline's two steps
+// before the filter read the cube once.  Its terms are centred, so they can not be one
+// more column of the product: each lane forms those of its pieces as they arrive (the
+// averages and eigenvector entries of its four bands stay in registers), and they go
+// through the item's LDS buffer to the four lanes of a pixel that sum them.  (Uncentred, as a column of the product with one constant subtracted at the
+// end, it took 25.3 instead of 27.2 us a call on 380 x 480 x 128, but its error was that
+// of the uncentred terms: sensor counts of 60,000 +- 2 came out up to 0.18 of a
+// binary32 ulp off at 128 bands, 1.1 at 4,096.)
 // What bounds it: 1000 x 1000 x 100, four classes, 84.5 us (105 us with the
 // lane-per-pixel product): the same kernel without its arithmetic takes 74 us
 // (5.6 TB/s, the rate of a plain read of the cube), the vector pipe is busy
-// for 50 us, and the two overlap only in part.  380 x 480 x 128 fused, 21 us
-// of kernel (27 us before), 17 us without the arithmetic.
+// for 50 us, and the two overlap only in part.  380 x 480 x 128 fused, 23 us
+// of kernel (27 us with the lane-per-pixel product), 17 us without the arithmetic.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -229,13 +234,11 @@ __device__ __forceinline__ float4 load4(const char* p) {
     return v;
 }
 
-// Columns of the product: the M hyperplanes, and (PC1) the eigenvector; in
-// groups of four.
-template <int C, bool PC1>
+// Columns of the product, the M hyperplanes, in groups of four.
+template <int C>
 struct SvmCols {
     static constexpr int M = C * (C - 1) / 2;
-    static constexpr int N = M + (PC1 ? 1 : 0);
-    static constexpr int NG = (N + 3) / 4;
+    static constexpr int NG = (M + 3) / 4;
     static constexpr int ST = 4 * NG + 1;  // exchange row (doubles): odd, so the rows' banks differ
     // pixels per exchange: a whole tile where its rows are short
     static constexpr int XP = NG <= 3 ? SVM_TILE : 16;
@@ -259,17 +262,20 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
                 float* __restrict__ out, const double* __restrict__ mean,
                 const double* __restrict__ vec, float* __restrict__ band,
                 double* __restrict__ ws, double* __restrict__ pairs) {
-    using Cols = SvmCols<C, PC1>;
-    constexpr int M = Cols::M, N = Cols::N, NG = Cols::NG, ST = Cols::ST, XP = Cols::XP;
+    using Cols = SvmCols<C>;
+    constexpr int M = Cols::M, NG = Cols::NG, ST = Cols::ST, XP = Cols::XP;
     constexpr int G = SVM_TILE / 16;
     constexpr int MAXP = NL * 4;  // pieces per pixel of an item
     // weights[(4 s + e) / 2][group][k][n][e % 2]: lane (k, n) of matrix steps e
     // and e + 1 reads 16 bytes
     __shared__ __attribute__((aligned(16))) double wl[NL * Cols::WST];
     // an item's pieces, a row of MAXP per pixel and one of padding (bank
-    // spread); after the tile's last item, its sums
+    // spread), after the projection's term of each (PC1); after the tile's last
+    // item, its sums
     union Buf {
         float4 x[16 * (MAXP + 1)];
+        double term[16 * (MAXP + 1)];
+        double part[SVM_TILE / 16][64];
         double sum[XP * ST];
     };
     __shared__ __attribute__((aligned(16))) Buf buf[SVM_THREADS / 64];
@@ -303,14 +309,14 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
     constexpr int SPT = SVM_THREADS / (4 * NG), NSLOT = MAXP * 4;
     constexpr int NW = (NSLOT + SPT - 1) / SPT;
     const int wcol = tid % (4 * NG), wslot = tid / (4 * NG);
-    const double* wsrc = PC1 && wcol == M ? vec : w + (wcol < M ? wcol * bands : 0);
+    const double* wsrc = w + (wcol < M ? wcol * bands : 0);
     double wr[NW];
     auto fetch_weights = [&](int chunk) {
 #pragma unroll
         for (int j = 0; j < NW; ++j) {
             const int slot = wslot + SPT * j + chunk * NSLOT, piece = slot >> 2;
             const int b = piece < np - 1 ? slot : bands - 4 + (slot & 3);
-            const bool used = wcol < N && piece < np && b >= 4 * piece;
+            const bool used = wcol < M && piece < np && b >= 4 * piece;
             const double x = wsrc[used ? b : 0];
             wr[j] = used ? x : 0.0;
         }
@@ -338,6 +344,7 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
     for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int n = 0; n < NG; ++n) acc[g][n] = 0.0;
+    double pj[G] = {};  // projection: pixel 16 g + lane % 16, pieces lane / 16, + 4, ...
     int chunk = 0;
     do {
         const int pc = min(MAXP, np - chunk * MAXP);
@@ -346,13 +353,25 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
         const char* xr = xb + ((lane & 15) * (MAXP + 1) + (lane >> 4)) * 16;
         // slots past the row's pieces hold 0 (their weights are 0, but 0 times
         // an infinity is not)
-        if (lpc >= pc) {
+        auto zero_slots = [&]() {
+            if (lpc >= pc) {
 #pragma unroll
-            for (int i = 0; i < NL; ++i)
-                *(float4*)(xw + i * RPL * (MAXP + 1) * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+                for (int i = 0; i < NL; ++i)
+                    *(float4*)(xw + i * RPL * (MAXP + 1) * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        };
+        if (!PC1) zero_slots();
         // bands that the last piece repeats: 0 as well
         const int rep = lpc + chunk * MAXP == np - 1 ? 4 * np - bands : 0;
+        double mu[4], ev[4];  // of the lane's piece
+        if constexpr (PC1) {
+            const int b0 = lpc + chunk * MAXP < np - 1 ? 4 * (lpc + chunk * MAXP) : bands - 4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                mu[e] = mean[b0 + e];
+                ev[e] = e < rep ? 0.0 : vec[b0 + e];
+            }
+        }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             wave_lds_sync();
@@ -363,6 +382,24 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
                     v[i].y = rep > 1 ? 0.f : v[i].y;
                     v[i].z = rep > 2 ? 0.f : v[i].z;
                 }
+            }
+            if constexpr (PC1) {
+                double* term = buf[wv].term;
+#pragma unroll
+                for (int i = 0; i < NL; ++i) {
+                    double t = ((double)v[i].x - mu[0]) * ev[0];
+                    t = fma((double)v[i].y - mu[1], ev[1], t);
+                    t = fma((double)v[i].z - mu[2], ev[2], t);
+                    t = fma((double)v[i].w - mu[3], ev[3], t);
+                    term[(RPL * i + lrow) * (MAXP + 1) + lpc] = lpc < pc ? t : 0.0;
+                }
+                wave_lds_sync();
+#pragma unroll
+                for (int k = 0; k < MAXP / 4; ++k)
+                    pj[g] += term[(lane & 15) * (MAXP + 1) + 4 * k + (lane >> 4)];
+                asm volatile("" : "+v"(pj[g]));  // summed here: the terms are not kept
+                wave_lds_sync();
+                zero_slots();  // where the terms lay
             }
             if (lpc < pc) {
 #pragma unroll
@@ -402,7 +439,7 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
 
     // sums to one lane per pixel: lane l of group g holds pixel
     // 16 g + 4 ((l / 4) % 4) + l / 16, column 4 n + l % 4
-    double f[N];
+    double f[M];
     double* xr = buf[wv].sum;
     const int op = 4 * ((lane >> 2) & 3) + (lane >> 4), oc = lane & 3;
     wave_lds_sync();
@@ -413,7 +450,7 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
             for (int n = 0; n < NG; ++n) xr[(16 * g + op) * ST + 4 * n + oc] = acc[g][n];
         wave_lds_sync();
 #pragma unroll
-        for (int m = 0; m < N; ++m) f[m] = xr[lane * ST + m];
+        for (int m = 0; m < M; ++m) f[m] = xr[lane * ST + m];
     } else {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -421,7 +458,7 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
             for (int n = 0; n < NG; ++n) xr[op * ST + 4 * n + oc] = acc[g][n];
             wave_lds_sync();
 #pragma unroll
-            for (int m = 0; m < N; ++m) {
+            for (int m = 0; m < M; ++m) {
                 const double y = xr[(lane & 15) * ST + m];
                 f[m] = g == 0 || lane >> 4 == g ? y : f[m];
             }
@@ -431,27 +468,23 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
     const int64_t pix = tile0 + lane;
     const bool in = pix < npix;
     if constexpr (PC1) {
+        wave_lds_sync();
+#pragma unroll
+        for (int g = 0; g < G; ++g) buf[wv].part[g][lane] = pj[g];
+        wave_lds_sync();
+        double p = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p += buf[wv].part[lane >> 4][16 * k + (lane & 15)];
         if (ws) {
-            // (the constant -(band averages . eigenvector) is left out: the
-            // normalisation removes it)
-            const double pj = f[M];
-            if (in) ws[pix] = pj;
+            if (in) ws[pix] = p;
             __syncthreads();  // the buffers are free
-            svm_publish_minmax<SVM_THREADS>(in ? pj : __builtin_inf(), in ? pj : -__builtin_inf(),
+            svm_publish_minmax<SVM_THREADS>(in ? p : __builtin_inf(), in ? p : -__builtin_inf(),
                                             pairs, buf[0].sum);
-        } else {
-            double c = 0.0;
-            for (int b = lane; b < bands; b += 64) c = fma(-mean[b], vec[b], c);
-            for (int m = 1; m < 64; m <<= 1) c += __shfl_xor(c, m);
-            if (in) band[pix] = (float)(f[M] + c);
+        } else if (in) {
+            band[pix] = (float)p;
         }
     }
-    if (in) {
-        double fm[M];
-#pragma unroll
-        for (int m = 0; m < M; ++m) fm[m] = f[m];
-        svm_couple<C>(fm, bias, A, B, out + pix * C);
-    }
+    if (in) svm_couple<C>(f, bias, A, B, out + pix * C);
 }
 
 // Fewer than four bands: one lane per pixel.
