@@ -47,6 +47,7 @@
 
 #include "knnf_device.h"
 #include "knnf_networks.h"
+#include "knnf_select.h"
 
 namespace knnf {
 namespace {
@@ -411,48 +412,20 @@ __device__ __forceinline__ void tighten(TileState<QR, QC>& S, int q, int nb, uin
         return __builtin_popcountll(ballot(db <= t)) + __builtin_popcountll(ballot(dn <= t));
     };
     const int few = (K + WAVE) / 2;  // stop early: room for as many again
-    uint32_t lo = 0, hi = bound;     // fewer than K at lo (or lo = 0), at least K at hi
     int n = 2 * WAVE;
-    // the K-th is rarely below an eighth of the bound
-    if (hi > (3u << 23) && count(hi - (3u << 23)) < K) lo = hi - (3u << 23);
-    while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        const int c = count(mid);
-        if (c < K) {
-            lo = mid;
-        } else {
-            hi = mid;
-            n = c;
-            if (c <= few) break;
-        }
-    }
+    const uint32_t hi = cut_distance(bound, K, few, n, count);
     bool keepb = db <= hi, keepn = dn <= hi;
     if (n > WAVE) {
-        if (hi == 1 && count(0) >= K) {  // (the bisection never looks at 0)
-            hi = 0;
-            keepb = db == 0;
-            keepn = dn == 0;
-        }
         const uint64_t lb = ballot(db < hi), ln = ballot(dn < hi);  // fewer than K
         const uint64_t eb = ballot(db == hi), en = ballot(dn == hi);
         n = __builtin_popcountll(lb | eb) + __builtin_popcountll(ln | en);
         if (n > WAVE) {
-            int il = -1, ih = 0x7fffffff;  // fewer than K up to il, at least K up to ih
-            for (;;) {
-                const int mid = il + (int)((uint32_t)(ih - il) / 2);
-                const uint64_t mb = lb | (eb & ballot((int)ib <= mid));
-                const uint64_t mn = ln | (en & ballot((int)idx <= mid));
-                const int c = __builtin_popcountll(mb) + __builtin_popcountll(mn);
-                if (c < K) {
-                    il = mid;
-                } else {
-                    ih = mid;
-                    n = c;
-                    if (c <= few) break;  // reached: one index at a time adds one candidate
-                }
-            }
-            keepb = db < hi || (db == hi && (int)ib <= ih);
-            keepn = dn < hi || (dn == hi && (int)idx <= ih);
+            const uint32_t ih = cut_index(K, few, n, [&](uint32_t i) {
+                return __builtin_popcountll(lb | (eb & ballot(ib < i))) +
+                       __builtin_popcountll(ln | (en & ballot(idx < i)));
+            });
+            keepb = db < hi || (db == hi && ib < ih);
+            keepn = dn < hi || (dn == hi && idx < ih);
         }
     }
     const uint64_t mb = ballot(keepb), mn = ballot(keepn);
