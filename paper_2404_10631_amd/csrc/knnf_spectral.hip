@@ -314,10 +314,8 @@ __device__ __forceinline__ bool select_queries(const FrameDesc& f, const uint64_
         for (int u = 0; u < 8; ++u) {
             if (mine && rk[u] < K) {
                 list[j][rk[u]] = (uint16_t)((uint32_t)y[u] - first);
-                if (f.out_nbr) {
-                    f.out_nbr[(size_t)q * K + rk[u]] = (int32_t)(uint32_t)y[u];
-                    f.out_dist[(size_t)q * K + rk[u]] = __uint_as_float((uint32_t)(y[u] >> 32));
-                }
+                if (f.out_nbr) f.out_nbr[(size_t)q * K + rk[u]] = (int32_t)(uint32_t)y[u];
+                if (f.out_dist) f.out_dist[(size_t)q * K + rk[u]] = __uint_as_float((uint32_t)(y[u] >> 32));
             }
         }
         if (t == (L >> 3)) done = (uint32_t)(okb >> (8 * (L & 7))) & 0xffu;
@@ -481,10 +479,8 @@ spectral_filter_kernel(FrameDesc f, int T) {
         };
         auto emit = [&](uint64_t key, uint32_t d) __attribute__((always_inline)) {
             const uint32_t idx = key_index(key);
-            if (f.out_nbr) {
-                f.out_nbr[(size_t)q * K + k] = (int32_t)idx;
-                f.out_dist[(size_t)q * K + k] = __uint_as_float(d);
-            }
+            if (f.out_nbr) f.out_nbr[(size_t)q * K + k] = (int32_t)idx;
+            if (f.out_dist) f.out_dist[(size_t)q * K + k] = __uint_as_float(d);
 #pragma unroll
             for (int u = 0; u < SP_RING; ++u) ring[u] = u == nring ? idx : ring[u];
             if (++nring == SP_RING) {
