@@ -239,7 +239,7 @@ knnf::FrameDesc to_desc_impl(const knnf_frame& f) {
     d.W = f.W;
     d.C = f.C;
     d.K = f.K;
-    d.R = f.R;
+    d.R = std::min(f.R, f.H);  // all rows: the kernels compute row + R in 32 bits
     d.lambda = f.lambda;
     d.stats = nullptr;
     return d;

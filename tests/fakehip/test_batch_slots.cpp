@@ -219,6 +219,30 @@ bool test_server_closed_after_its_context() {
     return true;
 }
 
+// Windows of more rows than the frame has, up to the largest R, are the whole frame.
+bool test_whole_frame_windows() {
+    knnf_ctx* ctx = nullptr;
+    CHECK(knnf_create(&ctx, 0) == KNNF_OK);
+    for (int R : {8, 100000, 0x7fffffff}) {
+        Batch b(3, 95);
+        for (size_t k = 0; k < b.frames.size(); ++k) {
+            Frame& f = *b.frames[k];
+            std::vector<float> d(f.pc1.size() * f.K);
+            std::vector<int32_t> n(d.size());
+            knn_oracle_filter(f.H, f.W, f.C, f.K, f.H, 0.01f, f.pc1.data(), f.prob.data(), f.ref.data(),
+                              f.refc.data(), n.data(), d.data(), 1);
+            b.c[k].R = R;
+        }
+        CHECK(b.run(ctx, nullptr) == KNNF_OK);
+        CHECK(b.right());
+        b.clear();
+        for (knnf_frame& c : b.c) CHECK(knnf_filter(ctx, &c, nullptr, nullptr) == KNNF_OK);
+        CHECK(b.right());
+    }
+    CHECK(knnf_destroy(ctx) == KNNF_OK);
+    return true;
+}
+
 }  // namespace
 
 int main() {
@@ -228,6 +252,7 @@ int main() {
         {"per_thread_streams", test_per_thread_streams},
         {"captured_batches", test_captured_batches},
         {"server_closed_after_its_context", test_server_closed_after_its_context},
+        {"whole_frame_windows", test_whole_frame_windows},
     };
     int failed = 0;
     for (const auto& t : tests) {

@@ -6,7 +6,7 @@ launch that used it, whatever has become of that launch's stream: destroyed whil
 the launch still ran, with another stream at its handle; the per-thread stream of
 another thread, which has the caller's handle; a stream whose work a capture
 recorded, to be replayed at any time.  And closing a server leaves its context, which
-may be gone, alone.
+may be gone, alone; and a window's rows stay in range for every R.
 """
 import os
 import subprocess
@@ -39,4 +39,5 @@ def test_tables_are_reused_after_their_launch(oracle_obj, name, flags, env):  # 
     run = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=dict(os.environ, **env))
     assert run.returncode == 0, (run.stdout + run.stderr)[-4000:]
     assert run.stdout.split() == ["ok", "destroyed_stream", "ok", "per_thread_streams", "ok",
-                                  "captured_batches", "ok", "server_closed_after_its_context"]
+                                  "captured_batches", "ok", "server_closed_after_its_context", "ok",
+                                  "whole_frame_windows"]
