@@ -24,7 +24,8 @@
 // TB/s (raw projection of 380 x 480 x 128: 18.2 and 17.2 us per call, about
 // 2.3 us of each the launch).  Band counts that are no multiple of 4 and
 // unaligned cubes take the same path (500 x 500 x 33: 13.0 us with the
-// normalisation, 49.6 us with one thread per pixel).
+// normalisation, 49.6 us with one thread per pixel); PC1_FEW_BANDS and fewer, and more
+// than 256, have a thread per pixel.
 // Normalisation needs min and max over the frame: each projection block stores
 // its (min, max) pair, and every block of the second launch reduces those pairs
 // before rescaling its pixels (no atomics on one address, no device-wide fence).
@@ -49,6 +50,14 @@ constexpr int PC1_UNROLL = 4;  // loads of a wavefront in flight together (8: no
 // (1000 x 1000 x 100: 88.8 us, 91.2 with at most 1,024 blocks).
 constexpr int PC1_MAX_BLOCKS = 4096;
 constexpr int64_t PC1_BLOCK_BYTES = 32 * 1024;
+// One thread per pixel for few bands, where a wavefront's rows share cache lines and no
+// sum crosses lanes (700 x 800: 4 bands 12.1 against 23.3 us with segments, 9 bands 13.3 /
+// 18.8, 10 bands 15.7 / 17.9, 11 bands 16.9 / 16.7; 1000 x 1500 x 10: 32.6 / 30.8), and
+// beyond the 256 bands of a segment of 64 lanes.  There each thread's row is a stream of
+// its own, and more than four blocks of them per CU evict each other's lines (500 x 800 x
+// 300: 860 us with 1,024 blocks, 2,024 with 4,096).
+constexpr int PC1_FEW_BANDS = 10;
+constexpr int PC1_PIXEL_BLOCKS = 1024;
 
 // Value of the partner lane for one butterfly step (64-bit through two
 // 32-bit lane moves): DPP quad_perm xor 1 / xor 2, row_half_mirror (pairs the
@@ -213,7 +222,7 @@ pc1_project_vec4(const float* __restrict__ cube, int64_t npix, int bands,
     if (ws) publish_minmax(lo, hi, pairs);
 }
 
-// Projection for fewer than 4 or more than 256 bands: one thread per pixel.
+// Projection for few or for more than 256 bands: one thread per pixel.
 __global__ void __launch_bounds__(PC1_THREADS)
 pc1_project_scalar(const float* __restrict__ cube, int64_t npix, int bands,
                    const double* __restrict__ mean, const double* __restrict__ vec,
@@ -327,7 +336,7 @@ int launch_pc1(const float* cube, int64_t npix, int bands, const double* mean, c
                float* out, double* ws, double* pairs, int num_cu, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     int blocks;
-    if (bands >= 4 && bands <= 256) {
+    if (bands > PC1_FEW_BANDS && bands <= 256) {
         const int S = bands <= 32 ? 8 : bands <= 64 ? 16 : bands <= 128 ? 32 : 64;
         // a block's step: PC1_UNROLL loads of each wavefront
         const int64_t step = (int64_t)(PC1_THREADS / 64) * (64 / S) * PC1_UNROLL;
@@ -346,7 +355,7 @@ int launch_pc1(const float* cube, int64_t npix, int bands, const double* mean, c
         else launch(pc1_project_vec4<64>);
     } else {
         const int64_t want = (npix + PC1_THREADS - 1) / PC1_THREADS;
-        blocks = (int)(want < PC1_MAX_BLOCKS ? want : PC1_MAX_BLOCKS);
+        blocks = (int)(want < PC1_PIXEL_BLOCKS ? want : PC1_PIXEL_BLOCKS);
         hipLaunchKernelGGL(pc1_project_scalar, dim3(blocks), dim3(PC1_THREADS), 0, st, cube, npix,
                            bands, mean, vec, out, ws, pairs);
     }
