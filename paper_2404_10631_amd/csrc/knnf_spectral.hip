@@ -19,10 +19,11 @@
 //      XOR-swizzled positions, which spreads a wavefront's stores of 16
 //      consecutive keys per lane over the banks;
 //   2. a binary search per query pixel of the two rows (one a lane) finds where
-//      I_q falls in the sorted band.  The nearest 64 candidates of a query are then
-//      merged from the 64 keys on either side by eight lanes (select_queries);
-//   3. queries that this leaves (equal distances across the end of those 64, K
-//      close to 64) walk the band, one a lane: two cursors go outward (values
+//      I_q falls in the sorted band.  From some 18 neighbours on (see
+//      launch_spectral_frame) the nearest 64 candidates of a query are then merged from
+//      the 64 keys on either side by eight lanes (select_queries);
+//   3. the other queries (few neighbours, K close to 64, equal distances across the end
+//      of those 64) walk the band, one a lane: two cursors go outward (values
 //      below and above I_q), skipping the band row that lies outside the
 //      query's own window, taking at each step the whole run of candidates
 //      whose distance equals the smaller of the two cursors' distances (a
@@ -188,7 +189,9 @@ __device__ __forceinline__ uint32_t lane_get(uint32_t v, int src) {
 // dropped by rank afterwards, so a query is finished if K of the 64 remain and
 // the K-th lies strictly before the last one kept (dropped candidates are not
 // nearer); else (K close to 64, many equal values, distances at +inf) it is left to
-// the walk.  Per eight queries about 500 vector instructions and two trips to
+// the walk, and where more than half of eight are, so are the wavefront's later ones:
+// the walk takes nearly as long for one of its lanes as for 64.
+// Per eight queries about 500 vector instructions and two trips to
 // LDS, where the walk took K dependent steps of some 60 in each lane.
 //
 // Lane p of a segment holds the elements 8 l .. 8 l + 7 of the merged order, with
@@ -310,16 +313,21 @@ __device__ __forceinline__ bool select_queries(const FrameDesc& f, const uint64_
         ok0 = (t & 1) ? ok0 : okb;
         ok1 = (t & 1) ? okb : 0;
         const bool mine = (uint32_t)(okb >> (8 * seg)) & 0xffu;
+        // most of the round's queries are for the walk: the wavefront's later ones as well
+        // (one lane of a finished query has its bit set, eight of a live one)
+        const bool left = 16 * __builtin_popcountll(okb) < __builtin_popcountll(ballot(live));
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             if (mine && rk[u] < K) {
                 list[j][rk[u]] = (uint16_t)((uint32_t)y[u] - first);
-                if (f.out_nbr) f.out_nbr[(size_t)q * K + rk[u]] = (int32_t)(uint32_t)y[u];
-                if (f.out_dist) f.out_dist[(size_t)q * K + rk[u]] = __uint_as_float((uint32_t)(y[u] >> 32));
+                if (f.out_nbr) {  // and out_dist (see launch_spectral_frame)
+                    f.out_nbr[(size_t)q * K + rk[u]] = (int32_t)(uint32_t)y[u];
+                    f.out_dist[(size_t)q * K + rk[u]] = __uint_as_float((uint32_t)(y[u] >> 32));
+                }
             }
         }
         if (t == (L >> 3)) done = (uint32_t)(okb >> (8 * (L & 7))) & 0xffu;
-        const bool more = t < 7 && q0 + 8 * (t + 1) < 2 * W;
+        const bool more = !left && t < 7 && q0 + 8 * (t + 1) < 2 * W;
         if (!(t & 1) && more) continue;
 
         // ---- Eq. 2 of the last two rounds: one lane per (query, class)
@@ -380,14 +388,17 @@ __device__ __forceinline__ bool select_queries(const FrameDesc& f, const uint64_
             f.out_class[(size_t)(r0 + row) * W + (qq - row * W)] = best;
         }
         wave_sync();
+        if (left) break;
     }
     return done;
 }
 
+// SELECT: queries are tried by select_queries first (else every query walks).
+template <bool SELECT>
 __global__ void __launch_bounds__(SP_THREADS)
 spectral_filter_kernel(FrameDesc f, int T) {
     __shared__ uint64_t keys[SP_MAX];
-    __shared__ __attribute__((aligned(16))) uint16_t lists[SP_THREADS / 64][SP_GROUP][SP_SIDE];
+    __shared__ __attribute__((aligned(16))) uint16_t lists[SELECT ? SP_THREADS / 64 : 1][SP_GROUP][SP_SIDE];
     // two query rows per workgroup share one band: the rows of both windows
     const int r0 = 2 * (int)blockIdx.x;
     const int t = threadIdx.x;
@@ -433,9 +444,18 @@ spectral_filter_kernel(FrameDesc f, int T) {
             if (keys[sw(mid)] < probe) a0 = mid + 1;
             else a1 = mid;
         }
-        const bool done = select_queries(f, keys, n, first, lo, r0, qi - (t & 63), x, a0, lists[t >> 6]);
+        bool done = false;
+        if constexpr (SELECT) {
+            // A query with equal values across the selection's end on the right alone is
+            // for the walk, and with it the wavefront: values of a few levels have many
+            // such (256 levels: 191 us, 204 with every query tried; 16: 142 and 180).
+            const bool equal = live && a0 + SP_SIDE - 1 < n &&
+                               (uint32_t)(keys[sw(a0 + SP_SIDE - 1)] >> 32) == sortable(x);
+            if (!ballot(equal))
+                done = select_queries(f, keys, n, first, lo, r0, qi - (t & 63), x, a0, lists[t >> 6]);
+        }
         if (done || !live) continue;
-        // the walk, for what the selection leaves
+        // the walk, for few neighbours and for what the selection leaves
         int L = a0 - 1, Rc = a0;  // next candidates below and above
         float s[SP_MAX_C];
 #pragma unroll
@@ -622,8 +642,29 @@ int launch_spectral_frame(const FrameDesc& f, void* stream) {
     const int64_t n = spectral_band_rows(f) * f.W;
     int T = 1;
     while ((int64_t)T * SP_THREADS < n) T <<= 1;
-    hipLaunchKernelGGL(spectral_filter_kernel, dim3((uint32_t)((f.H + 1) / 2)), dim3(SP_THREADS), 0,
-                       (hipStream_t)stream, f, T);
+    // The selection takes the same time for every K; the walk takes a step per neighbour,
+    // and per candidate in the band row outside a query's window (one of `rows`).  So the
+    // selection is used from 18 steps on (380 x 480, +-14 rows: K = 8 115 us, the walk 90;
+    // K = 18 117 and 116; K = 24 117 and 134; R = 0, K = 16 70 and 80), from fewer where a
+    // step does more: class sums beyond four (C = 7: K = 8 119 and 119), neighbour outputs
+    // (K = 8 119 and 95, K = 16 121 and 145).  And up to a K that nearly every query's 64
+    // nearest hold when those in the other row are gone; one that is left in a wavefront
+    // costs it the walk (K = 44 122 and 180, K = 52 188 and 199, K = 56 250 and 210; R = 1,
+    // K = 40 184 and 143).
+    const int64_t rows = 2 * (int64_t)f.R + 2;
+    const bool drops = f.R < f.H - 1;
+    const int least = f.C > 4 ? 10 : f.out_nbr || f.out_dist ? 13 : 18;
+    const int64_t most = drops ? 64 - 64 / rows - 9 : 62;
+    // (One neighbour output without the other: the walk.  Both pointers' addresses in the
+    // selection spilled registers, 2 % of every call.)
+    const bool paired = !f.out_nbr == !f.out_dist;
+    const bool select = paired && f.K <= most && (drops ? f.K * rows >= least * (rows - 1) : f.K >= least);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)((f.H + 1) / 2)), dim3(SP_THREADS), 0, (hipStream_t)stream,
+                           f, T);
+    };
+    if (select) launch(spectral_filter_kernel<true>);
+    else launch(spectral_filter_kernel<false>);
     return (int)hipGetLastError();
 }
 
