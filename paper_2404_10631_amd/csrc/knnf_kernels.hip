@@ -413,9 +413,14 @@ __device__ __forceinline__ void tighten(TileState<QR, QC>& S, int q, int nb, uin
     };
     const int few = (K + WAVE) / 2;  // stop early: room for as many again
     int n = 2 * WAVE;
-    const uint32_t hi = cut_distance(bound, K, few, n, count);
+    uint32_t hi = cut_distance(bound, K, few, n, count);
     bool keepb = db <= hi, keepn = dn <= hi;
     if (n > WAVE) {
+        if (hi == 1 && count(0) >= K) {  // (the bisection never looks at 0)
+            hi = 0;
+            keepb = db == 0;
+            keepn = dn == 0;
+        }
         const uint64_t lb = ballot(db < hi), ln = ballot(dn < hi);  // fewer than K
         const uint64_t eb = ballot(db == hi), en = ballot(dn == hi);
         n = __builtin_popcountll(lb | eb) + __builtin_popcountll(ln | en);

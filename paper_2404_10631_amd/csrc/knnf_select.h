@@ -9,8 +9,8 @@
 namespace knnf {
 
 // A distance bound t <= hi with at least K candidates at or below it, given that hi
-// has: the first one found with at most `few`, else the smallest one there is.  n: its
-// count (left alone where hi itself is returned, uncounted).
+// has: the first one found with at most `few`, else the smallest one above 0 (which is
+// not counted).  n: its count (left alone where hi itself is returned, uncounted).
 template <class Count>
 __device__ __forceinline__ uint32_t cut_distance(uint32_t hi, int K, int few, int& n, Count count) {
     uint32_t lo = 0;  // fewer than K at lo (or lo = 0, not counted)
@@ -24,14 +24,7 @@ __device__ __forceinline__ uint32_t cut_distance(uint32_t hi, int K, int few, in
         } else {
             hi = mid;
             n = c;
-            if (c <= few) return hi;
-        }
-    }
-    if (hi == 1) {
-        const int c = count(0u);
-        if (c >= K) {
-            hi = 0;
-            n = c;
+            if (c <= few) break;
         }
     }
     return hi;

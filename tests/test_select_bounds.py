@@ -28,10 +28,11 @@ static int calls;
 static int cut(const std::vector<C>& v, uint32_t bound, int K, int few, int room) {
     auto count = [&](uint32_t t) { ++calls; int c = 0; for (auto& x : v) c += x.d <= t; return c; };
     int n = 2 * room;
-    const uint32_t hi = cut_distance(bound, K, few, n, count);
+    uint32_t hi = cut_distance(bound, K, few, n, count);
     std::vector<C> keep;
     uint32_t ih = 0xffffffffu;
     if (n > room) {
+        if (hi == 1 && count(0u) >= K) hi = 0;
         n = 0;
         for (auto& x : v) n += x.d <= hi;
         if (n > room)
