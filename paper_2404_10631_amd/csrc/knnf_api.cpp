@@ -241,6 +241,7 @@ knnf::FrameDesc to_desc_impl(const knnf_frame& f) {
     d.K = f.K;
     d.R = std::min(f.R, f.H);  // all rows: the kernels compute row + R in 32 bits
     d.lambda = f.lambda;
+    d.wide = knnf::wide_bound(f.H, f.W, d.R, f.lambda);
     d.stats = nullptr;
     return d;
 }

@@ -5,6 +5,10 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
 namespace knnf {
 
 // One frame as the kernels see it (device pointers, sizes, parameters).
@@ -17,8 +21,27 @@ struct FrameDesc {
     float* out_dist;      // [H][W][K] or null
     int32_t H, W, C, K, R;
     float lambda;
+    uint32_t wide;        // distance bits: tiles with a larger bound scan the whole window (wide_bound)
     unsigned long long* stats;  // [0] pairs evaluated, [1] tiles; null: not counted
 };
+
+// Distance bits of a bound so wide that the whole-window scan is the faster one for a
+// tile of the pruned search.  With radius rho (in pixels) a bound leaves min(x, rows) x
+// min(x, W) candidates of the window, x = 2 rho; the whole-window scan takes about a third
+// of the patches' time for each, in chunks of 64 columns, but its bounds tighten as late as
+// theirs: 0.45 of the window (380 x 480, lambda 0.0003, K = 48: 575 us, with 0.6 598, with
+// a third 545; lambda 0.001, K = 16: 128, 126 and 137, 122 without).  Windows of fewer than
+// 4,096 candidates are done with before it matters.
+inline uint32_t wide_bound(int H, int W, int R, float lambda) {
+    const double rows = std::min(2.0 * R + 1.0, (double)H), chunks = (W + 63) / 64 * 64.0;
+    const double area = rows * chunks * 0.45, m = std::min(rows, (double)W);
+    if (area >= rows * W || rows * W < 4096) return 0x7f800000u;  // never
+    const double x = area <= m * m ? std::sqrt(area) : area / m;
+    const float t = (float)(0.25 * x * x * (double)lambda * (double)lambda);
+    uint32_t bits;
+    std::memcpy(&bits, &t, sizeof bits);
+    return bits;
+}
 
 // Kernel launch configuration chosen by the host (see knnf_plan).
 struct LaunchCfg {
@@ -56,7 +79,7 @@ int launch_check_items(const FrameDesc* d_frames, uint32_t n, uint32_t max_words
 // len[k] words from w[src[k]] to d_base[dst[k]].  Writing a small table this
 // way needs no host-to-device copy, which could hold up the launching thread
 // for milliseconds.
-constexpr int kTableWords = 880;
+constexpr int kTableWords = 952;  // 39 items
 struct TableWords {
     uint32_t w[kTableWords];
     uint32_t src[3], dst[3], len[3];

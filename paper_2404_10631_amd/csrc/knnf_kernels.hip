@@ -29,7 +29,8 @@
 //     of the groups' ceil(K/2)-th keys.
 //   * pass B (collect): candidates with d <= d_K are appended to a per-query
 //     LDS buffer with ballot + mbcnt; a full buffer is cut down by a tighter
-//     bound.  Two scans:
+//     bound, and a tile that keeps filling them is done over in parts with larger
+//     ones (crowded_tile).  Two scans:
 //       - pruned (default): patches of 64 candidates, as high as the block of
 //         rows, swept over the rows and columns whose spatial lower bound is
 //         within some query's bound (bit-identical: every term of Eq. 1 is
@@ -41,6 +42,7 @@
 //   * The tail is fused: gather the K neighbours' probabilities (L2-resident),
 //     sum in key order, divide, argmax, and write the outputs.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -160,7 +162,7 @@ __device__ __forceinline__ uint64_t sort64(uint64_t key, int L) {
 }
 
 // ---- segmented networks: the Q queries of a tile together.  A segment of P
-// lanes (4 or 8) holds one query's P * E elements, E registers a lane; the
+// lanes (4, 8 or 16) holds one query's P * E elements, E registers a lane; the
 // sorted order is element lp * E + r in register r of the segment's lane lp.
 //
 // Each lane sorts its E elements, then runs of E, 2E, 4E elements are merged
@@ -194,18 +196,26 @@ __device__ __forceinline__ uint64_t sort64(uint64_t key, int L) {
 // Ascending sort of each segment of P lanes.
 template <int P, int E>
 __device__ __forceinline__ void seg_sort(uint32_t (&x)[E], int lp) {
-    static_assert(P == 4 || P == 8, "segment width");
+    static_assert(P == 4 || P == 8 || P == 16, "segment width");
     const uint32_t k0 = (lp & 1) ? ~0u : 0u, k1 = (lp & 2) ? ~0u : 0u;
     lane_sort<E>(x);
     cross<DPP_XOR1, true>(x, k0);  // runs of 2E
     lane_merge<E>(x);
     cross<DPP_XOR3, true>(x, k1);  // runs of 4E
     cross<DPP_XOR1, false>(x, k0);
-    if constexpr (P == 8) {
+    if constexpr (P >= 8) {
+        const uint32_t k2 = (lp & 4) ? ~0u : 0u;
         lane_merge<E>(x);
-        cross<DPP_XOR7, true>(x, (lp & 4) ? ~0u : 0u);  // runs of 8E
+        cross<DPP_XOR7, true>(x, k2);  // runs of 8E
         cross<DPP_XOR2, false>(x, k1);
         cross<DPP_XOR1, false>(x, k0);
+        if constexpr (P == 16) {
+            lane_merge<E>(x);
+            cross<DPP_XOR15, true>(x, (lp & 8) ? ~0u : 0u);  // runs of 16E
+            cross_xor4(x, k2);
+            cross<DPP_XOR2, false>(x, k1);
+            cross<DPP_XOR1, false>(x, k0);
+        }
     }
     lane_merge<E>(x);
 }
@@ -325,17 +335,33 @@ __device__ __forceinline__ uint32_t pack_hi(uint32_t lo, uint32_t hi) {
 // merge), and no two empty slots alike once the slot bits are set aside.
 constexpr uint32_t PAD = 0x7f7f0000u;
 constexpr uint32_t BIG = PAD - 1;
+
+// When a tile counts as crowded (see crowded_tile).  A cut of a full buffer costs about 400
+// cycles and frees a part of the 64 - K slots beyond the K that stay, so the larger K, the
+// fewer cuts are worth making: pruned scan, 64 - K cuts for eight queries (380 x 480, K =
+// 40 and 64, lambda 0.01: 56.4 and 144 us; 16 cuts for every K 56.4 and 160, 48 cuts 57 and
+// 191; without crowded tiles 56.2 and 175), and more than eight steps of the block to go (K =
+// 60, lambda 1: 86 us, 107 wherever it stands).  The whole-window scan meets the nearest
+// candidates first and crowds only for K near 64: 48 cuts there (K = 64, lambda 0.001: 945
+// us; 80 cuts 1,109, without 1,414; lambda 0.01 506, 514, 472), else 32 a query.
+__device__ __forceinline__ int crowded_cuts(int Q, int K) { return max(1, (64 - K) * Q / 8); }
+__device__ __forceinline__ int crowded_cuts_all(int Q, int K) { return Q * (K < 58 || Q > 8 ? 32 : 6); }
+constexpr int CROWDED_STEPS = 8;
+// Candidates that a cut leaves where it stops early: the middle between K and 64; with 128
+// slots, which fill up slowly, a quarter of the way (uniform noise, K = 52: 373 us, 390).
+template <int SLOTS>
+__device__ __forceinline__ int cut_target(int K) { return SLOTS > WAVE ? (3 * K + SLOTS) / 4 : (K + SLOTS) / 2; }
 constexpr int ROWS = 32;  // neighbour rows staged at a time in Eq. 2 (four classes)
 
 // Per-wavefront LDS state of one tile of QR x QC query pixels.
 template <int E>
 __device__ __forceinline__ int row_at(int r) { return E >= 8 ? r + (r >> 3) : r; }
 
-template <int QR, int QC>
+template <int QR, int QC, int NSLOT = WAVE>
 struct alignas(16) TileState {
-    static constexpr int Q = QR * QC;
+    static constexpr int Q = QR * QC, SLOTS = NSLOT;
     union {
-        uint32_t pend[Q][2][WAVE]; // candidates that passed the bound, unsorted: distance
+        uint32_t pend[Q][2][SLOTS]; // candidates that passed the bound, unsorted: distance
                                  // bits, linear indices
         // four classes: the neighbours' probability rows, in order; where a lane
         // stores eight, one row is skipped after them (row_at: without the gap half
@@ -358,12 +384,12 @@ struct alignas(16) TileState {
 
 // The exhaustive scan also keeps a table of row terms; the pruned scan
 // computes them per lane.
-template <int QR, int QC, bool PRUNE>
-struct alignas(16) TileLds : TileState<QR, QC> {
+template <int QR, int QC, bool PRUNE, int NSLOT = WAVE>
+struct alignas(16) TileLds : TileState<QR, QC, NSLOT> {
     float a2t[A2ROWS + A2PAD][QR];  // fl32(a*a) for a block of window rows (NaN: inactive)
 };
-template <int QR, int QC>
-struct alignas(16) TileLds<QR, QC, true> : TileState<QR, QC> {};
+template <int QR, int QC, int NSLOT>
+struct alignas(16) TileLds<QR, QC, true, NSLOT> : TileState<QR, QC, NSLOT> {};
 
 // Coordinate feature fr(x) = fl32(lambda * (float)x).
 __device__ __forceinline__ float feat(float lam, int x) { return lam * (float)x; }
@@ -371,8 +397,8 @@ __device__ __forceinline__ float feat(float lam, int x) { return lam * (float)x;
 // Put query q's cnt candidates in exact (d, idx) order and write its neighbour
 // outputs, for bounds beyond the packed keys' range.  The buffer then holds the
 // indices in order under distance parts that only number them.
-template <int QR, int QC>
-__device__ __forceinline__ void order_query(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
+template <int QR, int QC, int NSLOT>
+__device__ __forceinline__ void order_query(TileState<QR, QC, NSLOT>& S, const FrameDesc& f, int r0, int c0,
                                             int q, int cnt) {
     const int L = lane_id_here();
     const int W = f.W, K = f.K;
@@ -394,54 +420,75 @@ __device__ __forceinline__ void order_query(TileState<QR, QC>& S, const FrameDes
     wave_sync();
 }
 
-// Make room in query q's full buffer: nb pending candidates and this step's (dn:
-// each lane's distance bits, all ones for none; idx its linear index), more than
-// 64 of them within the bound.  Any distance t with at least K candidates at or
-// below it bounds the K-th key, so a t that leaves at most 64 of them is found
-// by bisection (its counts are ballots), the buffer keeps those, and the bound
-// becomes t.  Where equal distances leave no such t, the smallest t with K
+// Cut query q's buffer down to at most `room` candidates: nb pending ones and this
+// step's (dn: each lane's distance bits, all ones for none; idx its linear index), more
+// than room of them within the bound.  Any distance t with at least K candidates at or
+// below it bounds the K-th key, so a t that leaves few enough of them is found by
+// bisection (its counts are ballots; it stops early at `few`), the buffer keeps those,
+// and the bound becomes t.  Where equal distances leave no such t, the smallest t with K
 // candidates is taken, and of those at t the ones up to an index that is found
 // the same way: ties go by the index.  About 100 instructions, 200 with ties.
-template <int QR, int QC>
-__device__ __forceinline__ void tighten(TileState<QR, QC>& S, int q, int nb, uint32_t dn, uint32_t idx,
-                                        uint32_t bound, int K, uint32_t own) {
+template <int QR, int QC, int NSLOT>
+__device__ __forceinline__ void tighten(TileState<QR, QC, NSLOT>& S, int q, int nb, uint32_t dn, uint32_t idx,
+                                        uint32_t bound, int K, uint32_t own, int room, int few) {
+    constexpr int B = NSLOT / WAVE;  // a lane's slots
     const int L = lane_id_here();
-    const uint32_t kb = S.pend[q][0][L], ib = S.pend[q][1][L];
-    const uint32_t db = L < nb ? kb : ~0u;
-    auto count = [&](uint32_t t) {
-        return __builtin_popcountll(ballot(db <= t)) + __builtin_popcountll(ballot(dn <= t));
-    };
-    const int few = (K + WAVE) / 2;  // stop early: room for as many again
-    int n = 2 * WAVE;
-    uint32_t hi = cut_distance(bound, K, few, n, count);
-    bool keepb = db <= hi, keepn = dn <= hi;
-    if (n > WAVE) {
-        if (hi == 1 && count(0) >= K) {  // (the bisection never looks at 0)
-            hi = 0;
-            keepb = db == 0;
-            keepn = dn == 0;
-        }
-        const uint64_t lb = ballot(db < hi), ln = ballot(dn < hi);  // fewer than K
-        const uint64_t eb = ballot(db == hi), en = ballot(dn == hi);
-        n = __builtin_popcountll(lb | eb) + __builtin_popcountll(ln | en);
-        if (n > WAVE) {
-            const uint32_t ih = cut_index(K, few, n, [&](uint32_t i) {
-                return __builtin_popcountll(lb | (eb & ballot(ib < i))) +
-                       __builtin_popcountll(ln | (en & ballot(idx < i)));
-            });
-            keepb = db < hi || (db == hi && ib < ih);
-            keepn = dn < hi || (dn == hi && idx < ih);
-        }
+    uint32_t kb[B], ib[B], db[B];
+#pragma unroll
+    for (int v = 0; v < B; ++v) {
+        kb[v] = S.pend[q][0][WAVE * v + L];
+        ib[v] = S.pend[q][1][WAVE * v + L];
+        db[v] = WAVE * v + L < nb ? kb[v] : ~0u;
     }
-    const uint64_t mb = ballot(keepb), mn = ballot(keepn);
+    auto count = [&](uint32_t t) {
+        int n = __builtin_popcountll(ballot(dn <= t));
+#pragma unroll
+        for (int v = 0; v < B; ++v) n += __builtin_popcountll(ballot(db[v] <= t));
+        return n;
+    };
+    int n = NSLOT + WAVE;
+    uint32_t hi = cut_distance(bound, K, few, n, count), ih = 0;  // ih: of those at hi, indices below it
+    if (n > room) {
+        if (hi == 1 && count(0) >= K) hi = 0;  // (the bisection never looks at 0)
+        ih = 0x80000000u;
+        n = count(hi);
+        if (n > room) {
+            const uint64_t ln = ballot(dn < hi), en = ballot(dn == hi);
+            uint64_t lb[B], eb[B];
+#pragma unroll
+            for (int v = 0; v < B; ++v) {
+                lb[v] = ballot(db[v] < hi);  // fewer than K, all in all
+                eb[v] = ballot(db[v] == hi);
+            }
+            ih = cut_index(K, few, n, [&](uint32_t i) {
+                int c = __builtin_popcountll(ln | (en & ballot(idx < i)));
+#pragma unroll
+                for (int v = 0; v < B; ++v) c += __builtin_popcountll(lb[v] | (eb[v] & ballot(ib[v] < i)));
+                return c;
+            });
+        }
+    } else {
+        ih = 0x80000000u;
+    }
     wave_sync();
     auto put = [&](int slot, uint32_t dist, uint32_t id) {
         S.pend[q][0][slot] = dist;
         S.pend[q][1][slot] = id;
     };
-    if (keepb) put(mbcnt(mb), kb, ib);
-    if (keepn) put(__builtin_popcountll(mb) + mbcnt(mn), dn, idx);
-    if (L >= n) put(L, PAD + 64u * (uint32_t)L, own);
+    int at = 0;
+#pragma unroll
+    for (int v = 0; v < B; ++v) {
+        const bool keep = db[v] < hi || (db[v] == hi && ib[v] < ih);
+        const uint64_t m = ballot(keep);
+        if (keep) put(at + mbcnt(m), kb[v], ib[v]);
+        at += __builtin_popcountll(m);
+    }
+    const bool keep = dn < hi || (dn == hi && idx < ih);
+    const uint64_t m = ballot(keep);
+    if (keep) put(at + mbcnt(m), dn, idx);
+#pragma unroll
+    for (int v = 0; v < B; ++v)
+        if (WAVE * v + L >= n) put(WAVE * v + L, PAD + 64u * (uint32_t)(WAVE * v + L), own);
     if (L == 0) {
         S.cnt[q] = n;
         S.tauhi[q] = hi;
@@ -449,11 +496,12 @@ __device__ __forceinline__ void tighten(TileState<QR, QC>& S, int q, int nb, uin
     wave_sync();
 }
 
-// Buffer counts as the pruned scan holds them: 4 * (n + 63), the byte offset of
-// the next slot plus a bias for which a count beyond 64 sets bit 9.
-constexpr int PEND_FULL = 512;
-__device__ __forceinline__ int pend_code(int n) { return 4 * (n + WAVE - 1); }
-__device__ __forceinline__ int pend_count(int code) { return code / 4 - (WAVE - 1); }
+// Buffer counts as the pruned scan holds them: 4 * (n + SLOTS - 1), the byte offset of
+// the next slot plus a bias for which a count beyond SLOTS sets the bit 8 * SLOTS.
+template <int SLOTS>
+__device__ __forceinline__ int pend_code(int n) { return 4 * (n + SLOTS - 1); }
+template <int SLOTS>
+__device__ __forceinline__ int pend_count(int code) { return code / 4 - (SLOTS - 1); }
 
 // Append to the buffers of queries q .. q + 3 the lanes of masks m (distances d,
 // linear index idx); cnt: the queries' counts before, slot0: the buffers' LDS
@@ -462,8 +510,10 @@ __device__ __forceinline__ int pend_count(int code) { return code / 4 - (WAVE - 
 // two are needed, with nearly every query storing in nearly every step.  The
 // caller's branch on the counts orders the compares before the masks' first
 // vector read; all 64 lanes are active.  LDS accesses of a wavefront stay in order.
+template <int SLOTS>
 __device__ __forceinline__ void append4(int q, const uint64_t* m, const float* d, const int* cnt,
                                         uint32_t idx, uint32_t slot0) {
+    constexpr int B = SLOTS / WAVE;  // a buffer half in units of the store's offsets
     uint32_t t;
 #define KNNF_APPEND(M, D, N, O)                                    \
     "s_mov_b64 exec, %[" #M "]\n\t"                                \
@@ -478,9 +528,10 @@ __device__ __forceinline__ void append4(int q, const uint64_t* m, const float* d
                  : [t] "=&v"(t)
                  : [ma] "s"(m[0]), [mb] "s"(m[1]), [mc] "s"(m[2]), [md] "s"(m[3]), [da] "v"(d[0]),
                    [db] "v"(d[1]), [dc] "v"(d[2]), [dd] "v"(d[3]), [na] "s"(cnt[0]), [nb] "s"(cnt[1]),
-                   [nc] "s"(cnt[2]), [nd] "s"(cnt[3]), [i] "v"(idx), [s] "v"(slot0), [a0] "i"(2 * q),
-                   [a1] "i"(2 * q + 1), [b0] "i"(2 * q + 2), [b1] "i"(2 * q + 3), [c0] "i"(2 * q + 4),
-                   [c1] "i"(2 * q + 5), [d0] "i"(2 * q + 6), [d1] "i"(2 * q + 7)
+                   [nc] "s"(cnt[2]), [nd] "s"(cnt[3]), [i] "v"(idx), [s] "v"(slot0), [a0] "i"(2 * B * q),
+                   [a1] "i"(2 * B * q + B), [b0] "i"(2 * B * (q + 1)), [b1] "i"(2 * B * (q + 1) + B),
+                   [c0] "i"(2 * B * (q + 2)), [c1] "i"(2 * B * (q + 2) + B), [d0] "i"(2 * B * (q + 3)),
+                   [d1] "i"(2 * B * (q + 3) + B)
                  : "memory");
 #undef KNNF_APPEND
 }
@@ -504,14 +555,15 @@ __device__ __forceinline__ void append4(int q, const uint64_t* m, const float* d
 // 8: 59.0; 1000 x 1000 231, 233, 236, 248).
 // Survivors (d <= tau's distance) are appended per query with ballot +
 // mbcnt; a full buffer is cut down to the candidates within a tighter bound
-// (tighten).
-template <int QR, int QC>
-__device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDesc& f, int r0,
+// (tighten).  After `cuts` of those the scan is given up and returns true (see
+// crowded_tile); the bounds that it reached stay.
+template <int QR, int QC, int NSLOT>
+__device__ __forceinline__ bool scan_pruned(TileState<QR, QC, NSLOT>& S, const FrameDesc& f, int r0,
                                             int c0, int nqr, int nqc, int lpr, int L,
                                             const float (&iq)[QR * QC],
                                             uint32_t (&th)[QR * QC], int (&cnt)[QR * QC],
-                                            unsigned long long& pairs) {
-    constexpr int Q = QR * QC;
+                                            unsigned long long& pairs, int cuts) {
+    constexpr int Q = QR * QC, FULL = 8 * NSLOT;
     const int H = f.H, W = f.W, R = f.R;
     const float lam = f.lambda;
     const float* __restrict__ pc1 = f.pc1;
@@ -520,9 +572,10 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
 
     // the counts are kept as buffer offsets (see append4)
 #pragma unroll
-    for (int q = 0; q < Q; ++q) cnt[q] = pend_code(cnt[q]);
-    const uint32_t slot0 = ((uint32_t)(uintptr_t)&S.pend[0][0][0] - (uint32_t)pend_code(0)) / 4;
+    for (int q = 0; q < Q; ++q) cnt[q] = pend_code<NSLOT>(cnt[q]);
+    const uint32_t slot0 = ((uint32_t)(uintptr_t)&S.pend[0][0][0] - (uint32_t)pend_code<NSLOT>(0)) / 4;
     const bool stats = f.stats != nullptr;
+    bool given_up = false;
 
     // ---- live rows
     int lo = 0x7fffffff, hi = -1;
@@ -554,11 +607,11 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
     }
 
     const int nrows = hi - lo + 1;
-    if (nrows <= 0) return;
+    if (nrows <= 0) return false;
     const int nblk = (nrows + (2 << lpr) - 1) >> (lpr + 1);
     int PR = nrows;
     if (nblk > 1) PR = (nrows + nblk - 1) / nblk;
-    // x / PR by a reciprocal: (x + 0.5) / PR is at least 1/64 from an integer
+    // x / PR by a reciprocal: (x + 0.5) / PR is at least 1/128 from an integer
     const float rp = __builtin_amdgcn_rcpf((float)PR);
     const int lc = (int)(((float)L + 0.5f) * rp), lr = L - lc * PR;
     const int SW = uni((int)((WAVE + 0.5f) * rp));
@@ -603,7 +656,8 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
             }
             nside[side] = n;
         }
-        const int cl = c0 - nside[1], cr = c0 + nqc - 1 + nside[0];
+        const int cl = c0 - nside[1];
+        int cr = c0 + nqc - 1 + nside[0];
 
         // rows past the frame or the window and columns past the frame are loaded clamped
         const float* __restrict__ rowp = pc1 + (size_t)min(i, rhi) * W;
@@ -636,10 +690,10 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                 full |= cn[q];
             }
             uint32_t ovf = 0;  // queries whose buffer cannot take this step's survivors
-            if (__builtin_expect((full & PEND_FULL) != 0, 0)) {
+            if (__builtin_expect((full & FULL) != 0, 0)) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    if (cn[q] & PEND_FULL) {
+                    if (cn[q] & FULL) {
                         ovf |= 1u << q;
                         m[q] = 0;
                         cn[q] = cnt[q];
@@ -647,7 +701,7 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                 }
             }
 #pragma unroll
-            for (int q = 0; q < Q; q += 4) append4(q, m + q, d + q, cnt + q, idx, slot0);
+            for (int q = 0; q < Q; q += 4) append4<NSLOT>(q, m + q, d + q, cnt + q, idx, slot0);
 #pragma unroll
             for (int q = 0; q < Q; ++q) cnt[q] = cn[q];
             if (__builtin_expect(ovf != 0, 0)) {
@@ -655,7 +709,7 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                 // append this step's survivors
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
-                    if (L == 0) S.cnt[q] = pend_count(cnt[q]);
+                    if (L == 0) S.cnt[q] = pend_count<NSLOT>(cnt[q]);
                 wave_sync();
                 while (ovf) {
                     const int q = __builtin_ctz(ovf);
@@ -670,18 +724,206 @@ __device__ __forceinline__ void scan_pruned(TileState<QR, QC>& S, const FrameDes
                     const int nb = uni(S.cnt[q]);
                     const uint32_t thq = uniu(S.tauhi[q]);
                     const uint32_t own = (uint32_t)r * (uint32_t)W + (uint32_t)(c0 + qc);
-                    tighten(S, q, nb, jok && rq ? __float_as_uint(d) : ~0u, idx, thq, f.K, own);
+                    tighten(S, q, nb, jok && rq ? __float_as_uint(d) : ~0u, idx, thq, f.K, own, NSLOT,
+                            cut_target<NSLOT>(f.K));
+                    --cuts;
                 }
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    cnt[q] = pend_code(uni(S.cnt[q]));
+                    cnt[q] = pend_code<NSLOT>(uni(S.cnt[q]));
                     th[q] = S.tauhi[q];
+                }
+                if (cuts <= 0 && cr - jc > CROWDED_STEPS * SW) {
+                    cr = hi = -1;  // ends both loops
+                    given_up = true;
                 }
             }
         }
     }
 #pragma unroll
-    for (int q = 0; q < Q; ++q) cnt[q] = pend_count(cnt[q]);
+    for (int q = 0; q < Q; ++q) cnt[q] = pend_count<NSLOT>(cnt[q]);
+    return given_up;
+}
+
+// The whole window: rows x 64-column chunks, nearest chunk first, four rows per group.
+// Given up after `cuts` cuts of full buffers, as scan_pruned is.
+template <int QR, int QC, int NSLOT>
+__device__ __forceinline__ bool scan_all(TileLds<QR, QC, false, NSLOT>& S, const FrameDesc& f, int r0, int c0,
+                                         int nqr, int nqc, int L, const float (&iq)[QR * QC],
+                                         uint32_t (&th)[QR * QC], int (&cnt)[QR * QC],
+                                         unsigned long long& pairs, int cuts) {
+    constexpr int Q = QR * QC;
+    const int H = f.H, W = f.W, R = f.R, K = f.K;
+    const float lam = f.lambda;
+    const float* __restrict__ pc1 = f.pc1;
+    const float pinf = __int_as_float(0x7f800000), qnan = __int_as_float(0x7fc00000);
+    const int rlo = max(0, r0 - R);
+    const int rhi = min(H - 1, r0 + nqr - 1 + R);
+    int nch = (W + WAVE - 1) / WAVE;
+    const int cc = (c0 + (nqc - 1) / 2) / WAVE;
+    int tab_base = -1;       // first row of the a2 table contents
+
+    for (int t = 0; t < 2 * nch; ++t) {
+        const int m = (t & 1) ? cc + (t + 1) / 2 : cc - t / 2;
+        if (m < 0 || m >= nch) continue;
+        const int J = m * WAVE;
+        const int j = J + L;
+        const bool valid = j < W;
+        const uint64_t vm = ballot(valid);
+        const int jl = valid ? j : W - 1;
+        // lanes past the right edge get b = NaN, so no distance there is
+        // within a bound
+        float b[QC];
+#pragma unroll
+        for (int qc = 0; qc < QC; ++qc) b[qc] = valid ? feat(lam, c0 + qc) - feat(lam, j) : qnan;
+
+        const int lo = rlo;
+        int hi = rhi;
+
+        // Table blocks are aligned to rlo: block k holds rows rlo + 64k ...
+        // rlo + 64k + 63 (NaN past rhi and in the padding), so windows of up
+        // to 64 rows fill it once per tile.
+        for (int blk = rlo + ((lo - rlo) / A2ROWS) * A2ROWS; blk <= hi; blk += A2ROWS) {
+            if (blk != tab_base) {
+                wave_sync();
+                for (int u = L; u < (A2ROWS + A2PAD) * QR; u += WAVE) {
+                    const int rr = u / QR, qr = u % QR;
+                    const int r = r0 + qr, i = blk + rr;
+                    const bool act = rr < A2ROWS && qr < nqr && i <= rhi && i >= r - R && i <= r + R;
+                    const float a = feat(lam, r) - feat(lam, i);
+                    S.a2t[rr][qr] = act ? a * a : qnan;
+                }
+                wave_sync();
+                tab_base = blk;
+            }
+            const int g0 = max(lo, blk) - blk;
+            int g1 = min(hi, blk + A2ROWS - 1) - blk;  // last table row used
+            const uint32_t joff = (uint32_t)jl;
+            const float* __restrict__ rowp = pc1 + (size_t)(blk + g0) * W;
+            float ipn[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                ipn[u] = rowp[(size_t)min(u, g1 - g0) * W + joff];
+            for (int g = g0; g <= g1; g += 4) {
+                float ip[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) ip[u] = ipn[u];
+                if (g + 4 <= g1) {
+                    const float* __restrict__ np = pc1 + (size_t)(blk + g + 4) * W;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) ipn[u] = np[(size_t)min(u, g1 - g - 4) * W + joff];
+                }
+                float a2[4][QR];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int qr = 0; qr < QR; ++qr) a2[u][qr] = S.a2t[g + u][qr];
+                const int i0 = blk + g;
+                if (f.stats) {
+                    const int nvl = min(WAVE, W - J);
+#pragma unroll
+                    for (int qr = 0; qr < QR; ++qr) {
+                        const int r = r0 + qr;
+                        const int a = max(i0, max(lo, r - R)), z = min(i0 + 3, min(hi, r + R));
+                        if (qr < nqr && z >= a) pairs += (unsigned long long)(z - a + 1) * nqc * nvl;
+                    }
+                }
+                uint32_t ovf = 0;  // queries whose buffer cannot take this group's survivors
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int qr = q / QC, qc = q % QC;
+                    float d[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float e = iq[q] - ip[u];
+                        const float tt = fmaf(b[qc], b[qc], a2[u][qr]);
+                        d[u] = fmaf(e, e, tt);
+                    }
+                    const uint32_t mn = min(min(__float_as_uint(d[0]), __float_as_uint(d[1])),
+                                            min(__float_as_uint(d[2]), __float_as_uint(d[3])));
+                    if (ballot(mn <= th[q])) {
+                        // rare: some candidate of the group is within the
+                        // bound; append the group's survivors if they fit
+                        uint64_t mu[4];
+                        int n = 0;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            mu[u] = ballot(__float_as_uint(d[u]) <= th[q]);
+                            n += __builtin_popcountll(mu[u]);
+                        }
+                        if (cnt[q] + n <= NSLOT) {
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                if (__float_as_uint(d[u]) <= th[q]) {
+                                    const int slot = cnt[q] + mbcnt(mu[u]);
+                                    S.pend[q][0][slot] = __float_as_uint(d[u]);
+                                    S.pend[q][1][slot] = (uint32_t)((i0 + u) * W + j);
+                                }
+                                cnt[q] += __builtin_popcountll(mu[u]);
+                            }
+                        } else {
+                            ovf |= 1u << q;
+                        }
+                    }
+                }
+                if (ovf) {
+                    // rare: cut the full buffers down (which tightens the
+                    // bounds), appending the group row by row
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        if (L == 0) S.cnt[q] = cnt[q];
+                    wave_sync();
+                    while (ovf) {
+                        const int q = __builtin_ctz(ovf);
+                        ovf &= ovf - 1;
+                        const int qr = q / QC, qc = q % QC;
+                        const int r = r0 + qr;
+                        int cq = uni(S.cnt[q]);
+                        uint32_t thq = uniu(S.tauhi[q]);
+                        const float bq = valid ? feat(lam, c0 + qc) - feat(lam, j) : pinf;
+                        const float iqq = S.iq[q];
+                        for (int u = 0; u < 4; ++u) {
+                            const int i = i0 + u;
+                            if (qr >= nqr || i > hi || i < r - R || i > r + R) continue;
+                            const float a2q = S.a2t[g + u][qr];
+                            const float e = iqq - ip[u];
+                            const float du = fmaf(e, e, fmaf(bq, bq, a2q));
+                            uint64_t msk = ballot(__float_as_uint(du) <= thq) & vm;
+                            if (!msk) continue;
+                            if (cq + __builtin_popcountll(msk) > NSLOT) {
+                                const uint32_t own = (uint32_t)r * (uint32_t)W + (uint32_t)(c0 + qc);
+                                tighten(S, q, cq, valid ? __float_as_uint(du) : ~0u,
+                                        (uint32_t)(i * W + j), thq, K, own, NSLOT,
+                                        cut_target<NSLOT>(K));
+                                --cuts;
+                                cq = uni(S.cnt[q]);
+                                thq = uniu(S.tauhi[q]);
+                                continue;
+                            }
+                            if (valid && __float_as_uint(du) <= thq) {
+                                S.pend[q][0][cq + mbcnt(msk)] = __float_as_uint(du);
+                                S.pend[q][1][cq + mbcnt(msk)] = (uint32_t)(i * W + j);
+                            }
+                            cq += __builtin_popcountll(msk);
+                        }
+                        wave_sync();
+                        if (L == 0) {
+                            S.cnt[q] = cq;
+                            S.tauhi[q] = thq;
+                        }
+                        wave_sync();
+                    }
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        cnt[q] = uni(S.cnt[q]);
+                        th[q] = S.tauhi[q];
+                    }
+                    if (cuts <= 0) nch = hi = g1 = -1;  // ends all loops
+                }
+            }
+        }
+    }
+    return cuts <= 0;
 }
 
 // s + v[0] + v[1] + ... + v[N-1], left to right, where v[u] is the float at
@@ -867,8 +1109,8 @@ __device__ __forceinline__ void tile_bound(TileState<QR, QC>& S, const FrameDesc
 
 // Final selection and Eq. 2 of a tile; E: buffer slots per lane (all of them,
 // or the first half where no buffer holds more).
-template <int QR, int QC, int E>
-__device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDesc& f, int r0, int c0,
+template <int QR, int QC, int E, int NSLOT>
+__device__ __forceinline__ void finish_tile(TileState<QR, QC, NSLOT>& S, const FrameDesc& f, int r0, int c0,
                                             int nqr, int nqc, int L) {
     constexpr int Q = QR * QC, P = WAVE / Q;
     const int H = f.H, W = f.W, K = f.K, C = f.C;
@@ -1082,11 +1324,137 @@ __device__ __forceinline__ void finish_tile(TileState<QR, QC>& S, const FrameDes
     }
 }
 
+// Order the queries whose bound lies beyond the packed keys' range (rare), then select,
+// average and write.  The buffers hold at most 64 candidates each.
+template <int QR, int QC, int NSLOT>
+__device__ __forceinline__ void select_tile(TileState<QR, QC, NSLOT>& S, const FrameDesc& f, int r0, int c0,
+                                            int nqr, int nqc, int L, const int (&cnt)[QR * QC]) {
+    constexpr int Q = QR * QC, E = Q;
+    int most = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) most = max(most, uni(cnt[q]));
+    wave_sync();
+    {
+        const bool one = L < Q && L / QC < nqr && L % QC < nqc;
+        uint64_t need = ballot(one && S.tauhi[L % Q] > BIG);
+        if (__builtin_expect(need != 0, 0)) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (L == 0) S.cnt[q] = cnt[q];
+            wave_sync();
+            while (need) {
+                const int q = (int)__builtin_ctzll(need);
+                need &= need - 1;
+                order_query(S, f, r0, c0, q, uni(S.cnt[q]));
+            }
+        }
+    }
+    if constexpr (E >= 8) {
+        if (most <= WAVE / 2 && f.K <= WAVE / 2) {
+            finish_tile<QR, QC, E / 2>(S, f, r0, c0, nqr, nqc, L);
+            return;
+        }
+    }
+    finish_tile<QR, QC, E>(S, f, r0, c0, nqr, nqc, L);
+}
+
+// v, as a value that is not known before this point.
+__device__ __forceinline__ uint32_t here(uint32_t v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+// The same pointer, known to point to global memory.
+template <class T>
+__device__ __forceinline__ T* in_global(T* p) {
+    typedef __attribute__((address_space(1))) T Global;
+    return (T*)(Global*)(uintptr_t)p;
+}
+
+// A tile whose buffers overflow again and again, because a bound from 64 or 128 of its
+// block's candidates lets far more than 64 through (small lambda, unstructured bands, K
+// close to 64), is done over in parts of four queries, whose buffers have 128 slots in
+// the same LDS, from the bounds that its scan has reached; and a tile of the pruned search
+// whose bounds leave about half of the window (FrameDesc::wide) is done in this way from
+// the start, by the whole-window scan.  380 x 480, with and without: lambda 0.0001, K = 40
+// 670 and 1,380 us; lambda 0.001, K = 64 490 and 1,230; uniform noise, K = 56 400 and 700.
+// It keeps no registers in the ordinary tiles: the frame is read again from where the
+// kernel has it (`frame`), and nothing that it computes can be moved ahead (kept in a
+// function of its own, its calls' stack cost every tile 4 %).
+template <int QR, int QC, bool PRUNE>
+__device__ __forceinline__ unsigned long long crowded_tile(
+    uint32_t tile, const FrameDesc* frame, int r0, int c0, int lpr) {
+    typedef __attribute__((address_space(3))) char Lds;
+    typedef TileLds<1, 4, false, 2 * WAVE> Part;
+    typedef TileState<QR, QC> Tile;
+    static_assert(sizeof(Part) <= offsetof(Tile, tauhi), "a part fits below the tile's bounds");
+    unsigned long long pairs = 0;
+    for (int part = 0; part < QR * QC / 4; ++part) {
+        // everything anew in each part: what the compiler moves out of the loop, or finds
+        // in the ordinary tile's registers, costs registers there
+        Tile& S = *(Tile*)(char*)(Lds*)here(tile);
+        const uint64_t at = (uint64_t)here((uint32_t)((uint64_t)frame >> 32)) << 32 | here((uint32_t)(uint64_t)frame);
+        FrameDesc f = *in_global((const FrameDesc*)at);
+        f.pc1 = in_global(f.pc1);
+        f.prob = in_global(f.prob);
+        f.out_prob = in_global(f.out_prob);
+        f.out_class = in_global(f.out_class);
+        f.out_nbr = in_global(f.out_nbr);
+        f.out_dist = in_global(f.out_dist);
+        const int L = lane_id_here();
+        const int r = (int)here((uint32_t)(r0 + 4 * part / QC)), c = (int)here((uint32_t)(c0 + 4 * part % QC));
+        if (r >= f.H || c >= f.W) continue;
+        Part& T = *(Part*)&S;
+        const int nq = min(4, f.W - c);
+        float iq[4];
+        uint32_t th[4];
+        int cnt[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            iq[q] = S.iq[4 * part + q];
+            th[q] = S.tauhi[4 * part + q];
+            cnt[q] = 0;
+        }
+        if (L < 4) {
+            T.iq[L] = S.iq[4 * part + L];
+            T.tauhi[L] = S.tauhi[4 * part + L];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                T.pend[q][0][WAVE * v + L] = PAD + 64u * (uint32_t)(WAVE * v + L);
+                T.pend[q][1][WAVE * v + L] = (uint32_t)r * (uint32_t)f.W + (uint32_t)(c + q);
+            }
+        }
+        wave_sync();
+        if (PRUNE && !ballot(T.tauhi[L & 3] > f.wide))
+            scan_pruned(T, f, r, c, 1, nq, lpr, L, iq, th, cnt, pairs, 0x7fffffff);
+        else
+            scan_all(T, f, r, c, 1, nq, L, iq, th, cnt, pairs, 0x7fffffff);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (L == 0) T.cnt[q] = cnt[q];
+        wave_sync();
+        for (int q = 0; q < 4; ++q) {
+            const int nb = uni(T.cnt[q]);
+            if (nb > WAVE)
+                tighten(T, q, nb, ~0u, 0u, uniu(T.tauhi[q]), f.K,
+                        (uint32_t)r * (uint32_t)f.W + (uint32_t)(c + q), WAVE, WAVE);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cnt[q] = uni(T.cnt[q]);
+        select_tile(T, f, r, c, 1, nq, L, cnt);
+        wave_sync();
+    }
+    return pairs;
+}
+
 // Process one tile: query pixels (r0 + qr, c0 + qc), qr < QR, qc < QC.
+// frame: f, as the kernel was given it in memory.
 // NA: largest pass-A block (128 candidates per query; 64 for 16-query tiles).
 template <int QR, int QC, bool PRUNE, int NA = (QR * QC == 8 ? 128 : WAVE)>
-__device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const FrameDesc& f, int r0,
-                                             int c0, int lpr, int L) {
+__device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const FrameDesc& f,
+                                             const FrameDesc* frame, int r0, int c0, int lpr, int L) {
     constexpr int Q = QR * QC;
     const int H = f.H, W = f.W, R = f.R, K = f.K;
     const float lam = f.lambda;
@@ -1126,197 +1494,19 @@ __device__ __forceinline__ void process_tile(TileLds<QR, QC, PRUNE>& S, const Fr
     }
 
     // ---- pass B
+    bool crowded = false;
     if constexpr (PRUNE) {
-        scan_pruned<QR, QC>(S, f, r0, c0, nqr, nqc, lpr, L, iq, th, cnt, pairs);
+        crowded = ballot(S.tauhi[L % Q] > f.wide) != 0;
+        if (!crowded) crowded = scan_pruned(S, f, r0, c0, nqr, nqc, lpr, L, iq, th, cnt, pairs, crowded_cuts(Q, K));
     } else {
-        // exhaustive: window rows x 64-column chunks, nearest chunk first
-        const int rlo = max(0, r0 - R);
-        const int rhi = min(H - 1, r0 + nqr - 1 + R);
-        const int nch = (W + WAVE - 1) / WAVE;
-        const int cc = (c0 + (nqc - 1) / 2) / WAVE;
-        int tab_base = -1;       // first row of the a2 table contents
-
-        for (int t = 0; t < 2 * nch; ++t) {
-            const int m = (t & 1) ? cc + (t + 1) / 2 : cc - t / 2;
-            if (m < 0 || m >= nch) continue;
-            const int J = m * WAVE;
-            const int j = J + L;
-            const bool valid = j < W;
-            const uint64_t vm = ballot(valid);
-            const int jl = valid ? j : W - 1;
-            // lanes past the right edge get b = NaN, so no distance there is
-            // within a bound
-            float b[QC];
-#pragma unroll
-            for (int qc = 0; qc < QC; ++qc) b[qc] = valid ? feat(lam, c0 + qc) - feat(lam, j) : qnan;
-
-            const int lo = rlo, hi = rhi;
-
-            // Table blocks are aligned to rlo: block k holds rows rlo + 64k ...
-            // rlo + 64k + 63 (NaN past rhi and in the padding), so windows of up
-            // to 64 rows fill it once per tile.
-            for (int blk = rlo + ((lo - rlo) / A2ROWS) * A2ROWS; blk <= hi; blk += A2ROWS) {
-                if (blk != tab_base) {
-                    wave_sync();
-                    for (int u = L; u < (A2ROWS + A2PAD) * QR; u += WAVE) {
-                        const int rr = u / QR, qr = u % QR;
-                        const int r = r0 + qr, i = blk + rr;
-                        const bool act = rr < A2ROWS && qr < nqr && i <= rhi && i >= r - R && i <= r + R;
-                        const float a = feat(lam, r) - feat(lam, i);
-                        S.a2t[rr][qr] = act ? a * a : qnan;
-                    }
-                    wave_sync();
-                    tab_base = blk;
-                }
-                const int g0 = max(lo, blk) - blk;
-                const int g1 = min(hi, blk + A2ROWS - 1) - blk;  // last table row used
-                const uint32_t joff = (uint32_t)jl;
-                const float* __restrict__ rowp = pc1 + (size_t)(blk + g0) * W;
-                float ipn[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    ipn[u] = rowp[(size_t)min(u, g1 - g0) * W + joff];
-                for (int g = g0; g <= g1; g += 4) {
-                    float ip[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) ip[u] = ipn[u];
-                    if (g + 4 <= g1) {
-                        const float* __restrict__ np = pc1 + (size_t)(blk + g + 4) * W;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) ipn[u] = np[(size_t)min(u, g1 - g - 4) * W + joff];
-                    }
-                    float a2[4][QR];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int qr = 0; qr < QR; ++qr) a2[u][qr] = S.a2t[g + u][qr];
-                    const int i0 = blk + g;
-                    if (f.stats) {
-                        const int nvl = min(WAVE, W - J);
-#pragma unroll
-                        for (int qr = 0; qr < QR; ++qr) {
-                            const int r = r0 + qr;
-                            const int a = max(i0, max(lo, r - R)), z = min(i0 + 3, min(hi, r + R));
-                            if (qr < nqr && z >= a) pairs += (unsigned long long)(z - a + 1) * nqc * nvl;
-                        }
-                    }
-                    uint32_t ovf = 0;  // queries whose buffer cannot take this group's survivors
-#pragma unroll
-                    for (int q = 0; q < Q; ++q) {
-                        const int qr = q / QC, qc = q % QC;
-                        float d[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const float e = iq[q] - ip[u];
-                            const float tt = fmaf(b[qc], b[qc], a2[u][qr]);
-                            d[u] = fmaf(e, e, tt);
-                        }
-                        const uint32_t mn = min(min(__float_as_uint(d[0]), __float_as_uint(d[1])),
-                                                min(__float_as_uint(d[2]), __float_as_uint(d[3])));
-                        if (ballot(mn <= th[q])) {
-                            // rare: some candidate of the group is within the
-                            // bound; append the group's survivors if they fit
-                            uint64_t mu[4];
-                            int n = 0;
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                mu[u] = ballot(__float_as_uint(d[u]) <= th[q]);
-                                n += __builtin_popcountll(mu[u]);
-                            }
-                            if (cnt[q] + n <= WAVE) {
-#pragma unroll
-                                for (int u = 0; u < 4; ++u) {
-                                    if (__float_as_uint(d[u]) <= th[q]) {
-                                        const int slot = cnt[q] + mbcnt(mu[u]);
-                                        S.pend[q][0][slot] = __float_as_uint(d[u]);
-                                        S.pend[q][1][slot] = (uint32_t)((i0 + u) * W + j);
-                                    }
-                                    cnt[q] += __builtin_popcountll(mu[u]);
-                                }
-                            } else {
-                                ovf |= 1u << q;
-                            }
-                        }
-                    }
-                    if (ovf) {
-                        // rare: cut the full buffers down (which tightens the
-                        // bounds), appending the group row by row
-#pragma unroll
-                        for (int q = 0; q < Q; ++q)
-                            if (L == 0) S.cnt[q] = cnt[q];
-                        wave_sync();
-                        while (ovf) {
-                            const int q = __builtin_ctz(ovf);
-                            ovf &= ovf - 1;
-                            const int qr = q / QC, qc = q % QC;
-                            const int r = r0 + qr;
-                            int cq = uni(S.cnt[q]);
-                            uint32_t thq = uniu(S.tauhi[q]);
-                            const float bq = valid ? feat(lam, c0 + qc) - feat(lam, j) : pinf;
-                            const float iqq = S.iq[q];
-                            for (int u = 0; u < 4; ++u) {
-                                const int i = i0 + u;
-                                if (qr >= nqr || i > hi || i < r - R || i > r + R) continue;
-                                const float a2q = S.a2t[g + u][qr];
-                                const float e = iqq - ip[u];
-                                const float du = fmaf(e, e, fmaf(bq, bq, a2q));
-                                uint64_t msk = ballot(__float_as_uint(du) <= thq) & vm;
-                                if (!msk) continue;
-                                if (cq + __builtin_popcountll(msk) > WAVE) {
-                                    const uint32_t own = (uint32_t)r * (uint32_t)W + (uint32_t)(c0 + qc);
-                                    tighten(S, q, cq, valid ? __float_as_uint(du) : ~0u,
-                                            (uint32_t)(i * W + j), thq, f.K, own);
-                                    cq = uni(S.cnt[q]);
-                                    thq = uniu(S.tauhi[q]);
-                                    continue;
-                                }
-                                if (valid && __float_as_uint(du) <= thq) {
-                                    S.pend[q][0][cq + mbcnt(msk)] = __float_as_uint(du);
-                                    S.pend[q][1][cq + mbcnt(msk)] = (uint32_t)(i * W + j);
-                                }
-                                cq += __builtin_popcountll(msk);
-                            }
-                            wave_sync();
-                            if (L == 0) {
-                                S.cnt[q] = cq;
-                                S.tauhi[q] = thq;
-                            }
-                            wave_sync();
-                        }
-#pragma unroll
-                        for (int q = 0; q < Q; ++q) {
-                            cnt[q] = uni(S.cnt[q]);
-                            th[q] = S.tauhi[q];
-                        }
-                    }
-                }
-            }
-        }
+        crowded = scan_all(S, f, r0, c0, nqr, nqc, L, iq, th, cnt, pairs, crowded_cuts_all(Q, K));
+        if (crowded) pairs = (unsigned long long)(nqr * nqc) * (big ? 128 : WAVE);  // all is evaluated again
     }
 
     // ---- final selection, Eq. 2, outputs
-    int most = 0;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) most = max(most, uni(cnt[q]));
-    wave_sync();
-    // queries with a bound beyond the packed keys' range need the exact order (rare)
-    {
-        const bool one = L < Q && L / QC < nqr && L % QC < nqc;
-        uint64_t need = ballot(one && S.tauhi[L % Q] > BIG);
-        if (__builtin_expect(need != 0, 0)) {
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (L == 0) S.cnt[q] = cnt[q];
-            wave_sync();
-            while (need) {
-                const int q = (int)__builtin_ctzll(need);
-                need &= need - 1;
-                order_query(S, f, r0, c0, q, uni(S.cnt[q]));
-            }
-        }
-    }
-    if (most <= WAVE / 2 && K <= WAVE / 2) finish_tile<QR, QC, Q / 2>(S, f, r0, c0, nqr, nqc, L);
-    else finish_tile<QR, QC, Q>(S, f, r0, c0, nqr, nqc, L);
+    if (__builtin_expect(crowded, 0)) pairs += crowded_tile<QR, QC, PRUNE>(
+        (uint32_t)(uintptr_t)&S, frame, r0, c0, lpr);
+    else select_tile(S, f, r0, c0, nqr, nqc, L, cnt);
     if (f.stats && L == 0) {
         atomicAdd(&f.stats[0], pairs);
         atomicAdd(&f.stats[1], 1ull);
@@ -1338,7 +1528,7 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 // 52.3 us, 1000 x 1000 210, 1024 frames of 50 x 50 449; six wavefronts 53.6, 218
 // and 472; eight (64 registers, some spilled) 54.4, 212 and 447.  Their 4,832
 // bytes of LDS would allow eight.
-#define KNNF_WAVES_PER_EU(QR, QC) __attribute__((amdgpu_waves_per_eu((QR) * (QC) == 8 ? 7 : 1)))
+#define KNNF_WAVES_PER_EU(QR, QC) __attribute__((amdgpu_waves_per_eu((QR) * (QC) == 8 ? 7 : 4)))
 
 template <int QR, int QC, int WPB, bool PRUNE>
 __global__ void __launch_bounds__(WPB * WAVE) KNNF_WAVES_PER_EU(QR, QC)
@@ -1353,7 +1543,7 @@ filter_frame_kernel(FrameDesc f, int lpr) {
     if (s >= ntiles) return;
     const uint32_t band = s / ntc;
     const uint32_t tc = s - band * ntc;
-    process_tile<QR, QC, PRUNE>(lds[w], f, (int)band * QR, (int)tc * QC, lpr, lane_id());
+    process_tile<QR, QC, PRUNE>(lds[w], f, (const FrameDesc*)__builtin_amdgcn_kernarg_segment_ptr(), (int)band * QR, (int)tc * QC, lpr, lane_id());
 }
 
 // Persistent batched kernel: each wavefront claims tile tasks from one global
@@ -1396,7 +1586,7 @@ filter_batch_kernel(const FrameDesc* __restrict__ frames, const uint32_t* __rest
             const int band = (int)(s / ntc);
             const int tc = (int)(s - (uint32_t)band * ntc);
             // the claim loop's registers leave no room for 128-candidate blocks
-            process_tile<QR, QC, PRUNE, WAVE>(lds[w], f, band * QR, tc * QC, lpr, lane_id_here());
+            process_tile<QR, QC, PRUNE, WAVE>(lds[w], f, frames + k, band * QR, tc * QC, lpr, lane_id_here());
         }
     }
 }
@@ -1424,7 +1614,7 @@ filter_items_kernel(const FrameDesc* __restrict__ frames, const uint32_t* __rest
     const uint32_t ntc = (uint32_t)((f.W + QC - 1) / QC);
     const int band = (int)(s / ntc);
     const int tc = (int)(s - (uint32_t)band * ntc);
-    process_tile<QR, QC, PRUNE>(lds[w], f, band * QR, tc * QC, lpr, lane_id());
+    process_tile<QR, QC, PRUNE>(lds[w], f, frames + lo, band * QR, tc * QC, lpr, lane_id());
 }
 
 template <int QR, int QC, int WPB, bool PRUNE>

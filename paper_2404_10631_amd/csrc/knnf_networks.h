@@ -94,7 +94,18 @@ __device__ __forceinline__ void cross(uint32_t (&x)[E], uint32_t keep) {
 #pragma unroll
     for (int r = 0; r < E; ++r) x[r] = med3u(x[r], t[r], keep);
 }
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_XOR7 = 0x141;
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR3 = 0x1B, DPP_XOR7 = 0x141, DPP_XOR15 = 0x140;
+// cross with lane L ^ 4, by way of L ^ 7.
+template <int E>
+__device__ __forceinline__ void cross_xor4(uint32_t (&x)[E], uint32_t keep) {
+    uint32_t t[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r)
+        t[r] = (uint32_t)__builtin_amdgcn_mov_dpp(
+            __builtin_amdgcn_mov_dpp((int)x[r], DPP_XOR7, 0xF, 0xF, false), DPP_XOR3, 0xF, 0xF, false);
+#pragma unroll
+    for (int r = 0; r < E; ++r) x[r] = med3u(x[r], t[r], keep);
+}
 
 }  // namespace
 }  // namespace knnf
