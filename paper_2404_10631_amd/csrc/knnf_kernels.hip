@@ -1638,9 +1638,12 @@ int launch_frame_t(const FrameDesc& f, int lpr, hipStream_t st) {
 template <int QR, int QC, int WPB, bool PRUNE>
 int launch_batch_t(const FrameDesc* fr, const uint32_t* ts, const uint32_t* tb, uint32_t n,
                    uint32_t tot, uint32_t* ctr, int grid, int lpr, hipStream_t st) {
-    // at least four claims per resident wavefront, at most 8 tasks per claim
+    // at least four claims per resident wavefront, at most 8 tasks per claim; but no more
+    // than 16,384 claims where 16 tasks each allow that: the counter takes one every 15 to
+    // 20 ns (64 frames of 100 x 120, 1 x 16 tiles: 24,000 claims 355 us, 16,000 234)
     const uint64_t waves = (uint64_t)grid * WPB;
-    const uint32_t claim = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(8, tot / (waves * 4)));
+    const uint64_t few = std::min<uint64_t>(16, (tot + 16383) / 16384);
+    const uint32_t claim = (uint32_t)std::max<uint64_t>({1, std::min<uint64_t>(8, tot / (waves * 4)), few});
     hipLaunchKernelGGL((filter_batch_kernel<QR, QC, WPB, PRUNE>), dim3((unsigned)grid),
                        dim3(WPB * WAVE), 0, st, fr, ts, tb, n, tot, claim, ctr, lpr);
     return (int)hipGetLastError();
