@@ -28,7 +28,8 @@
 //   * A wavefront owns a tile of 64 pixels and goes through it in items of 16
 //     pixels x up to 128 bands: one contiguous span of memory, each cache line
 //     requested once.  A load takes two pixel rows, 32 lanes of 16-byte pieces
-//     (4 bands) each; up to 64 bands, four rows of 16.  Any band count from 4 on
+//     (4 bands) each; up to 64, 32 and 16 bands, 4, 8
+//     and 16 rows.  Any band count from 4 on
 //     and any 4-byte alignment: the last piece of a pixel starts at bands - 4,
 //     and the bands that it repeats count as 0.  The next item's loads are
 //     issued before the current one is used.  (Two items in flight, persistent
@@ -46,12 +47,15 @@
 //     coupling iteration, whose sweep count differs from pixel to pixel.
 // The fused variant (PC1 = true) adds the PC1 projection, so the pipeline's two steps
 // before the filter read the cube once.  Its terms are centred, so they can not be one
-// more column of the product: each lane forms those of its pieces as they arrive (the
-// averages and eigenvector entries of its four bands stay in registers), and they go
-// through the item's LDS buffer to the four lanes of a pixel that sum them.  (Uncentred, as a column of the product with one constant subtracted at the
-// end, it took 25.3 instead of 27.2 us a call on 380 x 480 x 128, but its error was that
-// of the uncentred terms: sensor counts of 60,000 +- 2 came out up to 0.18 of a
-// binary32 ulp off at 128 bands, 1.1 at 4,096.)
+// more column of the product: each lane forms those of the operands that it has
+// converted for the product, (x - average) times eigenvector entry, whose 16-byte pairs
+// lie in LDS beside the weights (0 for the bands and slots that the product leaves out).
+// (Uncentred, as a column of the product with one constant subtracted at the end, the
+// error was that of the uncentred terms: sensor counts of 60,000 +- 2 came out up to 0.18
+// of a binary32 ulp off at 128 bands, 1.1 at 4,096.  Formed as the pieces arrive, before
+// the product, the terms cost a second conversion, an exchange through LDS and the work
+// of idle lanes: 1000 x 1000, four classes, 100 bands 121 us a call, 111 in this form;
+// 132 bands 172 and 149.)
 // What bounds it: 1000 x 1000 x 100, four classes, 84.5 us (105 us with the
 // lane-per-pixel product): the same kernel without its arithmetic takes 74 us
 // (5.6 TB/s, the rate of a plain read of the cube), the vector pipe is busy
@@ -114,9 +118,8 @@ __device__ __forceinline__ double rcp64(double x) {
 }
 
 // exp(z) for |z| <= 700: z = k ln 2 + r with |r| <= ln 2 / 2 (ln 2 in two
-// parts), and on that interval the degree-11 polynomial that interpolates exp
-// at Chebyshev points (relative error 1.6e-17 before rounding), by Horner's
-// rule.  The sigmoid's argument is capped to that range, so the special cases
+// parts), and on that interval the truncated Chebyshev series of degree 11
+// (relative error 1.6e-17 before rounding), by Horner's rule.  The sigmoid's argument is capped to that range, so the special cases
 // of the library function (a third of its instructions) have no place.
 __device__ __forceinline__ double exp_capped(double z) {
     const double k = __builtin_rint(z * 0x1.71547652b82fep+0);
@@ -252,8 +255,7 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// NL: 16-byte loads per lane and item (8: up to 128 bands per item; 4: up to
-// 64, for cubes of no more).
+// NL: 16-byte loads per lane and item, of up to 16 NL bands (1, 2, 4 or 8).
 template <int C, bool PC1, int NL>
 __global__ void __launch_bounds__(SVM_THREADS, C <= 4 ? 3 : C <= 6 ? 2 : 1)
 svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
@@ -270,11 +272,9 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
     // and e + 1 reads 16 bytes
     __shared__ __attribute__((aligned(16))) double wl[NL * Cols::WST];
     // an item's pieces, a row of MAXP per pixel and one of padding (bank
-    // spread), after the projection's term of each (PC1); after the tile's last
-    // item, its sums
+    // spread); after the tile's last item, its sums
     union Buf {
         float4 x[16 * (MAXP + 1)];
-        double term[16 * (MAXP + 1)];
         double part[SVM_TILE / 16][64];
         double sum[XP * ST];
     };
@@ -321,6 +321,19 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
             wr[j] = used ? x : 0.0;
         }
     };
+    // (average, eigenvector entry) of the chunk's band slots, one a thread (PC1)
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(16))) d2 pl[PC1 ? NSLOT : 1];
+    d2 pr = {0.0, 0.0};
+    auto fetch_piece = [&](int chunk) {
+        if constexpr (PC1) {
+            const int slot = (tid & (NSLOT - 1)) + chunk * NSLOT, piece = slot >> 2;
+            const int b = piece < np - 1 ? slot : bands - 4 + (slot & 3);
+            const bool used = piece < np && b >= 4 * piece;
+            const d2 x = {mean[used ? b : 0], vec[used ? b : 0]};
+            pr = used ? x : d2{0.0, 0.0};
+        }
+    };
     auto store_weights = [&]() {
 #pragma unroll
         for (int j = 0; j < NW; ++j) {
@@ -329,16 +342,17 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
             if (NSLOT % SPT == 0 || slot < NSLOT)
                 wl[s * Cols::WST + (((e >> 1) * NG + (wcol >> 2)) * 16 + k * 4 + (wcol & 3)) * 2 + (e & 1)] = wr[j];
         }
+        if (PC1 && tid < NSLOT) pl[tid] = pr;
     };
     load_item(0, 0);
     __builtin_amdgcn_sched_barrier(0);
     fetch_weights(0);
+    fetch_piece(0);
     store_weights();
     __syncthreads();
 
     char* xb = (char*)buf[wv].x;
     const double* wk = wl + ((lane >> 4) * 4 + (lane & 3)) * 2;
-    typedef double d2 __attribute__((ext_vector_type(2)));
     double acc[G][NG];
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -360,18 +374,9 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
                     *(float4*)(xw + i * RPL * (MAXP + 1) * 16) = make_float4(0.f, 0.f, 0.f, 0.f);
             }
         };
-        if (!PC1) zero_slots();
+        zero_slots();
         // bands that the last piece repeats: 0 as well
         const int rep = lpc + chunk * MAXP == np - 1 ? 4 * np - bands : 0;
-        double mu[4], ev[4];  // of the lane's piece
-        if constexpr (PC1) {
-            const int b0 = lpc + chunk * MAXP < np - 1 ? 4 * (lpc + chunk * MAXP) : bands - 4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                mu[e] = mean[b0 + e];
-                ev[e] = e < rep ? 0.0 : vec[b0 + e];
-            }
-        }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             wave_lds_sync();
@@ -382,24 +387,6 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
                     v[i].y = rep > 1 ? 0.f : v[i].y;
                     v[i].z = rep > 2 ? 0.f : v[i].z;
                 }
-            }
-            if constexpr (PC1) {
-                double* term = buf[wv].term;
-#pragma unroll
-                for (int i = 0; i < NL; ++i) {
-                    double t = ((double)v[i].x - mu[0]) * ev[0];
-                    t = fma((double)v[i].y - mu[1], ev[1], t);
-                    t = fma((double)v[i].z - mu[2], ev[2], t);
-                    t = fma((double)v[i].w - mu[3], ev[3], t);
-                    term[(RPL * i + lrow) * (MAXP + 1) + lpc] = lpc < pc ? t : 0.0;
-                }
-                wave_lds_sync();
-#pragma unroll
-                for (int k = 0; k < MAXP / 4; ++k)
-                    pj[g] += term[(lane & 15) * (MAXP + 1) + 4 * k + (lane >> 4)];
-                asm volatile("" : "+v"(pj[g]));  // summed here: the terms are not kept
-                wave_lds_sync();
-                zero_slots();  // where the terms lay
             }
             if (lpc < pc) {
 #pragma unroll
@@ -414,6 +401,13 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
                 const float4 x = *(const float4*)(xr + s * 64);
                 const double xd[4] = {(double)x.x, (double)x.y, (double)x.z, (double)x.w};
                 const double* wp = wk + s * Cols::WST;
+                if constexpr (PC1) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const d2 me = pl[16 * s + 4 * (lane >> 4) + e];
+                        pj[g] = fma(xd[e] - me.x, me.y, pj[g]);
+                    }
+                }
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     d2 wt[NG];
@@ -431,6 +425,7 @@ svm_prob_kernel(const float* __restrict__ cube, int64_t npix, int bands,
         }
         if (++chunk < nchunk) {
             fetch_weights(chunk);
+            fetch_piece(chunk);
             __syncthreads();
             store_weights();
             __syncthreads();
@@ -544,14 +539,25 @@ int launch_c(const SvmArgs& a, void* stream, int* nblocks) {
         hipLaunchKernelGGL((svm_prob_few_kernel<C, PC1>), dim3(blocks), dim3(SVM_THREADS), 0, st,
                            a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean, a.vec,
                            a.band, a.ws, a.pairs);
-    else if (a.bands <= 64)
-        hipLaunchKernelGGL((svm_prob_kernel<C, PC1, 4>), dim3(blocks), dim3(SVM_THREADS), 0, st,
-                           a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean, a.vec,
-                           a.band, a.ws, a.pairs);
-    else
-        hipLaunchKernelGGL((svm_prob_kernel<C, PC1, 8>), dim3(blocks), dim3(SVM_THREADS), 0, st,
-                           a.cube, a.npix, a.bands, a.w, a.bias, a.A, a.B, a.out, a.mean, a.vec,
-                           a.band, a.ws, a.pairs);
+    else {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(SVM_THREADS), 0, st, a.cube, a.npix, a.bands, a.w,
+                               a.bias, a.A, a.B, a.out, a.mean, a.vec, a.band, a.ws, a.pairs);
+        };
+        const int np = (a.bands + 3) / 4;
+        // The least NL whose item holds the pixel's pieces: a lane past them loads
+        // and stores nothing of use (us a call, 1000 x 1000, fused, two classes, NL 1
+        // and 4: 16 bands 29.7 and 34; four classes 43.8 and 53).  Past 128 bands,
+        // items of 64 where the last one of 128 would be half empty and rows start
+        // at full cache lines (us, 380 x 480, four classes, NL 4 and 8: 160 bands
+        // fused 31.1 and 34.7, 192 bands 33.8 and 37.7); where they do not, an item's
+        // end cuts a line (1000 x 1000 x 132, two classes: 124 in halves, 102 whole).
+        const bool halves = np > 32 && a.bands % 32 == 0 && (np - 1) % 32 < 16;
+        if (np <= 4) launch(svm_prob_kernel<C, PC1, 1>);
+        else if (np <= 8) launch(svm_prob_kernel<C, PC1, 2>);
+        else if (np <= 16 || halves) launch(svm_prob_kernel<C, PC1, 4>);
+        else launch(svm_prob_kernel<C, PC1, 8>);
+    }
     if (nblocks) *nblocks = (int)blocks;
     return (int)hipGetLastError();
 }
