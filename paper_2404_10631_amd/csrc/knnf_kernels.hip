@@ -64,9 +64,9 @@ constexpr int MAXC = 16;
 // (K = 40: 45 instead of 48 of the 64 buffer slots, and 1 % instead of 4 % of
 // the queries overflow them), but takes twice the distances and a network of
 // twice the registers.  380 x 480, smaller against larger block: lambda 0.01,
-// K = 32 52.6 against 53.9 us, K = 40 60.3 / 60.1 (1000 x 1000: 241 / 249),
-// K = 48 77 / 70; lambda 1, K = 36 52.0 / 55.9, K = 44 53.3 / 57.3, K = 52
-// 92 / 59.
+// K = 32 49.5 against 51.3 us, K = 40 53.7 / 54.1 (1000 x 1000: 205 / 216),
+// K = 48 71 / 64; lambda 1, K = 36 41.0 / 47.5, K = 44 43.7 / 49.6, K = 52
+// 79 / 52.
 constexpr int SMALL_K = 40;
 // A tile of such a K with a bound wider than eight pixels' spatial distance (its
 // K nearest reach far beyond the 8 x 8 block: outliers, about 1 % of the tiles)
