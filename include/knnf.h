@@ -118,9 +118,11 @@ typedef struct knnf_ctx knnf_ctx;
  *                           this search runs a 1-D selection instead when the
  *                           band of 2R + 2 rows (clipped to H) holds at most
  *                           16,384 pixels: the band of two query rows'
- *                           windows is sorted by PC1 value and each query
- *                           walks outward from its own value over its own
- *                           window's pixels; same outputs again.  Its launches
+ *                           windows is sorted by PC1 value and each query's
+ *                           nearest are merged from both sides of its own
+ *                           value (or, where equal distances, few or nearly
+ *                           all of 64 neighbours ask for it, met one by one
+ *                           in a walk outward); same outputs again.  Its launches
  *                           leave the work counters (knnf_stats_*) unchanged.
  */
 typedef enum { KNNF_SEARCH_EXHAUSTIVE = 0, KNNF_SEARCH_PRUNED = 1 } knnf_search;

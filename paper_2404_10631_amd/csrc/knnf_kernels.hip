@@ -1524,9 +1524,11 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     return (b & 7) * per + (b >> 3);
 }
 
-// 8-query tiles are held to 72 VGPRs, seven wavefronts per SIMD: 380 x 480 K=40
-// 52.3 us, 1000 x 1000 210, 1024 frames of 50 x 50 449; six wavefronts 53.6, 218
-// and 472; eight (64 registers, some spilled) 54.4, 212 and 447.  Their 4,832
+// 8-query tiles are held to 72 VGPRs, seven wavefronts per SIMD (those of the
+// persistent kernels spill 18 to 35 of them around the claim loop).  The
+// kernels of the time it was set, side by side: 380 x 480 K=40 52.3 us, 1000 x 1000
+// 210, 1024 frames of 50 x 50 449; six wavefronts 53.6, 218 and 472; eight (64
+// registers, some spilled) 54.4, 212 and 447.  Their 4,832
 // bytes of LDS would allow eight.
 #define KNNF_WAVES_PER_EU(QR, QC) __attribute__((amdgpu_waves_per_eu((QR) * (QC) == 8 ? 7 : 4)))
 

@@ -59,8 +59,9 @@
 // What bounds it: 1000 x 1000 x 100, four classes, 84.5 us (105 us with the
 // lane-per-pixel product): the same kernel without its arithmetic takes 74 us
 // (5.6 TB/s, the rate of a plain read of the cube), the vector pipe is busy
-// for 50 us, and the two overlap only in part.  380 x 480 x 128 fused, 23 us
-// of kernel (27 us with the lane-per-pixel product), 17 us without the arithmetic.
+// for 50 us, and the two overlap only in part.  380 x 480 x 128 fused, 24.4 us
+// of kernel (kernel trace), 15 of them the cube's read at that rate: all its blocks are
+// resident at once, so they load together and then couple together.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
