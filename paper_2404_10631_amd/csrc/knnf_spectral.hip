@@ -253,7 +253,8 @@ __device__ __forceinline__ bool select_queries(const FrameDesc& f, const uint64_
             y[u] = ((uint64_t)(z[u] < NOKEY ? dist0(xq, key_value(key)) : ~0u) << 32) | key_index(key);
         }
         const uint32_t zlast = lane_get(z[7], last);
-        bool tie = l < 7 && ((lane_get(z[0], next) ^ z[7]) < 128u);
+        const uint32_t znext = lane_get(z[0], next);  // by every lane: the last one's is asked for
+        bool tie = l < 7 && ((znext ^ z[7]) < 128u);
 #pragma unroll
         for (int u = 0; u < 7; ++u) tie |= (z[u] ^ z[u + 1]) < 128u;
         if (ballot(tie)) {
